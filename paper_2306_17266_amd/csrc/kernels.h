@@ -71,7 +71,8 @@ enum KernelClass {
     KC_CONV_PATCH = 9,  // conv_patch_kernel (large pixel counts; the input patch of a tile staged in LDS)
     KC_CONV_I8 = 10,    // conv_i8_kernel / conv_i8_direct_kernel (int8 mode)
     KC_I8_OTHER = 11,   // int8 mode: max-pool, pooled sums, classifier
-    KC_COUNT = 12
+    KC_STEM = 12,       // stem_mfma_kernel (bf16: the 3-channel input layer)
+    KC_COUNT = 13
 };
 const char *kernel_class_name(int kc);
 
@@ -84,6 +85,10 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
 // Dense 1x1 (stride 1) and 3x3 (stride 1 or 2) convolution, bf16, C and K multiples of 8, tensors below 2 GiB: the
 // patch kernel (conv_patch.hip).  Returns hipErrorNotSupported (nothing launched) for any other case.
 hipError_t launch_conv_patch(const ConvArgs &a, hipStream_t s);
+
+// 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
+// other case.
+hipError_t launch_stem(const ConvArgs &a, hipStream_t s);
 hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s);
 hipError_t launch_maxpool(const PoolArgs &a, bool bf16, hipStream_t s);   // 3x3 stride 2 pad 1
 hipError_t launch_gap(const PoolArgs &a, bool bf16, hipStream_t s);       // [B][H][W][C] -> [B][C]

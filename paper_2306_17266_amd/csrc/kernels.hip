@@ -26,8 +26,8 @@ void dw_tap_offsets(int t, int *dr, int *ds) {
 hipError_t upload_tap_table() { return hipSuccess; }
 
 // ------------------------------------------------------------------ dense conv, vector ALUs
-// One thread: one output pixel x 4 consecutive filters.  Serves the float32 mode, the 3-channel
-// stem and fully connected layers in float32.  y = act(scale * conv + shift (+ res)).
+// One thread: one output pixel x 4 consecutive filters.  Serves the float32 mode and the input layers that
+// stem_mfma_kernel does not cover.  y = act(scale * conv + shift (+ res)).
 
 template <typename T>
 __global__ __launch_bounds__(256) void conv_direct_kernel(ConvArgs a) {
@@ -604,7 +604,8 @@ const char *kernel_class_name(int kc) {
     static const char *names[KC_COUNT] = {"conv_direct_kernel", "conv_mfma_kernel", "conv_mfma_splitk_kernel",
                                           "dwconv_rows_kernel", "maxpool_kernel",   "gap_kernel",
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
-                                          "conv_patch_kernel",  "conv_i8_kernel",      "int8_pool_fc_kernels"};
+                                          "conv_patch_kernel",  "conv_i8_kernel",      "int8_pool_fc_kernels",
+                                          "stem_mfma_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 
@@ -613,6 +614,13 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
     int dummy;
     if (!kc) kc = &dummy;
     *kc = KC_CONV_DIRECT;
+    if (bf16) {
+        const hipError_t e = launch_stem(a, s);
+        if (e != hipErrorNotSupported) {
+            *kc = KC_STEM;
+            return e;
+        }
+    }
     if (!bf16 || (a.C & 7) != 0) {
         const long total = M * ((a.K + 3) / 4);
         if (bf16)
