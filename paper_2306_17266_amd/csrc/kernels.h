@@ -98,6 +98,10 @@ hipError_t launch_gate(const PoolArgs &a, bool bf16, hipStream_t s);      // y =
 // Returns hipErrorNotSupported (nothing launched) for any other case.
 hipError_t launch_dwconv_rows(const ConvArgs &a, hipStream_t s);
 
+// The same on the matrix cores, kernels 5x5 and 7x7 and small 3x3 layers (dwconv_mfma.hip).  Returns
+// hipErrorNotSupported (nothing launched) for any other case.
+hipError_t launch_dwconv_mfma(const ConvArgs &a, hipStream_t s);
+
 // int8 mode (int8.hip): dense conv 1x1 / 3x3 on the int8 matrix cores (3 input channels: vector ALUs) with integer
 // requantisation, 3x3/2 max-pool on codes, exact int32 pooled sums, int64 classifier with float32 logits.
 hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, long patch_min_pixels);

@@ -662,7 +662,8 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
 hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s) {
     const long total = (long)a.B * a.P * a.Q * (a.K >> 3);
     if (bf16) {
-        const hipError_t e = launch_dwconv_rows(a, s);
+        hipError_t e = launch_dwconv_mfma(a, s);
+        if (e == hipErrorNotSupported) e = launch_dwconv_rows(a, s);
         if (e != hipErrorNotSupported) return e;
     }
     if (bf16)

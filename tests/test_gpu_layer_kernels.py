@@ -52,3 +52,21 @@ def _chain(widths, strides, res, classes=64, channels=3):
 def test_input_layer(res, stride, width, batch):
     arch = _chain([width, 16], [stride, 2], res)
     _check(arch, A.max_cfg(arch), batch, 41, BF16_TOL)
+
+
+def _mobile(expand, kernel, strides, act, res, out=16):
+    """An inverted-residual net of one block per stage: stage widths `out`, one kernel size, no squeeze-excite."""
+    n = len(strides)
+    return dataclasses.replace(A.small_mbv3_arch(), stage_base_out=[out] * n, stage_stride=list(strides), stage_max_depth=[1] * n,
+                               stage_act=[act] * n, stage_se=[0] * n, depth_drop_choices=[0], expand_choices=[float(expand)],
+                               kernel_choices=[kernel], res_choices=[res], stem_out=out)
+
+
+# channel counts of half a group of 16 (24), 40 and 144; maps narrower than a column tile, one column past it (34 -> 17), odd
+# ones; one-row strips (one image) and long strips with a ragged last one (the large batches); both strides
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("expand,strides,res,batch,out", [(3, (1, 2), 8, 1, 8), (1, (2, 1), 34, 1, 40), (3, (1, 2), 30, 2, 48),
+                                                          (3, (1, 2), 46, 24, 48)])
+def test_depthwise(kernel, expand, strides, res, batch, out):
+    arch = _mobile(expand, kernel, strides, A.ACT_HSWISH if kernel == 5 else A.ACT_RELU, res, out)
+    _check(arch, A.max_cfg(arch), batch, 43, 2 * BF16_TOL)  # (twice the layers of the other nets)
