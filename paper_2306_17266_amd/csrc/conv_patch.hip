@@ -37,29 +37,6 @@ typedef __attribute__((ext_vector_type(4))) int cp_i32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned cp_u32x4;
 constexpr int CP_OOB = 0x7FFFFFF0;
 
-// Division of a non-negative int below 2^31 by a fixed divisor d: n / d = mulhi(n, mul) >> shr for d > 1
-// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1.  The host prepares (mul, shr).
-struct FastDiv {
-    unsigned mul, shr;
-    int d;
-};
-
-__host__ inline FastDiv make_fastdiv(int d) {
-    FastDiv f{0u, 0u, d};
-    if (d > 1) {
-        int lg = 0;
-        while ((1ll << lg) < d) ++lg;
-        const int p = 31 + lg;
-        f.mul = (unsigned)(((1ull << p) + (unsigned long long)d - 1) / (unsigned long long)d);
-        f.shr = (unsigned)(p - 32);
-    }
-    return f;
-}
-
-__device__ __forceinline__ int fdiv(int n, const FastDiv &f) {
-    return f.d == 1 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shr);
-}
-
 struct PatchGeom {
     int tiles_f, tiles_m;
     int hp, wp;      // frame: H + 2 pad, W + 2 pad
@@ -516,6 +493,17 @@ hipError_t launch_patch_tf(const ConvArgs &a, int tf, hipStream_t s, const Quant
 
 }  // namespace
 
+// Filters per tile: the tile width (64, 96, 128) that wastes the fewest padded filters, the wider on a tie.
+int conv_patch_tile_filters(int K) {
+    int tf = 4;
+    long waste = -1;
+    for (int t = 4; t >= 2; --t) {
+        const long w = (long)((K + 32 * t - 1) / (32 * t)) * 32 * t - K;
+        if (waste < 0 || w < waste) tf = t, waste = w;
+    }
+    return 32 * tf;
+}
+
 // Returns hipErrorNotSupported (nothing launched) for shapes the patch kernel does not cover.
 hipError_t launch_conv_patch(const ConvArgs &a, hipStream_t s) {
     if (a.in_f32 || a.out_f32 || (a.C & 7) || (a.K & 7) || a.K < 8) return hipErrorNotSupported;
@@ -526,13 +514,7 @@ hipError_t launch_conv_patch(const ConvArgs &a, hipStream_t s) {
     if (M * a.K * 2 >= lim || (long)a.B * a.H * a.W * a.C * 2 >= lim) return hipErrorNotSupported;
     if ((long)a.B * (a.H + 2 * a.pad) * (a.W + 2 * a.pad) >= lim) return hipErrorNotSupported;
     if ((long)a.R * a.R * a.CG * a.Kpad * 16 >= lim) return hipErrorNotSupported;
-    // filters per tile: the tile width (64, 96, 128) that wastes the fewest padded filters, the wider on a tie
-    int tf = 4;
-    long waste = -1;
-    for (int t = 4; t >= 2; --t) {
-        const long w = (long)((a.K + 32 * t - 1) / (32 * t)) * 32 * t - a.K;
-        if (waste < 0 || w < waste) tf = t, waste = w;
-    }
+    const int tf = conv_patch_tile_filters(a.K) / 32;
     if (a.R == 3) {
         if (a.stride == 2) return launch_patch_tf<1, 32, 3, 16, 1, 4>(a, tf, s);
         // 256-pixel tiles (eight waves of 32 pixels: two waves per SIMD get their LDS reads served at twice the
@@ -555,12 +537,7 @@ hipError_t launch_conv_patch_i8(const ConvArgs &a, const QuantArgs &q, hipStream
     if (M * a.K >= lim || (long)a.B * a.H * a.W * a.C >= lim) return hipErrorNotSupported;
     if ((long)a.B * (a.H + 2 * a.pad) * (a.W + 2 * a.pad) >= lim) return hipErrorNotSupported;
     if ((long)a.R * a.R * a.CG * a.Kpad * 16 >= lim) return hipErrorNotSupported;
-    int tf = 4;
-    long waste = -1;
-    for (int t = 4; t >= 2; --t) {
-        const long w = (long)((a.K + 32 * t - 1) / (32 * t)) * 32 * t - a.K;
-        if (waste < 0 || w < waste) tf = t, waste = w;
-    }
+    const int tf = conv_patch_tile_filters(a.K) / 32;
     if (a.R == 3) {
         if (a.stride == 2) return launch_patch_tf<1, 64, 3, 16, 1, 4, true>(a, tf, s, q);
         const long tiles256 = ((M + 255) / 256) * ((a.K + 32 * tf - 1) / (32 * tf));

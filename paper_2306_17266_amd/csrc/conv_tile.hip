@@ -1,0 +1,348 @@
+// Dense 1x1 and 3x3 convolution with few output tiles (late stages of a batch, middle stages of a small one) on the
+// matrix cores: an implicit GEMM whose reduction is split over wave groups INSIDE a workgroup.
+//
+// A workgroup of KS groups of four waves computes 64 filters x 64 consecutive output pixels.  The reduction is
+// one flat sequence of 16-byte cells, k = tap * (cells per tap) + cell, whatever the channel count: no padding to a
+// chunk per tap.  A step is eight cells; group g multiplies steps g * per .. (g + 1) * per - 1 in LDS buffers of its own
+// (two, [cell][row] planes of odd length: neighbouring lanes store the eight cells of one pixel and read 32 rows of one
+// cell, both free of bank conflicts), wave (wf, wm) of a group owning 32 filters x 32 pixels.  The loads of the next
+// two steps are in flight in registers, one barrier per step.  The KS partial tiles then meet in LDS as they were
+// accumulated (32 bits), are added in the order of the groups, and every thread finishes pieces of eight filters of one
+// pixel: 16-byte residual loads and stores, contiguous along the channels.
+//
+// Bound: the serial steps of a workgroup (load latency over two steps, the barrier) and LDS operand reads (a 32 x 32 wave
+// tile reads two bytes per clock of what the matrix core could use one of), so the chip has to be filled with
+// workgroups and each workgroup's chain be short: hence 64 x 64 tiles and the split.
+#include "kernels.h"
+#include "device_common.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace sushi {
+
+typedef __attribute__((ext_vector_type(16))) float ct_f32x16;
+typedef __attribute__((ext_vector_type(16))) int ct_i32x16;
+typedef __attribute__((ext_vector_type(4))) int ct_i32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned ct_u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned ct_u32x2;
+constexpr int CT_OOB = 0x7FFFFFF0;
+constexpr int CT_FAR = 0x40000000;  // added to any offset into the weights (below 1 GiB) it lies past their end
+
+struct TileGeom {
+    int tiles_f, tiles_m;
+    int M;       // B * P * Q
+    int kcells;  // cells of the reduction: taps * cells per tap
+    int per;     // steps (of eight cells) per wave group
+    int part;    // cell offset of the scale / shift (int8: multiplier, shift, bias) copies in LDS
+    FastDiv dq, dp, dcell;  // division by Q, P, cells per tap
+};
+
+template <int KS, int R, bool I8>
+__global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, TileGeom g, QuantArgs q) {
+    constexpr int ES = I8 ? 1 : 2, CPC = 16 / ES;  // bytes per element, channels per cell
+    constexpr int BN = 64, BM = 64, SA = BN + 1, SB = BM + 1, NT = 256 * KS;
+    constexpr int D = 2;  // (with four steps in flight int8 spills and bf16 gains nothing)
+    constexpr int BUF = 8 * (SA + SB);  // cells of one LDS buffer: eight weight planes, eight activation planes
+    constexpr int NB = 2;               // activation cells a thread stages per step (and two weight cells)
+    constexpr int PROW = BN / 4 + 1;    // 16-byte cells per pixel row of a partial tile
+    extern __shared__ uint4 ct_lds[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int grp = __builtin_amdgcn_readfirstlane(tid >> 8), wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
+    const int gt = tid & 255;
+    const int wf = wave >> 1, wm = wave & 1, l32 = lane & 31, kh = lane >> 5;
+    const int ntiles = g.tiles_f * g.tiles_m, per_xcd = (ntiles + 7) >> 3;
+    const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (tile >= ntiles) return;
+    const int tf = tile / g.tiles_m, tm = tile - tf * g.tiles_m;
+    const int f0 = tf * BN, m0 = tm * BM;
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C * ES), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)((long)R * R * a.CG * a.Kpad * 16), 0x00020000);
+
+    // what this thread stages: cell bk of pixels (gt >> 3) + 32 i (byte offset of the pixel's window, one bit per tap
+    // inside the image), weight cells wave and wave + 4 of filter f0 + lane
+    const int bk = gt & 7;
+    int boff[NB];
+    unsigned bmask[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int m = m0 + (gt >> 3) + 32 * i;
+        const bool live = m < g.M;
+        const int t = fdiv(live ? m : 0, g.dq), qq = (live ? m : 0) - t * a.Q;
+        const int n = fdiv(t, g.dp), pp = t - n * a.P;
+        const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
+        boff[i] = ((n * a.H + h0) * a.W + w0) * a.C * ES;
+        bmask[i] = 0;
+        if (R == 1) {
+            bmask[i] = live ? 1u : 0u;
+        } else {
+#pragma unroll
+            for (int tap = 0; tap < R * R; ++tap) {
+                const int h = h0 + tap / R, w = w0 + tap % R;
+                if (live && h >= 0 && h < a.H && w >= 0 && w < a.W) bmask[i] |= 1u << tap;
+            }
+        }
+    }
+    const int woff = f0 + lane < a.Kpad ? (f0 + lane) * 16 : CT_FAR;
+    const int k0 = grp * g.per * 8;  // first cell of this group
+    ct_u32x4 ra[D][2], rb[D][NB];
+    unsigned rin[D];  // int8: bits 0 .. NB - 1: the cell of pixel i holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
+    auto load_step = [&](int s, ct_u32x4 *qa, ct_u32x4 *qb, unsigned &in) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = k0 + s * 8 + wave + 4 * i;
+            const int tap = R == 1 ? 0 : fdiv(k, g.dcell);
+            const int cg = k - tap * g.dcell.d;
+            const int off = k < g.kcells ? (tap * a.CG + cg) * a.Kpad * 16 : CT_FAR;
+            qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + off, 0, 0);
+        }
+        const int k = k0 + s * 8 + bk;
+        const bool live = k < g.kcells;
+        const int tap = R == 1 ? 0 : fdiv(live ? k : 0, g.dcell);
+        const int cg = (live ? k : 0) - tap * g.dcell.d;
+        const int dr = R == 1 ? 0 : (tap * 11) >> 5, ds = tap - dr * R;  // (tap / 3 for tap < 9)
+        const int off = ((dr * a.W + ds) * a.C + cg * CPC) * ES;
+        in = live ? 256u : 0u;
+        if (I8 && cg * CPC + 8 >= a.C) in |= 512u;
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const bool ok = live && (bmask[i] >> tap & 1u);
+            qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? boff[i] + off : CT_OOB, 0, 0);
+            if (I8 && ok) in |= 1u << i;
+        }
+    };
+    // int8: a cell of the frame holds the code of the real value 0 (the input's zero point) in its active channels, the
+    // upper half of a cell that straddles the SubNet's channel count zeros
+    const unsigned zfill = (unsigned)(q.zx & 0xFF) * 0x01010101u;
+    uint4 *const base = ct_lds + grp * 2 * BUF;
+    auto store_step = [&](int buf, const ct_u32x4 *qa, const ct_u32x4 *qb, unsigned in) {
+        uint4 *dst = base + buf * BUF;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dst[(wave + 4 * i) * SA + lane] = __builtin_bit_cast(uint4, qa[i]);
+        dst += 8 * SA + bk * SB + (gt >> 3);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            ct_u32x4 v = qb[i];
+            if (I8) {
+                if ((in & 256u) && !(in >> i & 1u)) v = ct_u32x4{zfill, zfill, zfill, zfill};
+                if (in & 512u) v[2] = 0u, v[3] = 0u;
+            }
+            dst[32 * i] = __builtin_bit_cast(uint4, v);
+        }
+    };
+
+    // The tile's epilogue constants first, then the loads of the first D steps.  Every load below is issued on every
+    // path, also past the last step (those return zeros and store them where nobody reads): a load under a branch
+    // would make the wait for a step's cells a wait for ALL loads in flight.
+    uint4 cst[I8 ? 4 : 2];
+    {
+        auto rsrc = [&](const void *p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, p ? a.K * 4 : 0, 0x00020000); };
+        const void *const src[4] = {I8 ? (const void *)q.qmult : (const void *)a.scale, I8 ? (const void *)q.qshift : (const void *)a.shift, q.qbias, q.wsum};
+#pragma unroll
+        for (int i = 0; i < (I8 ? 4 : 2); ++i)
+            cst[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc(src[i]), (f0 + (tid & 15) * 4) * 4, 0, 0));
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_step(d, ra[d], rb[d], rin[d]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (I8) {  // (the zero-point term goes to the bias: minus z_x times the sum of the active weights)
+        cst[1] = make_uint4(max((int)cst[1].x, 1), max((int)cst[1].y, 1), max((int)cst[1].z, 1), max((int)cst[1].w, 1));  // (filters beyond K: any valid shift)
+        cst[I8 ? 2 : 0].x -= q.zx * cst[I8 ? 3 : 0].x, cst[I8 ? 2 : 0].y -= q.zx * cst[I8 ? 3 : 0].y, cst[I8 ? 2 : 0].z -= q.zx * cst[I8 ? 3 : 0].z, cst[I8 ? 2 : 0].w -= q.zx * cst[I8 ? 3 : 0].w;
+    } else if (!a.scale) {
+        cst[0] = make_uint4(0x3F800000u, 0x3F800000u, 0x3F800000u, 0x3F800000u);
+    }
+    if (tid < BN / 4)
+#pragma unroll
+        for (int i = 0; i < (I8 ? 3 : 2); ++i) ct_lds[g.part + i * (BN / 4) + tid] = cst[i];
+
+    typename std::conditional<I8, ct_i32x16, ct_f32x16>::type acc;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc[k] = 0;
+
+    store_step(0, ra[0], rb[0], rin[0]);
+    __syncthreads();
+    // one step: s is in LDS buffer s & 1, set d took it there and is free; the cells of step s + 1 are in set (d + 1) % D
+    auto step = [&](int s, auto d_tag, auto load_tag) {
+        constexpr int d = decltype(d_tag)::value, dn = (d + 1) % D;
+        const uint4 *wb = base + (s & 1) * BUF, *pb = wb + 8 * SA;
+        Frag fa[4], fb[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            fa[h].u = wb[(2 * h + kh) * SA + wf * 32 + l32];
+            fb[h].u = pb[(2 * h + kh) * SB + wm * 32 + l32];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (decltype(load_tag)::value) load_step(s + D, ra[d], rb[d], rin[d]);
+        store_step((s + 1) & 1, ra[dn], rb[dn], rin[dn]);
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            if constexpr (I8)
+                acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(ct_i32x4, fa[h].u), __builtin_bit_cast(ct_i32x4, fb[h].u), acc, 0, 0, 0);
+            else
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[h].v, fb[h].v, acc, 0, 0, 0);
+        __syncthreads();
+    };
+    using std::integral_constant;
+    int s = 0;
+    for (; s + D <= g.per; s += D) {
+        step(s, integral_constant<int, 0>{}, std::true_type{});
+        step(s + 1, integral_constant<int, 1>{}, std::true_type{});
+    }
+    if (s < g.per) step(s, integral_constant<int, 0>{}, std::false_type{});  // (in flight already)
+
+    // ---- the partial tiles meet: [group][pixel][filter] (32-bit), over the staging buffers (the barrier above has released them)
+    uint4 *const part = ct_lds;
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+        typedef typename std::conditional<I8, ct_i32x4, f32x4_t>::type v4;
+        const v4 v = {acc[4 * jj], acc[4 * jj + 1], acc[4 * jj + 2], acc[4 * jj + 3]};
+        part[(grp * BM + wm * 32 + l32) * PROW + wf * 8 + 2 * jj + kh] = __builtin_bit_cast(uint4, v);
+    }
+    constexpr int PIECES = BM * (BN / 8), EPT = (PIECES + NT - 1) / NT;
+    const int cc = tid & 7, f = f0 + cc * 8;  // (the same eight filters in all of a thread's pieces)
+    const int obytes = (int)((long)g.M * a.K * ES);
+    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.res ? a.res : a.y), 0, obytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(a.y, 0, obytes, 0x00020000);
+    ct_u32x4 res[EPT];
+    int ooff[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int idx = tid + NT * e, m = m0 + (idx >> 3);
+        ooff[e] = idx < PIECES && m < g.M && f < a.K ? (m * a.K + f) * ES : CT_OOB;
+        res[e] = ct_u32x4{0u, 0u, 0u, 0u};
+        if (a.res) {
+            if (I8) {
+                const ct_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rr, ooff[e], 0, 0);
+                res[e][0] = v[0], res[e][1] = v[1];
+            } else {
+                res[e] = __builtin_amdgcn_raw_buffer_load_b128(rr, ooff[e], 0, 0);
+            }
+        }
+    }
+    __syncthreads();
+    const uint4 *const ss = ct_lds + g.part;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int idx = tid + NT * e;
+        if (PIECES % NT != 0 && idx >= PIECES) break;
+        const uint4 *src = part + (idx >> 3) * PROW + 2 * cc;
+        if constexpr (I8) {
+            int v[8] = {};
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const uint4 lo = src[k * BM * PROW], hi = src[k * BM * PROW + 1];
+                v[0] += (int)lo.x, v[1] += (int)lo.y, v[2] += (int)lo.z, v[3] += (int)lo.w;
+                v[4] += (int)hi.x, v[5] += (int)hi.y, v[6] += (int)hi.z, v[7] += (int)hi.w;
+            }
+            const int *mu = reinterpret_cast<const int *>(ss) + cc * 8;
+            const int lo = a.act == 1 ? q.zy : -128;
+            unsigned packed[2] = {0u, 0u};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                long long t = rr64((long long)(v[i] + mu[2 * BN + i]) * (long long)mu[i], mu[BN + i]);
+                if (a.res) t += rr64((long long)((int)(int8_t)(res[e][i >> 2] >> (8 * (i & 3))) - q.z_res) * (long long)q.m_res, q.sh_res);
+                t += q.zy;
+                const int c = (int)(t < lo ? lo : t > 127 ? 127 : t);
+                packed[i >> 2] |= (unsigned)(c & 0xFF) << (8 * (i & 3));
+            }
+            __builtin_amdgcn_raw_buffer_store_b64(ct_u32x2{packed[0], packed[1]}, ry, ooff[e], 0, 0);
+        } else {
+            float v[8] = {};
+#pragma unroll
+            for (int k = 0; k < KS; ++k) {
+                const float4 lo = __builtin_bit_cast(float4, src[k * BM * PROW]), hi = __builtin_bit_cast(float4, src[k * BM * PROW + 1]);
+                v[0] += lo.x, v[1] += lo.y, v[2] += lo.z, v[3] += lo.w;
+                v[4] += hi.x, v[5] += hi.y, v[6] += hi.z, v[7] += hi.w;
+            }
+            const float *sc = reinterpret_cast<const float *>(ss) + cc * 8, *sh = sc + BN;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                v[i] = v[i] * sc[i] + sh[i];
+                if (a.res) v[i] += bf2f(i & 1 ? res[e][i >> 1] >> 16 : res[e][i >> 1] & 0xFFFFu);
+                v[i] = activate(v[i], a.act, a.hsigmoid);
+            }
+            const ct_u32x4 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+            __builtin_amdgcn_raw_buffer_store_b128(o, ry, ooff[e], 0, 0);
+        }
+    }
+}
+
+template <int KS, int R, bool I8>
+static hipError_t launch_tile(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
+    constexpr int BM = 64, BUF = 8 * (65 + BM + 1), CPC = I8 ? 16 : 8;
+    TileGeom g;
+    g.M = a.B * a.P * a.Q;
+    g.tiles_f = (a.K + 63) / 64, g.tiles_m = (g.M + BM - 1) / BM;
+    const int cells = (a.C + CPC - 1) / CPC;
+    g.kcells = R * R * cells;
+    g.per = ((g.kcells + 7) / 8 + KS - 1) / KS;
+    g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells);
+    g.part = std::max(KS * 2 * BUF, KS * BM * 17);
+    const size_t lds = ((size_t)g.part + (I8 ? 48 : 32)) * 16;
+    static_assert((size_t)KS * 2 * BUF * 16 + 768 <= 160 * 1024 && (size_t)KS * BM * 17 * 16 + 768 <= 160 * 1024, "LDS of a compute unit");
+    auto kern = conv_tile_kernel<KS, R, I8>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    const int per_xcd = (g.tiles_m * g.tiles_f + 7) / 8;
+    hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256 * KS), lds, s, a, g, q);
+    return hipGetLastError();
+}
+
+template <bool I8>
+static bool tile_covers(const ConvArgs &a) {
+    const int es = I8 ? 1 : 2;
+    if (a.in_f32 || a.out_f32 || (a.C & 7) || a.C < 8 || (a.K & 7) || a.K < 8) return false;
+    if (!(a.R == 1 || a.R == 3) || a.pad != (a.R - 1) / 2 || a.stride < 1 || a.stride > 2 || a.Rmax != a.R) return false;
+    const long M = (long)a.B * a.P * a.Q, lim = (1l << 31) - 4096;
+    return M * a.K * es < lim && (long)a.B * a.H * a.W * a.C * es < lim && (long)a.R * a.R * a.CG * a.Kpad * 16 < CT_FAR;
+}
+
+// Wave groups per workgroup: a reduction is split where the tiles leave compute units without enough waves and each
+// group still has steps to run (every group costs a partial tile in LDS).  One, two, four groups, bf16, us:
+// 16 x 7 x 7 x 720 3x3 (156 tiles, 102 steps) 39.6 / 27.3 / 23.6; 16 x 14 x 14 x 360 3x3 (294, 51) 27.7 / 25.8 / 29.1;
+// 16 x 14 x 14, 1024 -> 360 (294, 16) 11.5 / 12.2 / 15.7; 28 x 28, 512 -> 176 (39, 8) 6.0 / 5.2 / 6.0.
+template <bool I8>
+static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
+    constexpr int CPC = I8 ? 16 : 8;
+    const long tiles = (((long)a.B * a.P * a.Q + 63) / 64) * ((a.K + 63) / 64);
+    const int steps = (a.R * a.R * ((a.C + CPC - 1) / CPC) + 7) / 8;
+    const int ks = tiles <= 192 && steps >= (I8 ? 16 : 64) ? 4 : (tiles <= 256 && steps >= 4) || (tiles <= 512 && steps >= (I8 ? 6 : 32)) ? 2 : 1;
+    if (a.R == 1)
+        return ks == 4 ? launch_tile<4, 1, I8>(a, q, s) : ks == 2 ? launch_tile<2, 1, I8>(a, q, s) : launch_tile<1, 1, I8>(a, q, s);
+    return ks == 4 ? launch_tile<4, 3, I8>(a, q, s) : ks == 2 ? launch_tile<2, 3, I8>(a, q, s) : launch_tile<1, 3, I8>(a, q, s);
+}
+
+// Which layers.  With few tiles the kernels that give a workgroup one 16-filter tile spread a layer over more compute
+// units: bf16 3 x 14 x 14, 816 -> 208 (40 tiles of 10 pixel rows) 5.8 us there, 6.3 here, but 4 x 7 x 7 x 720 3x3 (48) 30.8
+// against 23.4 and 1 x 28 x 28, 512 -> 176 (39, 784 pixels) 5.6 against 5.2; int8 4 x 7 x 7 x 720 3x3 15.3 against 20.4, but
+// 8 x 7 x 7, 720 -> 2048 (224) 13.3 against 6.3 and 1 x 28 x 28, 176 -> 512 (104, 784 pixels) 6.6 against 4.8.
+// Of the layers that the patch kernel covers as well (patch, stride 1) these stay there:
+//   3x3 with at least 128 of its tiles: one copy of the input serves nine taps (16 x 56 x 56 x 88: 15.6 us there, 26.2
+//       here; with 75 tiles, 16 x 14 x 14 x 360, 33.8 against 25.8);
+//   bf16 1x1 of one step, or of two without a residual: all prologue and epilogue (64 x 112 x 112, 16 -> 96: 54 us there,
+//       110 here; 64 x 14 x 14, 80 -> 480: 8.8 against 10.8; with a residual, 16 x 56 x 56, 88 -> 256: 22.3 against 18.5);
+//   1x1 of many pixels where its tiles pad fewer filters (16 x 56 x 56, 256 -> 88: 11.3 us there, 16.1 here).
+template <bool I8>
+static bool tile_is_faster(const ConvArgs &a, bool patch) {
+    const long M = (long)a.B * a.P * a.Q, tiles = ((M + 63) / 64) * ((a.K + 63) / 64);
+    if (tiles < (M >= 768 ? (I8 ? 72 : 36) : (I8 ? 128 : 44))) return false;
+    if (!patch || a.stride != 1) return true;
+    const int pf = conv_patch_tile_filters(a.K);
+    if (a.R == 3) return ((M + 127) / 128) * ((a.K + pf - 1) / pf) < 128;
+    if (!I8 && (a.C <= 64 || (a.C <= 128 && !a.res))) return false;
+    return M <= 32768 || (a.K + 63) / 64 * 64 <= (a.K + pf - 1) / pf * pf;
+}
+
+hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch) {
+    if (!tile_covers<false>(a) || !tile_is_faster<false>(a, patch)) return hipErrorNotSupported;
+    return launch_tile_ks<false>(a, QuantArgs{}, s);
+}
+
+hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch) {
+    if (!tile_covers<true>(a) || !tile_is_faster<true>(a, patch)) return hipErrorNotSupported;
+    return launch_tile_ks<true>(a, q, s);
+}
+
+}  // namespace sushi

@@ -108,4 +108,27 @@ __device__ __forceinline__ float activate(float v, int act, int hsig) {
     return v;
 }
 
+// Division of a non-negative int below 2^31 by a fixed divisor d: n / d = mulhi(n, mul) >> shr for d > 1
+// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1.  The host prepares (mul, shr).
+struct FastDiv {
+    unsigned mul, shr;
+    int d;
+};
+
+__host__ inline FastDiv make_fastdiv(int d) {
+    FastDiv f{0u, 0u, d};
+    if (d > 1) {
+        int lg = 0;
+        while ((1ll << lg) < d) ++lg;
+        const int p = 31 + lg;
+        f.mul = (unsigned)(((1ull << p) + (unsigned long long)d - 1) / (unsigned long long)d);
+        f.shr = (unsigned)(p - 32);
+    }
+    return f;
+}
+
+__device__ __forceinline__ int fdiv(int n, const FastDiv &f) {
+    return f.d == 1 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shr);
+}
+
 }  // namespace sushi

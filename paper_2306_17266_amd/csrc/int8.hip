@@ -302,8 +302,11 @@ hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, 
     const long M = (long)a.B * a.P * a.Q;
     if ((a.K & 3) || M * a.K >= (1l << 31) - 256 || (long)a.B * a.H * a.W * a.C >= (1l << 31) - 256) return hipErrorInvalidValue;
     if ((long)a.R * a.R * a.CG * a.Kpad * 16 >= (1l << 31) - 256) return hipErrorInvalidValue;
-    if (patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 2048)) {
-        const hipError_t e = launch_conv_patch_i8(a, q, s);
+    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 2048);
+    hipError_t e = launch_conv_tile_i8(a, q, s, patch);
+    if (e != hipErrorNotSupported) return e;
+    if (patch) {
+        e = launch_conv_patch_i8(a, q, s);
         if (e != hipErrorNotSupported) return e;
     }
     if (a.C < 8 || (a.C & 7)) {

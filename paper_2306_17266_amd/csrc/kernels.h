@@ -72,7 +72,8 @@ enum KernelClass {
     KC_CONV_I8 = 10,    // conv_i8_kernel / conv_i8_direct_kernel (int8 mode)
     KC_I8_OTHER = 11,   // int8 mode: max-pool, pooled sums, classifier
     KC_STEM = 12,       // stem_mfma_kernel (bf16: the 3-channel input layer)
-    KC_COUNT = 13
+    KC_CONV_TILE = 13,  // conv_tile_kernel (64-filter tiles, the reduction split over wave groups)
+    KC_COUNT = 14
 };
 const char *kernel_class_name(int kc);
 
@@ -85,6 +86,13 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
 // Dense 1x1 (stride 1) and 3x3 (stride 1 or 2) convolution, bf16, C and K multiples of 8, tensors below 2 GiB: the
 // patch kernel (conv_patch.hip).  Returns hipErrorNotSupported (nothing launched) for any other case.
 hipError_t launch_conv_patch(const ConvArgs &a, hipStream_t s);
+int conv_patch_tile_filters(int K);  // filters of one of its tiles for a layer of K filters
+
+// Dense 1x1 and 3x3 convolution (stride 1 or 2), C and K multiples of 8, few output tiles: the tile kernel
+// (conv_tile.hip).  patch: the patch kernel would take the layer otherwise.  Returns hipErrorNotSupported (nothing
+// launched) for any other case and where another kernel is the faster one.
+hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch);
+hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
 
 // 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
 // other case.

@@ -605,7 +605,7 @@ const char *kernel_class_name(int kc) {
                                           "dwconv_rows_kernel", "maxpool_kernel",   "gap_kernel",
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
                                           "conv_patch_kernel",  "conv_i8_kernel",      "int8_pool_fc_kernels",
-                                          "stem_mfma_kernel"};
+                                          "stem_mfma_kernel",   "conv_tile_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 
@@ -636,14 +636,21 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
         return launch_splitk<1, 1, 4, 1024, true>(a, (a.R * a.R * ((a.C + 31) / 32) + 3) / 4, s);
     }
     // (at the threshold itself only long reductions: short ones are quicker in the kernels below)
-    if (patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 1024)) {
-        const hipError_t e = launch_conv_patch(a, s);
+    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 1024);
+    hipError_t e = launch_conv_tile(a, s, patch);
+    if (e != hipErrorNotSupported) {
+        *kc = KC_CONV_TILE;
+        return e;
+    }
+    if (patch) {
+        e = launch_conv_patch(a, s);
         if (e != hipErrorNotSupported) {
             *kc = KC_CONV_PATCH;
             return e;
         }
     }
-    // Many tiles: LDS-tiled workgroups; the largest tile that still yields two workgroups per compute unit.
+    // What neither covers (a fully connected layer on many images, filter counts that are no multiple of 8): LDS-tiled
+    // workgroups; the largest tile that still yields two workgroups per compute unit.
     *kc = KC_CONV_MFMA;
     if (a.K > 64 && ((M + 127) / 128) * ((a.K + 127) / 128) >= 512) return launch_mfma<128, 128>(a, s);
     if (((M + 127) / 128) * ((a.K + 63) / 64) >= 512) return launch_mfma<64, 128>(a, s);

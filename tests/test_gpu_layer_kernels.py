@@ -70,3 +70,26 @@ def _mobile(expand, kernel, strides, act, res, out=16):
 def test_depthwise(kernel, expand, strides, res, batch, out):
     arch = _mobile(expand, kernel, strides, A.ACT_HSWISH if kernel == 5 else A.ACT_RELU, res, out)
     _check(arch, A.max_cfg(arch), batch, 43, 2 * BF16_TOL)  # (twice the layers of the other nets)
+
+
+def _bottleneck(widths, strides, res, expand, classes=64):
+    """A bottleneck net of two blocks per stage (projection, then a residual from the block's input)."""
+    n = len(widths)
+    return dataclasses.replace(A.small_resnet_arch(), n_classes=classes, stage_base_out=list(widths), stage_stride=list(strides),
+                               stage_max_depth=[2] * n, stage_act=[A.ACT_RELU] * n, stage_se=[0] * n, depth_drop_choices=[0],
+                               width_choices=[1.0], expand_choices=[expand], res_choices=[res])
+
+
+# 60, 44 and 45 tiles of 64 x 64 with ragged pixels and filters; reductions of one step, of an odd number of steps and of 69
+# (split over one, two and four wave groups), not a multiple of a step; 1x1 and 3x3, both strides, with and without a residual;
+# int8: channel counts that are no multiple of a cell of 16, 128 tiles and more
+@pytest.mark.parametrize("arch,batch", [(_chain([24, 200, 72], [1, 1, 2], 15), 6), (_chain([24, 488, 72], [1, 1, 1], 15), 6),
+                                        (_chain([8, 264, 40], [2, 1, 1], 59), 1), (_bottleneck([264, 520], [1, 2], 60, 0.35), 5),
+                                        (_bottleneck([200, 328], [1, 2], 112, 0.2), 9)])
+@pytest.mark.parametrize("int8", [False, True])
+def test_tiled_layers(arch, batch, int8):
+    if int8:
+        from tests.test_gpu_int8 import _check as check_int8
+        check_int8(arch, [A.max_cfg(arch)], 47, batch)
+    else:
+        _check(arch, A.max_cfg(arch), batch, 47, 2 * BF16_TOL)  # (up to fourteen layers)
