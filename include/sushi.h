@@ -386,7 +386,7 @@ typedef enum {
                                    pixels (batch x rows x columns) run in the kernel that stages a tile's input
                                    patch in LDS (large batches); below four times this many only if the layer's
                                    reduction (input channels x taps) is at least 1024 long.  0 = never.
-                                   Default 3136.  In mode 1 it applies to SubNets recorded afterwards */
+                                   Default 3136: there only the layers that it runs fastest.  In mode 1 it applies to SubNets recorded afterwards */
 } sushi_option;
 int sushi_set_option(sushi_ctx *ctx, int option, int64_t value);
 

@@ -303,21 +303,39 @@ static bool tile_covers(const ConvArgs &a) {
 // group still has steps to run (every group costs a partial tile in LDS).  One, two, four groups, bf16, us:
 // 16 x 7 x 7 x 720 3x3 (156 tiles, 102 steps) 39.6 / 27.3 / 23.6; 16 x 14 x 14 x 360 3x3 (294, 51) 27.7 / 25.8 / 29.1;
 // 16 x 14 x 14, 1024 -> 360 (294, 16) 11.5 / 12.2 / 15.7; 28 x 28, 512 -> 176 (39, 8) 6.0 / 5.2 / 6.0.
+static int tile_groups(const ConvArgs &a, bool i8, int *steps) {
+    const int cpc = i8 ? 16 : 8;
+    const long tiles = (((long)a.B * a.P * a.Q + 63) / 64) * ((a.K + 63) / 64);
+    const int n = (a.R * a.R * ((a.C + cpc - 1) / cpc) + 7) / 8;
+    *steps = n;
+    return tiles <= 192 && n >= (i8 ? 16 : 64) ? 4 : (tiles <= 256 && n >= 4) || (tiles <= 512 && n >= (i8 ? 6 : 32)) ? 2 : 1;
+}
+
 template <bool I8>
 static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
-    constexpr int CPC = I8 ? 16 : 8;
-    const long tiles = (((long)a.B * a.P * a.Q + 63) / 64) * ((a.K + 63) / 64);
-    const int steps = (a.R * a.R * ((a.C + CPC - 1) / CPC) + 7) / 8;
-    const int ks = tiles <= 192 && steps >= (I8 ? 16 : 64) ? 4 : (tiles <= 256 && steps >= 4) || (tiles <= 512 && steps >= (I8 ? 6 : 32)) ? 2 : 1;
+    int steps;
+    const int ks = tile_groups(a, I8, &steps);
     if (a.R == 1)
         return ks == 4 ? launch_tile<4, 1, I8>(a, q, s) : ks == 2 ? launch_tile<2, 1, I8>(a, q, s) : launch_tile<1, 1, I8>(a, q, s);
     return ks == 4 ? launch_tile<4, 3, I8>(a, q, s) : ks == 2 ? launch_tile<2, 3, I8>(a, q, s) : launch_tile<1, 3, I8>(a, q, s);
 }
 
-// Which layers.  With few tiles the kernels that give a workgroup one 16-filter tile spread a layer over more compute
-// units: bf16 3 x 14 x 14, 816 -> 208 (40 tiles of 10 pixel rows) 5.8 us there, 6.3 here, but 4 x 7 x 7 x 720 3x3 (48) 30.8
-// against 23.4 and 1 x 28 x 28, 512 -> 176 (39, 784 pixels) 5.6 against 5.2; int8 4 x 7 x 7 x 720 3x3 15.3 against 20.4, but
-// 8 x 7 x 7, 720 -> 2048 (224) 13.3 against 6.3 and 1 x 28 x 28, 176 -> 512 (104, 784 pixels) 6.6 against 4.8.
+// Few pixels: conv_small_kernel's 16 x 16 tiles spread a layer over the chip but re-read its operands per tile, so its time
+// grows with tiles x steps; this kernel's grows with the serial steps of one workgroup.  Fits in us to 45 layer shapes from
+// 1 x 7 x 7 to 32 x 7 x 7 and 1 x 112 x 112 (constants common to both left out): small = W / 6500 (bf16 1x1), W / 8500
+// (bf16 3x3), W / 5000 (int8) with W = 16 x 16 tiles x steps of four cells; tile = 0.4 + steps per group x 0.23, 0.42, 0.75
+// (int8 0.5, 0.75, 1.35) for one, two, four groups, and 1 for 3x3.  On both sides of the line: 2 x 28 x 28 x 176 3x3 9.9 us
+// small, 10.2 tile; 4 x 28 x 28 16.9 and 10.5; 1 x 56 x 56, 208 -> 56 3.5 and 4.5, 208 -> 128 5.3 and 4.5.
+bool conv_small_is_faster(const ConvArgs &a, bool i8) {
+    const double M = (double)a.B * a.P * a.Q;
+    const int cells = a.R * a.R * ((a.C + (i8 ? 15 : 7)) / (i8 ? 16 : 8));
+    const double work = (double)(long)((M + 15) / 16) * ((a.K + 15) / 16) * ((cells + 3) / 4);
+    int steps;
+    const int ks = tile_groups(a, i8, &steps);
+    const double per_step = ks == 1 ? (i8 ? 0.5 : 0.23) : ks == 2 ? (i8 ? 0.75 : 0.42) : (i8 ? 1.35 : 0.75);
+    return work / (i8 ? 5000.0 : a.R == 1 ? 6500.0 : 8500.0) <= 0.4 + (steps + ks - 1) / ks * per_step + (a.R == 3 ? 1.0 : 0.0);
+}
+
 // Of the layers that the patch kernel covers as well (patch, stride 1) these stay there:
 //   3x3 with at least 128 of its tiles: one copy of the input serves nine taps (16 x 56 x 56 x 88: 15.6 us there, 26.2
 //       here; with 75 tiles, 16 x 14 x 14 x 360, 33.8 against 25.8);
@@ -326,8 +344,7 @@ static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStrea
 //   1x1 of many pixels where its tiles pad fewer filters (16 x 56 x 56, 256 -> 88: 11.3 us there, 16.1 here).
 template <bool I8>
 static bool tile_is_faster(const ConvArgs &a, bool patch) {
-    const long M = (long)a.B * a.P * a.Q, tiles = ((M + 63) / 64) * ((a.K + 63) / 64);
-    if (tiles < (M >= 768 ? (I8 ? 72 : 36) : (I8 ? 128 : 44))) return false;
+    const long M = (long)a.B * a.P * a.Q;
     if (!patch || a.stride != 1) return true;
     const int pf = conv_patch_tile_filters(a.K);
     if (a.R == 3) return ((M + 127) / 128) * ((a.K + pf - 1) / pf) < 128;

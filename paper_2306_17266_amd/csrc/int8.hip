@@ -6,11 +6,8 @@
 // Layouts: activations [B][H][W][C] int8, C a multiple of 8 (3 for the network input); weights
 // [tap][channel group of 16][filter, padded to 16][16 channels] int8, channels beyond the layer's width zero.
 //
-// conv_i8_kernel: v_mfma_i32_16x16x64_i8; filters are the rows, pixels the columns.  A lane supplies, for its
-// filter (or pixel) lane & 15, the 16 channels of channel group lane >> 4 of the current 64-channel step: one
-// 16-byte load per operand and step, straight from memory (which channel a lane holds does not matter as long as
-// both operands agree: the instruction sums over all 64).  Zero points: the matrix cores multiply the raw codes,
-// sum w * (x - z_x) = sum w * x - z_x * sum w.  Cells outside the image are filled with the code z_x (the real
+// Dense layers run in conv_small.hip, conv_tile.hip and conv_patch.hip.  Zero points: the matrix cores multiply the raw
+// codes, sum w * (x - z_x) = sum w * x - z_x * sum w.  Cells outside the image are filled with the code z_x (the real
 // value 0), channels beyond the SubNet's width with the code 0, so the correction is z_x times the weight sum
 // over the ACTIVE channels and all taps, which the host has as a prefix table per 8 channels.
 #include "kernels.h"
@@ -19,9 +16,6 @@
 #include <algorithm>
 
 namespace sushi {
-
-typedef __attribute__((ext_vector_type(4))) int i32x4_t;
-constexpr int I8_OOB = 0x7FFFFFF0;
 
 // Requantises four accumulators of consecutive filters f .. f+3 of pixel m and stores four codes.
 __device__ __forceinline__ void store_codes(const ConvArgs &a, const QuantArgs &q, const int acc[4], int f, long m) {
@@ -39,113 +33,6 @@ __device__ __forceinline__ void store_codes(const ConvArgs &a, const QuantArgs &
         packed |= (unsigned)(v & 0xFF) << (8 * i);
     }
     *reinterpret_cast<unsigned *>(static_cast<int8_t *>(a.y) + m * a.K + f) = packed;  // K is a multiple of 4
-}
-
-// A workgroup of four waves computes FT x PT tiles of 16 filters x 16 pixels; the waves split the reduction steps
-// (one tap, 64 channels) among them, each requests the operands of U of its steps before it multiplies them, and
-// the partial sums meet in LDS.  Integer addition is exact in any order, so the split changes no result.
-template <int FT, int PT, int U>
-__global__ __launch_bounds__(256) void conv_i8_kernel(ConvArgs a, QuantArgs q) {
-    __shared__ int red[4][FT * PT][4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int l16 = lane & 15, kg = lane >> 4;
-    const long M = (long)a.B * a.P * a.Q;
-    const int f0 = blockIdx.y * FT * 16;
-    const long m0 = (long)blockIdx.x * PT * 16;
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C), 0x00020000);
-    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<void *>(a.w), 0, (int)((long)a.R * a.R * a.CG * a.Kpad * 16), 0x00020000);
-    int pn[PT], ph[PT], pw[PT];
-    bool pv[PT];
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-        const long m = m0 + pt * 16 + l16;
-        pv[pt] = m < M;
-        const long mm = pv[pt] ? m : 0;
-        const int qq = (int)(mm % a.Q), pp = (int)((mm / a.Q) % a.P);
-        pn[pt] = (int)(mm / ((long)a.Q * a.P));
-        ph[pt] = pp * a.stride - a.pad;
-        pw[pt] = qq * a.stride - a.pad;
-    }
-    int fw[FT];
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft) fw[ft] = (f0 + ft * 16 + l16 < a.Kpad) ? (f0 + ft * 16 + l16) * 16 : -1;
-    const unsigned zfill = (unsigned)(q.zx & 0xFF) * 0x01010101u;
-    i32x4_t acc[FT][PT];
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int pt = 0; pt < PT; ++pt) acc[ft][pt] = i32x4_t{0, 0, 0, 0};
-    const int csteps = (a.C + 63) >> 6;
-    const int nsteps = a.R * a.R * csteps;
-    for (int base = wave; base < nsteps; base += 4 * U) {
-        i32x4_t fa[U][FT], fb[U][PT];
-        bool inside[U][PT];
-        int c0s[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int step = base + 4 * u;
-            const bool live = step < nsteps;
-            const int st = live ? step : 0;
-            const int tap = st / csteps, cs = st - tap * csteps;
-            const int dr = tap / a.R, ds = tap - dr * a.R;
-            const int c0 = cs * 64 + kg * 16;       // this lane's 16 channels
-            const int cg = c0 >> 4;
-            c0s[u] = live ? c0 : a.C;               // (a step beyond the end: treated as channels beyond the SubNet's)
-#pragma unroll
-            for (int ft = 0; ft < FT; ++ft)
-                fa[u][ft] = __builtin_bit_cast(i32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                    rw, live && fw[ft] >= 0 && cg < a.CG ? ((tap * a.CG + cg) * a.Kpad) * 16 + fw[ft] : I8_OOB, 0, 0));
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt) {
-                const int h = ph[pt] + dr, v = pw[pt] + ds;
-                inside[u][pt] = pv[pt] && h >= 0 && h < a.H && v >= 0 && v < a.W;
-                const int off = live && inside[u][pt] && c0 < a.C ? ((pn[pt] * a.H + h) * a.W + v) * a.C + c0 : I8_OOB;
-                fb[u][pt] = __builtin_bit_cast(i32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rx, off, 0, 0));
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int c0 = c0s[u];
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt) {
-                i32x4_t b = fb[u][pt];
-                if (c0 + 8 >= a.C) b[2] = 0, b[3] = 0;        // the cell's upper half lies beyond the active channels
-                if (!inside[u][pt] && c0 < a.C) {               // a cell of the frame: the code of the real value 0
-                    b[0] = (int)zfill, b[1] = (int)zfill;
-                    if (c0 + 8 < a.C) b[2] = (int)zfill, b[3] = (int)zfill;
-                }
-                fb[u][pt] = b;
-            }
-#pragma unroll
-            for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-                for (int pt = 0; pt < PT; ++pt)
-                    acc[ft][pt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(fa[u][ft], fb[u][pt], acc[ft][pt], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[wave][ft * PT + pt][i][lane] = acc[ft][pt][i];
-    __syncthreads();
-    // wave w finishes tiles w, w + 4, ...; the lane holds pixel l16 and filters 4 kg .. 4 kg + 3 of a tile
-    for (int t = wave; t < FT * PT; t += 4) {
-        const int ft = t / PT, pt = t - ft * PT;
-        const int f = f0 + ft * 16 + kg * 4;
-        const long m = m0 + pt * 16 + l16;
-        if (f >= a.K || m >= M) continue;
-        int v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] = red[0][t][i][lane] + red[1][t][i][lane] + red[2][t][i][lane] + red[3][t][i][lane];
-            if (q.zx != 0) v[i] -= q.zx * q.wsum[f + i];
-        }
-        store_codes(a, q, v, f, m);
-    }
 }
 
 // Fewer than 8 input channels (the network input): one thread per output pixel, all filters of a group of up to 32;
@@ -289,37 +176,27 @@ __global__ __launch_bounds__(256) void fc_i8_kernel(ConvArgs a, QuantArgs q) {
 
 static inline unsigned i8_blocks(long total) { return (unsigned)((total + 255) / 256); }
 
-template <int FT, int PT, int U>
-static hipError_t launch_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
-    const long M = (long)a.B * a.P * a.Q;
-    const long n_pgroups = (M + 16 * PT - 1) / (16 * PT);
-    const int n_fgroups = (a.K + 16 * FT - 1) / (16 * FT);
-    hipLaunchKernelGGL((conv_i8_kernel<FT, PT, U>), dim3((unsigned)n_pgroups, n_fgroups), dim3(256), 0, s, a, q);
-    return hipGetLastError();
-}
-
 hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, long patch_min_pixels) {
     const long M = (long)a.B * a.P * a.Q;
     if ((a.K & 3) || M * a.K >= (1l << 31) - 256 || (long)a.B * a.H * a.W * a.C >= (1l << 31) - 256) return hipErrorInvalidValue;
     if ((long)a.R * a.R * a.CG * a.Kpad * 16 >= (1l << 31) - 256) return hipErrorInvalidValue;
-    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 2048);
-    hipError_t e = launch_conv_tile_i8(a, q, s, patch);
-    if (e != hipErrorNotSupported) return e;
-    if (patch) {
-        e = launch_conv_patch_i8(a, q, s);
-        if (e != hipErrorNotSupported) return e;
-    }
     if (a.C < 8 || (a.C & 7)) {
         if (a.C > 4 || a.R * a.R > 49) return hipErrorInvalidValue;
         hipLaunchKernelGGL(conv_i8_direct_kernel, dim3(i8_blocks(M), (unsigned)((a.K + 31) / 32)), dim3(256), 0, s, a, q);
         return hipGetLastError();
     }
-    // more tiles per workgroup where that still leaves every compute unit about two workgroups
-    const long tiles = ((M + 15) / 16) * ((a.K + 15) / 16);
-    if (tiles >= 8 * 512 && a.K > 16) return launch_i8<2, 4, 2>(a, q, s);
-    if (tiles >= 4 * 512) return launch_i8<1, 4, 4>(a, q, s);
-    if (tiles >= 2 * 512) return launch_i8<1, 2, 4>(a, q, s);
-    return launch_i8<1, 1, 4>(a, q, s);
+    const bool chosen = patch_min_pixels != PATCH_MIN_PIXELS;  // (by the caller: then it decides by itself)
+    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 2048);
+    hipError_t e = chosen && patch ? launch_conv_patch_i8(a, q, s) : hipErrorNotSupported;
+    if (e != hipErrorNotSupported) return e;
+    if (conv_small_is_faster(a, true)) return launch_conv_small_i8(a, q, s);
+    e = launch_conv_tile_i8(a, q, s, patch && !chosen);
+    if (e != hipErrorNotSupported) return e;
+    if (patch && !chosen) {
+        e = launch_conv_patch_i8(a, q, s);
+        if (e != hipErrorNotSupported) return e;
+    }
+    return launch_conv_small_i8(a, q, s);
 }
 
 hipError_t launch_fc_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {

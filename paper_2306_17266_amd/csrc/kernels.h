@@ -61,7 +61,7 @@ struct PoolArgs {
 enum KernelClass {
     KC_CONV_DIRECT = 0,   // conv_direct_kernel
     KC_CONV_MFMA = 1,     // conv_mfma_kernel (whole-reduction waves)
-    KC_CONV_SPLITK = 2,   // conv_mfma_splitk_kernel
+    KC_CONV_SMALL = 2,    // conv_small_kernel
     KC_DWCONV = 3,
     KC_MAXPOOL = 4,
     KC_GAP = 5,
@@ -69,7 +69,7 @@ enum KernelClass {
     KC_STREAM = 7,  // sushi_stream_kernel (one launch per query)
     KC_TEAM = 8,    // sushi_team_kernel (persistent; one launch serves many queries)
     KC_CONV_PATCH = 9,  // conv_patch_kernel (large pixel counts; the input patch of a tile staged in LDS)
-    KC_CONV_I8 = 10,    // conv_i8_kernel / conv_i8_direct_kernel (int8 mode)
+    KC_CONV_I8 = 10,    // dense layers of the int8 mode
     KC_I8_OTHER = 11,   // int8 mode: max-pool, pooled sums, classifier
     KC_STEM = 12,       // stem_mfma_kernel (bf16: the 3-channel input layer)
     KC_CONV_TILE = 13,  // conv_tile_kernel (64-filter tiles, the reduction split over wave groups)
@@ -80,7 +80,8 @@ const char *kernel_class_name(int kc);
 // Every launcher returns hipSuccess or the launch error.  bf16 = activations and weights are bf16.
 // launch_conv reports the kernel family it picked in *kc (may be null).
 // patch_min_pixels: dense 1x1 / 3x3 layers with at least that many output pixels (B * P * Q) go to the patch
-// kernel (conv_patch.hip) where it covers the shape; 0 = never.
+// kernel (conv_patch.hip) where it covers the shape; 0 = never; at the default only where it is the fastest.
+constexpr long PATCH_MIN_PIXELS = 3136;
 hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels);  // dense conv and FC
 
 // Dense 1x1 (stride 1) and 3x3 (stride 1 or 2) convolution, bf16, C and K multiples of 8, tensors below 2 GiB: the
@@ -88,11 +89,18 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
 hipError_t launch_conv_patch(const ConvArgs &a, hipStream_t s);
 int conv_patch_tile_filters(int K);  // filters of one of its tiles for a layer of K filters
 
-// Dense 1x1 and 3x3 convolution (stride 1 or 2), C and K multiples of 8, few output tiles: the tile kernel
+// Dense 1x1 and 3x3 convolution (stride 1 or 2), C and K multiples of 8, tensors below 2 GiB: the tile kernel
 // (conv_tile.hip).  patch: the patch kernel would take the layer otherwise.  Returns hipErrorNotSupported (nothing
 // launched) for any other case and where another kernel is the faster one.
 hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch);
 hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
+
+// Dense convolution of few pixels and fully connected layers, C a multiple of 8 (conv_small.hip).  bf16 and float32:
+// return hipErrorNotSupported (nothing launched) for tensors of 2 GiB and more.
+hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s);
+hipError_t launch_conv_small_f32(const ConvArgs &a, hipStream_t s);  // the float32 mode
+hipError_t launch_conv_small_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s);
+bool conv_small_is_faster(const ConvArgs &a, bool i8);  // than the tile kernel (conv_tile.hip)
 
 // 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
 // other case.

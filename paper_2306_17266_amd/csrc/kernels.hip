@@ -26,8 +26,8 @@ void dw_tap_offsets(int t, int *dr, int *ds) {
 hipError_t upload_tap_table() { return hipSuccess; }
 
 // ------------------------------------------------------------------ dense conv, vector ALUs
-// One thread: one output pixel x 4 consecutive filters.  Serves the float32 mode and the input layers that
-// stem_mfma_kernel does not cover.  y = act(scale * conv + shift (+ res)).
+// One thread: one output pixel x 4 consecutive filters.  Serves the input layers of the float32 mode and those that
+// stem_mfma_kernel does not cover, and float32 tensors of 2 GiB and more.  y = act(scale * conv + shift (+ res)).
 
 template <typename T>
 __global__ __launch_bounds__(256) void conv_direct_kernel(ConvArgs a) {
@@ -272,141 +272,6 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a, int tiles_f,
         }
 }
 
-// Small problems (batch-1 layers, FC): latency decides, so the reduction is split over the WK waves
-// of the workgroup (WK = blockDim.x / 64, chosen by the host), every wave issues the loads of U steps
-// before the first MFMA, and the partial sums are added in a fixed order through LDS.  One
-// workgroup computes FT x PT tiles.  Loads are unconditional (addresses clamped into the tensor);
-// masked activations are zeroed afterwards, which also covers the spatial zero padding.
-// IN32: the input is a float32 vector per image (H = W = 1): every value is split into two bf16 terms,
-// x = hi + lo with hi = bf16(x) and lo = bf16(x - hi), and both are multiplied with the same weight fragment, so
-// the product carries about 16 bits of the input's mantissa instead of 8.
-template <int FT, int PT, int U, int MAXT, bool IN32 = false>
-__global__ __launch_bounds__(MAXT) void conv_mfma_splitk_kernel(ConvArgs a) {
-    extern __shared__ float red[];  // [WK][FT*PT][4][64]
-    const int WK = blockDim.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int wk = threadIdx.x >> 6;
-    const int l16 = lane & 15, kg = lane >> 4;
-    const int M = a.B * a.P * a.Q;
-    const int n_pgroups = (M + 16 * PT - 1) / (16 * PT);
-    const int pgroup = blockIdx.x % n_pgroups, ftile = blockIdx.x / n_pgroups;
-    const int f0 = ftile * FT * 16;
-    const int m0 = pgroup * PT * 16;
-    const uint16_t *x = static_cast<const uint16_t *>(a.x);
-    const uint16_t *w = static_cast<const uint16_t *>(a.w);
-
-    int pn[PT], ph[PT], pw[PT];
-    bool pv[PT];
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-        const int m = m0 + pt * 16 + l16;
-        pv[pt] = m < M;
-        const int mm = pv[pt] ? m : 0;
-        const int qq = mm % a.Q, pp = (mm / a.Q) % a.P;
-        pn[pt] = mm / (a.Q * a.P);
-        ph[pt] = pp * a.stride - a.pad;
-        pw[pt] = qq * a.stride - a.pad;
-    }
-    int fw[FT];
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft) fw[ft] = min(f0 + ft * 16 + l16, a.Kpad - 1) * 8;
-
-    f32x4_t acc[FT][PT];
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int pt = 0; pt < PT; ++pt) acc[ft][pt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    const int csteps = (a.C + 31) >> 5;
-    const int nsteps = a.R * a.R * csteps;
-    for (int base = wk; base < nsteps; base += WK * U) {
-        Frag fa[U][FT], fb[U][PT];
-        Frag fb2[IN32 ? U : 1][IN32 ? PT : 1];  // IN32: the second four floats of the lane's eight
-        bool ok[U][PT];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int step = base + u * WK;
-            const bool live = step < nsteps;
-            const int st = live ? step : 0;
-            const int tap = st / csteps;
-            const int c0 = (st - tap * csteps) * 32 + kg * 8;
-            const int dr = tap / a.R, ds = tap - dr * a.R;
-            const bool cv = live && c0 < a.C;
-            const int cc = cv ? c0 : 0;
-            const uint16_t *wp = w + ((long)tap * a.CG + (cc >> 3)) * a.Kpad * 8;
-#pragma unroll
-            for (int ft = 0; ft < FT; ++ft) fa[u][ft].u = *reinterpret_cast<const uint4 *>(wp + fw[ft]);
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt) {
-                const int h = ph[pt] + dr, v = pw[pt] + ds;
-                ok[u][pt] = cv && pv[pt] && h >= 0 && h < a.H && v >= 0 && v < a.W;
-                const int hh = ok[u][pt] ? h : 0, vv = ok[u][pt] ? v : 0;
-                const long e0 = (((long)pn[pt] * a.H + hh) * a.W + vv) * a.C + cc;
-                if (IN32) {
-                    const float *xf = static_cast<const float *>(a.x) + e0;
-                    fb[u][pt].u = *reinterpret_cast<const uint4 *>(xf);
-                    fb2[IN32 ? u : 0][IN32 ? pt : 0].u = *reinterpret_cast<const uint4 *>(xf + 4);
-                } else {
-                    fb[u][pt].u = *reinterpret_cast<const uint4 *>(x + e0);
-                }
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt)
-                if (!ok[u][pt]) {
-                    fb[u][pt].u = make_uint4(0, 0, 0, 0);
-                    if (IN32) fb2[IN32 ? u : 0][IN32 ? pt : 0].u = make_uint4(0, 0, 0, 0);
-                }
-            if (IN32) {
-#pragma unroll
-                for (int pt = 0; pt < PT; ++pt) {
-                    Frag hi, lo;
-                    split_f32x8(fb[u][pt].u, fb2[IN32 ? u : 0][IN32 ? pt : 0].u, &hi.u, &lo.u);
-#pragma unroll
-                    for (int ft = 0; ft < FT; ++ft) {
-                        acc[ft][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][ft].v, hi.v, acc[ft][pt], 0, 0, 0);
-                        acc[ft][pt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][ft].v, lo.v, acc[ft][pt], 0, 0, 0);
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-                    for (int pt = 0; pt < PT; ++pt)
-                        acc[ft][pt] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u][ft].v, fb[u][pt].v, acc[ft][pt], 0, 0, 0);
-            }
-        }
-    }
-
-    if (WK == 1) {
-#pragma unroll
-        for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-            for (int pt = 0; pt < PT; ++pt) store_tile(a, acc[ft][pt], f0 + ft * 16 + kg * 4, m0 + pt * 16 + l16, M);
-        return;
-    }
-    constexpr int NT = FT * PT;
-#pragma unroll
-    for (int ft = 0; ft < FT; ++ft)
-#pragma unroll
-        for (int pt = 0; pt < PT; ++pt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) red[((wk * NT + ft * PT + pt) * 4 + i) * 64 + lane] = acc[ft][pt][i];
-    __syncthreads();
-    // wave t finishes tile t: partial sums of wave 0, 1, ... in that order
-    for (int t = wk; t < NT; t += WK) {
-        f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < WK; ++k)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s[i] += red[((k * NT + t) * 4 + i) * 64 + lane];
-        const int ft = t / PT, pt = t - ft * PT;
-        store_tile(a, s, f0 + ft * 16 + kg * 4, m0 + pt * 16 + l16, M);
-    }
-}
-
 // ------------------------------------------------------------------ depthwise k x k
 // One thread: one output pixel x 8 channels, taps in ring order (prefix of the stored 7x7).
 
@@ -589,19 +454,8 @@ static hipError_t launch_mfma(const ConvArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int FT, int PT, int U, int MAXT, bool IN32 = false>
-static hipError_t launch_splitk(const ConvArgs &a, int wk, hipStream_t s) {
-    const int M = a.B * a.P * a.Q;
-    const int n_pgroups = (M + 16 * PT - 1) / (16 * PT);
-    const int n_ftiles = (a.K + 16 * FT - 1) / (16 * FT);
-    wk = std::max(1, std::min(wk, MAXT / 64));
-    const size_t lds = wk > 1 ? (size_t)wk * FT * PT * 256 * sizeof(float) : 0;
-    hipLaunchKernelGGL((conv_mfma_splitk_kernel<FT, PT, U, MAXT, IN32>), dim3(n_pgroups * n_ftiles), dim3(64 * wk), lds, s, a);
-    return hipGetLastError();
-}
-
 const char *kernel_class_name(int kc) {
-    static const char *names[KC_COUNT] = {"conv_direct_kernel", "conv_mfma_kernel", "conv_mfma_splitk_kernel",
+    static const char *names[KC_COUNT] = {"conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel",
                                           "dwconv_rows_kernel", "maxpool_kernel",   "gap_kernel",
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
                                           "conv_patch_kernel",  "conv_i8_kernel",      "int8_pool_fc_kernels",
@@ -621,6 +475,14 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
             return e;
         }
     }
+    if (!bf16) {
+        // (1 x 32 x 32 x 32 3x3: 37 us on the vector ALUs, one thread's 288 serial loads; here 5)
+        const hipError_t e = launch_conv_small_f32(a, s);
+        if (e != hipErrorNotSupported) {
+            *kc = KC_CONV_SMALL;
+            return e;
+        }
+    }
     if (!bf16 || (a.C & 7) != 0) {
         const long total = M * ((a.K + 3) / 4);
         if (bf16)
@@ -629,41 +491,36 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
             hipLaunchKernelGGL(conv_direct_kernel<float>, dim3(blocks_for(total)), dim3(256), 0, s, a);
         return hipGetLastError();
     }
-    const long ptiles = (M + 15) / 16, ftiles = (a.K + 15) / 16;
-    if (a.in_f32) {  // a float32 vector per image (fully connected layers): always the latency-oriented kernel
-        if (a.H * a.W != 1) return hipErrorInvalidValue;
-        *kc = KC_CONV_SPLITK;
-        return launch_splitk<1, 1, 4, 1024, true>(a, (a.R * a.R * ((a.C + 31) / 32) + 3) / 4, s);
+    if (a.in_f32) {  // a float32 vector per image (fully connected layers)
+        *kc = KC_CONV_SMALL;
+        return launch_conv_small(a, s);
     }
-    // (at the threshold itself only long reductions: short ones are quicker in the kernels below)
+    // A threshold set by the caller decides by itself; under the default the measured rules of the other kernels come first.
+    // (At the threshold only long reductions: short ones are quicker in the tile kernel.)
+    const bool chosen = patch_min_pixels != PATCH_MIN_PIXELS;
     const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 1024);
-    hipError_t e = launch_conv_tile(a, s, patch);
-    if (e != hipErrorNotSupported) {
-        *kc = KC_CONV_TILE;
+    auto picked = [&](hipError_t e, int family) {
+        if (e != hipErrorNotSupported) *kc = family;
         return e;
-    }
-    if (patch) {
-        e = launch_conv_patch(a, s);
-        if (e != hipErrorNotSupported) {
-            *kc = KC_CONV_PATCH;
-            return e;
-        }
-    }
-    // What neither covers (a fully connected layer on many images, filter counts that are no multiple of 8): LDS-tiled
-    // workgroups; the largest tile that still yields two workgroups per compute unit.
+    };
+    hipError_t e = chosen && patch ? picked(launch_conv_patch(a, s), KC_CONV_PATCH) : hipErrorNotSupported;
+    if (e == hipErrorNotSupported && conv_small_is_faster(a, false)) e = picked(launch_conv_small(a, s), KC_CONV_SMALL);
+    if (e == hipErrorNotSupported) e = picked(launch_conv_tile(a, s, patch && !chosen), KC_CONV_TILE);
+    if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch(a, s), KC_CONV_PATCH);
+    if (e != hipErrorNotSupported) return e;
+    // What none of them covers (tensors of 2 GiB and more, filter counts that are no multiple of 8): LDS-tiled workgroups,
+    // the largest tile that still yields two workgroups per compute unit; few tiles as above.
     *kc = KC_CONV_MFMA;
     if (a.K > 64 && ((M + 127) / 128) * ((a.K + 127) / 128) >= 512) return launch_mfma<128, 128>(a, s);
     if (((M + 127) / 128) * ((a.K + 63) / 64) >= 512) return launch_mfma<64, 128>(a, s);
-    if (((M + 63) / 64) * ((a.K + 63) / 64) >= 384) return launch_mfma<64, 64>(a, s);
-    *kc = KC_CONV_SPLITK;
-    // Few tiles: the widest pixel group that still leaves about one workgroup per compute unit, and
-    // about four reduction steps per wave.
-    const int nsteps = a.R * a.R * ((a.C + 31) / 32);
-    const int wk = (nsteps + 3) / 4;
-    if (ftiles * ((ptiles + 3) / 4) >= 256) return launch_splitk<1, 4, 4, 512>(a, wk, s);
-    if (ftiles * ((ptiles + 1) / 2) >= 256 || ptiles == 2) return launch_splitk<1, 2, 4, 1024>(a, wk, s);
-    if (ptiles >= 3 && ptiles <= 4) return launch_splitk<1, 4, 4, 512>(a, wk, s);
-    return launch_splitk<1, 1, 4, 1024>(a, wk, s);
+    if (((M + 63) / 64) * ((a.K + 63) / 64) < 384) {
+        e = launch_conv_small(a, s);
+        if (e != hipErrorNotSupported) {
+            *kc = KC_CONV_SMALL;
+            return e;
+        }
+    }
+    return launch_mfma<64, 64>(a, s);
 }
 
 hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s) {

@@ -118,8 +118,8 @@ def report_from_trace(args, arch, cfg, batch):
 
     import paper_2306_17266_amd as S
     ops = S.sushi_team_plan(arch, cfg, batch, 32)
-    mine = ("conv_i8_kernel", "conv_i8_direct_kernel", "maxpool_i8_kernel", "gap_i8_kernel", "fc_i8_kernel",
-            "conv_direct_kernel", "conv_mfma_kernel", "conv_mfma_splitk_kernel", "conv_patch_kernel", "dwconv_kernel",
+    mine = ("conv_i8_direct_kernel", "maxpool_i8_kernel", "gap_i8_kernel", "fc_i8_kernel",
+            "conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel", "conv_tile_kernel", "stem_mfma_kernel", "dw_mfma_kernel", "conv_patch_kernel", "dwconv_kernel",
             "dwconv_rows_kernel", "maxpool_kernel", "gap_kernel", "gate_kernel")
     rows = []
     for r in csv.DictReader(open(args.from_trace)):

@@ -93,3 +93,17 @@ def test_tiled_layers(arch, batch, int8):
         check_int8(arch, [A.max_cfg(arch)], 47, batch)
     else:
         _check(arch, A.max_cfg(arch), batch, 47, 2 * BF16_TOL)  # (up to fourteen layers)
+
+
+# reductions of less than a step, of less than a round, of several rounds with a ragged last one and of 194 steps (16 waves);
+# pixel tiles of one to 16 pixels, both strides, residuals; a classifier whose class count is no multiple of 4; int8: cells
+# that straddle the channel count
+@pytest.mark.parametrize("arch,batch", [(_chain([8, 24, 200], [1, 2, 1], 9, 10), 1), (_chain([40, 688, 24], [2, 1, 1], 11, 37), 1),
+                                        (_bottleneck([208, 328], [1, 2], 60, 0.35), 1), (_bottleneck([72, 136], [1, 2], 44, 0.2), 3)])
+@pytest.mark.parametrize("dtype", ["bf16", "int8", "fp32"])
+def test_few_pixels(arch, batch, dtype):
+    if dtype == "fp32":
+        # float32 sums of up to 6192 products against float64: 2^-24 per addition, at random 2^-24 sqrt(6192) = 4.7e-6
+        _check(arch, A.max_cfg(arch), batch, 47, 1e-5, False)
+    else:
+        test_tiled_layers(arch, batch, dtype == "int8")
