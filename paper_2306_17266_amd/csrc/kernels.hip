@@ -359,11 +359,18 @@ __global__ __launch_bounds__(256) void gap_kernel(PoolArgs a) {
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
     if (cg < cgs) {
         const T *x = static_cast<const T *>(a.x) + (long)n * hw * a.C + cg * 8;
-        for (int p = pl; p < hw; p += 32) {
-            float xv[8];
-            load8(x + (long)p * a.C, xv);
+        // eight pixels' loads in flight at a time (one by one, 28 x 28 x 240 waited out 25 loads in sequence: 11.6 us at 64
+        // images), added in the same order
+        constexpr int U = 8;
+        for (int p = pl; p < hw; p += 32 * U) {
+            float xv[U][8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] += xv[j];
+            for (int u = 0; u < U; ++u) load8(x + (long)min(p + 32 * u, hw - 1) * a.C, xv[u]);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (p + 32 * u < hw)
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc[j] += xv[u][j];
         }
     }
 #pragma unroll
