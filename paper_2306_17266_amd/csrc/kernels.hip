@@ -46,6 +46,32 @@ __global__ __launch_bounds__(256) void conv_direct_kernel(ConvArgs a) {
     const int cgs = (a.C + 7) >> 3;
     const bool vec = (a.C & 7) == 0;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.R == 3 && a.C == 3) {
+        // The input layer: its 27 values are requested at once (from clamped positions, values outside the image are not
+        // added); tap by tap they were 27 round trips, 1 x 32 x 32 x 32 13 us.  Same order of the sums.
+        float xv[27];
+        unsigned inside = 0;
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            const int h = pp * a.stride - a.pad + tap / 3, v = qq * a.stride - a.pad + tap % 3;
+            if (h >= 0 && h < a.H && v >= 0 && v < a.W) inside |= 1u << tap;
+            const T *xp = x + (((long)n * a.H + min(max(h, 0), a.H - 1)) * a.W + min(max(v, 0), a.W - 1)) * 3;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) xv[tap * 3 + j] = ld1(xp + j);
+        }
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+            const T *wp = w + ((long)tap * a.CG * a.Kpad + fb) * 8;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float wv[8], sum = acc[i];
+                load8(wp + i * 8, wv);
+#pragma unroll
+                for (int j = 0; j < 3; ++j) sum = fmaf(wv[j], xv[tap * 3 + j], sum);
+                acc[i] = inside >> tap & 1u ? sum : acc[i];
+            }
+        }
+    } else
     for (int tap = 0; tap < a.R * a.R; ++tap) {
         const int h = pp * a.stride - a.pad + tap / a.R;
         const int v = qq * a.stride - a.pad + tap % a.R;
