@@ -17,8 +17,11 @@
 // write whole cache lines.
 //
 // Bound by the first loads on small maps; on large ones by the matrix cores to about a half (64 x 56 x 56 x 144, 7x7:
-// 50 us, of them 24 matrix instructions).  Zero times infinity is not zero: an
-// infinity or NaN in one channel of a group reaches the other channels of the group at the same outputs.
+// 50 us, of them 24 matrix instructions).
+//
+// Zero times infinity is not zero: an infinity or NaN in one channel makes the sums of its whole group NaN at the outputs
+// that use it.  Sums that are not finite are therefore computed again channel by channel on the vector ALUs, so channels
+// stay apart; finite sums cannot have met such a value.
 #include "kernels.h"
 #include "device_common.h"
 
@@ -132,14 +135,38 @@ __global__ __launch_bounds__(256, 2) void dw_mfma_kernel(ConvArgs a, DwTasks t) 
                 }
             __builtin_amdgcn_sched_barrier(0);
         }
+        const int f = c0 + kg * 4;
+        const bool mine = q < a.Q && f < a.K;
+        auto finish = [&](int p, float s0, float s1, float s2, float s3) {
+            const float v0 = activate(s0 * sc.x + sh.x, a.act, 0), v1 = activate(s1 * sc.y + sh.y, a.act, 0);
+            const float v2 = activate(s2 * sc.z + sh.z, a.act, 0), v3 = activate(s3 * sc.w + sh.w, a.act, 0);
+            *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.y) + (((long)n * a.P + p) * a.Q + q) * a.K + f) =
+                make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+        };
+        float bad = 0.f;  // NaN if one of the lane's sums is not finite
 #pragma unroll
         for (int j = 0; j < T; ++j)
-            if (p0 + j < a.P && q < a.Q && c0 + kg * 4 < a.K) {
-                const float v0 = activate(acc[j][0] * sc.x + sh.x, a.act, 0), v1 = activate(acc[j][1] * sc.y + sh.y, a.act, 0);
-                const float v2 = activate(acc[j][2] * sc.z + sh.z, a.act, 0), v3 = activate(acc[j][3] * sc.w + sh.w, a.act, 0);
-                *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.y) + (((long)n * a.P + p0 + j) * a.Q + q) * a.K + c0 + kg * 4) =
-                    make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+            if (mine && p0 + j < a.P) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) bad = fmaf(acc[j][i], 0.f, bad);
+                finish(p0 + j, acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
             }
+        // (channel by channel, cells outside the image as zeros)
+#pragma unroll 1
+        for (int p = bad == bad ? a.P : p0; p < min(p0 + T, a.P); ++p) {
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+            for (int k = 0; k < R * R; ++k) {
+                const int dr = k / R - HALF, ds = k % R - HALF, h = p * S + dr, x = q * S + ds;
+                const uint2 wv = *reinterpret_cast<const uint2 *>(w + dw_tap_index(dr, ds) * a.Kpad + f);
+                uint2 xv = make_uint2(0u, 0u);
+                if (h >= 0 && h < a.H && x >= 0 && x < a.W)
+                    xv = *reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(a.x) + (((long)n * a.H + h) * a.W + x) * a.C + f);
+                s[0] = fmaf(bf2f(wv.x & 0xFFFFu), bf2f(xv.x & 0xFFFFu), s[0]), s[1] = fmaf(bf2f(wv.x >> 16), bf2f(xv.x >> 16), s[1]);
+                s[2] = fmaf(bf2f(wv.y & 0xFFFFu), bf2f(xv.y & 0xFFFFu), s[2]), s[3] = fmaf(bf2f(wv.y >> 16), bf2f(xv.y >> 16), s[3]);
+            }
+            finish(p, s[0], s[1], s[2], s[3]);
+        }
     }
 }
 

@@ -72,6 +72,38 @@ def test_depthwise(kernel, expand, strides, res, batch, out):
     _check(arch, A.max_cfg(arch), batch, 43, 2 * BF16_TOL)  # (twice the layers of the other nets)
 
 
+# A channel whose expanded values overflow to infinity and whose depthwise weights are all negative: minus infinity, which
+# ReLU makes 0.  The other channels must be what they are with that channel's map at 0.
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("strides,res,batch", [((1, 2), 8, 1), ((2, 1), 46, 24)])
+def test_depthwise_keeps_channels_apart(kernel, strides, res, batch):
+    import paper_2306_17266_amd as S
+    arch = _mobile(1, kernel, strides, A.ACT_RELU, res, 40)
+    cfg = A.max_cfg(arch)
+    table = S.sushi_describe_supernet(arch)
+    got = []
+    for scale in (3e38, 0.0):
+        tens = T.make_weights([(s, k) for _, s, k in table], 53, True)
+        for (name, _, _), t in zip(table, tens):
+            for block in ("s0b0.", "s1b0."):
+                if name == block + "expand.scale":
+                    t[[5, 38]] = scale
+                elif name in (block + "expand.shift", block + "dw.shift"):
+                    t[[5, 38]] = 0.0
+                elif name == block + "dw.w":
+                    t[[5, 38]] = -np.abs(t[[5, 38]]) - 0.01
+        ctx = S.Sushi(0)
+        ctx.sushi_load_supernet(arch, T.flatten(tens), S.BF16)
+        x = torch.from_numpy(T.make_input(53, 0, batch, cfg.resolution, arch.in_channels, True)).cuda().to(torch.bfloat16)
+        logits = torch.full((batch, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32)
+        ctx.sushi_infer(cfg, x, logits)
+        torch.cuda.synchronize()
+        ctx.close()
+        got.append(logits.cpu().numpy())
+    for n in range(batch):
+        assert rel_l2(got[0][n], got[1][n]) <= 2 * BF16_TOL, n
+
+
 def _bottleneck(widths, strides, res, expand, classes=64):
     """A bottleneck net of two blocks per stage (projection, then a residual from the block's input)."""
     n = len(widths)
