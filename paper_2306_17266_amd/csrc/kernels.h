@@ -82,7 +82,9 @@ const char *kernel_class_name(int kc);
 // patch_min_pixels: dense 1x1 / 3x3 layers with at least that many output pixels (B * P * Q) go to the patch
 // kernel (conv_patch.hip) where it covers the shape; 0 = never; at the default only where it is the fastest.
 constexpr long PATCH_MIN_PIXELS = 3136;
-hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels);  // dense conv and FC
+// finite_w: the layer's weights are all finite; if not, float32 layers and the input layer run in the kernel that skips
+// taps outside the image (in the others zero meets the tap's weight, and zero times infinity is NaN).
+hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w);  // dense conv and FC
 
 // Dense 1x1 (stride 1) and 3x3 (stride 1 or 2) convolution, bf16, C and K multiples of 8, tensors below 2 GiB: the
 // patch kernel (conv_patch.hip).  Returns hipErrorNotSupported (nothing launched) for any other case.

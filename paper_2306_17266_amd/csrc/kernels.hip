@@ -27,7 +27,7 @@ hipError_t upload_tap_table() { return hipSuccess; }
 
 // ------------------------------------------------------------------ dense conv, vector ALUs
 // One thread: one output pixel x 4 consecutive filters.  Serves the input layers of the float32 mode and those that
-// stem_mfma_kernel does not cover, and float32 tensors of 2 GiB and more.  y = act(scale * conv + shift (+ res)).
+// stem_mfma_kernel does not cover, float32 tensors of 2 GiB and more, and the layers of both whose weights are not finite.  y = act(scale * conv + shift (+ res)).
 
 template <typename T>
 __global__ __launch_bounds__(256) void conv_direct_kernel(ConvArgs a) {
@@ -496,19 +496,20 @@ const char *kernel_class_name(int kc) {
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 
-hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels) {
+hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w) {
     const long M = (long)a.B * a.P * a.Q;
     int dummy;
     if (!kc) kc = &dummy;
     *kc = KC_CONV_DIRECT;
-    if (bf16) {
+    const bool finite = finite_w || a.R == 1;
+    if (bf16 && finite) {
         const hipError_t e = launch_stem(a, s);
         if (e != hipErrorNotSupported) {
             *kc = KC_STEM;
             return e;
         }
     }
-    if (!bf16) {
+    if (!bf16 && finite) {
         // (1 x 32 x 32 x 32 3x3: 37 us on the vector ALUs, one thread's 288 serial loads; here 5)
         const hipError_t e = launch_conv_small_f32(a, s);
         if (e != hipErrorNotSupported) {

@@ -29,6 +29,7 @@ struct Launch {
     PoolArgs pool{};
     QuantArgs quant{};  // int8 mode
     int in_patch = 0, out_patch = 0;  // 1 = pointer is the caller's input / logits buffer
+    bool finite_w = true;             // SuperLayer::finite_w
 };
 
 struct CachedPlan {
@@ -178,6 +179,10 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 size_t elem_size(const sushi_ctx *c) { return c->int8 ? 1 : c->bf16 ? 2 : 4; }
 
+// 0 for a finite value, NaN for an infinity or NaN.
+float finite_probe(float v) { return v * 0.f; }
+float finite_probe(uint16_t bf16) { return (bf16 & 0x7F80u) == 0x7F80u ? NAN : 0.f; }
+
 // Lays the SuperNet out for the device.  Dense/FC layer: [tap][channel group][filter, padded to 16][8];
 // depthwise: [tap in ring order][channel, padded to 16].  Scale/shift/bias: float32 runs, each
 // starting on a 32-byte boundary.  Returns the two host staging buffers.
@@ -200,7 +205,7 @@ void pack_weights(SuperNet &sn, const float *blob, std::vector<T> &w, std::vecto
     }
     w.assign(welems, T(0));
     params.assign(pfloats, 0.f);
-    for (const SuperLayer &L : sn.layers) {
+    for (SuperLayer &L : sn.layers) {
         const float *src = blob + L.blob_w;
         T *dst = w.data() + L.pk_w;
         const int R = L.Rmax;
@@ -220,6 +225,12 @@ void pack_weights(SuperNet &sn, const float *blob, std::vector<T> &w, std::vecto
                     for (int t = 0; t < R * R; ++t)
                         dst[(((size_t)t * L.CG + c / 8) * L.Kpad + k) * 8 + (c & 7)] =
                             cvt(src[((size_t)k * L.Cmax + c) * R * R + t]);
+        }
+        if (L.type != L_DW && (sizeof(T) == 4 || L.Cmax < 8)) {  // (what launch_conv asks for)
+            const size_t n = (size_t)L.Kmax * L.Cmax * R * R;
+            float sum = 0.f;  // NaN if one is not finite
+            for (size_t i = 0; i < n; ++i) sum += finite_probe(cvt(src[i]));
+            L.finite_w = sum == sum;
         }
         if (L.has_scale) std::memcpy(&params[L.pk_scale], blob + L.blob_scale, sizeof(float) * L.Kmax);
         std::memcpy(&params[L.pk_shift], blob + L.blob_shift, sizeof(float) * L.Kmax);
@@ -333,6 +344,7 @@ void bind_plan(sushi_ctx *c, CachedPlan &cp, const BufBase &bb = BufBase()) {
                     q.pool_hw = g.H * g.W;
                 }
             }
+            L.finite_w = S.finite_w;
             L.in_patch = op.in_buf == BUF_INPUT;
             L.out_patch = op.out_buf == BUF_LOGITS;
         } else {
@@ -470,7 +482,7 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
                 ConvArgs a = L.conv;
                 if (L.in_patch) a.x = input_dev;
                 if (L.out_patch) a.y = logits_dev;
-                e = launch_conv(a, c->bf16, st, &kc, c->patch_min_pixels);
+                e = launch_conv(a, c->bf16, st, &kc, c->patch_min_pixels, L.finite_w);
                 break;
             }
             case OP_DW:

@@ -54,6 +54,39 @@ def test_input_layer(res, stride, width, batch):
     _check(arch, A.max_cfg(arch), batch, 41, BF16_TOL)
 
 
+# A weight of minus infinity and an input above 0: minus infinity, ReLU'd to 0, wherever its tap lies inside the image, and
+# outside it the tap is no part of the sum.  The oracle gets a large finite weight instead.  Input layer and float32 layers.
+@pytest.mark.parametrize("bf16,layer", [(True, 0), (False, 0), (False, 1)])
+def test_infinite_weight_outside_the_image(bf16, layer):
+    import paper_2306_17266_amd as S
+    from oracle import subnet_eval as E
+    arch = _chain([8, 16], [1, 1], 8)
+    cfg = A.max_cfg(arch)
+    table = S.sushi_describe_supernet(arch)
+
+    def tensors(weight):
+        tens = T.make_weights([(s, k) for _, s, k in table], 59, bf16)
+        for (name, _, _), t in zip(table, tens):
+            if name == "conv%d.w" % layer:
+                t[:4, 0, 0, 0] = weight
+            elif name == "conv0.shift":
+                t[:] = 20.0 if layer == 1 else t  # (its output is above 0 everywhere)
+        return tens
+
+    x = np.abs(T.make_input(59, 0, 2, 8, 3, bf16)) + np.float32(0.25)
+    x = T.round_to_bf16(x) if bf16 else x
+    wts = E.name_weights(arch, tensors(-1e30))
+    want = oracle_logits_bf16_stores(arch, wts, cfg, x) if bf16 else E.forward(arch, wts, cfg, np.ascontiguousarray(x.transpose(0, 3, 1, 2)))
+    ctx = S.Sushi(0)
+    ctx.sushi_load_supernet(arch, T.flatten(tensors(-np.inf)), S.BF16 if bf16 else S.FP32)
+    xd = torch.from_numpy(x).cuda()
+    logits = torch.full((2, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32)
+    ctx.sushi_infer(cfg, xd.to(torch.bfloat16) if bf16 else xd, logits)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert rel_l2(logits.cpu().numpy(), want) <= (BF16_TOL if bf16 else 1e-5)
+
+
 def _mobile(expand, kernel, strides, act, res, out=16):
     """An inverted-residual net of one block per stage: stage widths `out`, one kernel size, no squeeze-excite."""
     n = len(strides)
