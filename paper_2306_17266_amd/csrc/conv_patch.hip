@@ -470,13 +470,10 @@ hipError_t launch_patch(const ConvArgs &a, hipStream_t s, const QuantArgs &q = Q
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dwp = make_fastdiv(g.wp), g.dhp = make_fastdiv(g.hp);
     const size_t lds = (cells + 3 * BN / 4) * 16;
     if (lds > 160 * 1024) return hipErrorNotSupported;
-    static bool attr_set = false;
     auto kern = conv_patch_kernel<TF, TM, CK, R, MAXP, MINB, NW, I8>;
-    if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
+    static LdsLimit limit;
+    const hipError_t e = limit.raise(kern);
+    if (e != hipSuccess) return e;
     const int per_xcd = (g.tiles_m * g.tiles_f + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(NT), lds, s, a, g, q);
     return hipGetLastError();

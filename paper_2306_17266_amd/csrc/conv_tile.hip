@@ -283,8 +283,9 @@ static hipError_t launch_tile(const ConvArgs &a, const QuantArgs &q, hipStream_t
     const size_t lds = ((size_t)g.part + (I8 ? 48 : 32)) * 16;
     static_assert((size_t)KS * 2 * BUF * 16 + 768 <= 160 * 1024 && (size_t)KS * BM * 17 * 16 + 768 <= 160 * 1024, "LDS of a compute unit");
     auto kern = conv_tile_kernel<KS, R, I8>;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (attr != hipSuccess) return attr;
+    static LdsLimit limit;
+    const hipError_t e = limit.raise(kern);
+    if (e != hipSuccess) return e;
     const int per_xcd = (g.tiles_m * g.tiles_f + 7) / 8;
     hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(256 * KS), lds, s, a, g, q);
     return hipGetLastError();

@@ -14,9 +14,32 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 
 namespace sushi {
+
+// Raises a kernel's limit of dynamic LDS to all a compute unit has, once per device (the limit belongs to a kernel on one
+// device); what fails is tried again by the next launch.  One static object per kernel; any number of threads.
+class LdsLimit {
+    std::atomic<uint64_t> raised_{0};  // bit d: done on device d
+
+public:
+    template <typename Kernel>
+    hipError_t raise(Kernel kernel) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;  // (beyond 64 devices: by every launch)
+        if (raised_.load(std::memory_order_acquire) & bit) return hipSuccess;
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e == hipSuccess)
+            raised_.fetch_or(bit, std::memory_order_release);
+        else
+            (void)hipGetLastError();  // (reported here; the next launch must not find it)
+        return e;
+    }
+};
 
 struct ConvArgs {
     const void *x;       // input activations

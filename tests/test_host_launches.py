@@ -1,0 +1,27 @@
+"""The library's launches, seen from the host: limits of a launch, per-device state, which kernel serves which layer.  No GPU:
+the library runs on tests/fake_hip.cpp."""
+from tests.fake_hip import run
+
+
+def test_large_lds_on_every_device_and_after_a_failure(tmp_path):
+    """Kernels with more than 64 KiB of dynamic LDS need the limit raised on the device they run on, by every context that
+    is the first there; a failure is reported and the next query tries again."""
+    out = run(tmp_path, '''
+arch = A.resnet_arch()
+cfg = A.max_cfg(arch, 224)
+for dtype in ("bf16", "int8"):
+    for device in (0, 1):
+        ctx = context(arch, dtype, device)
+        if device == 1:
+            fake.fake_fail_attributes(1)
+            try:
+                infer(ctx, cfg, 16)
+                raise SystemExit("no error")
+            except S.SushiError as e:
+                assert e.code == -5, e
+        big = [k for k in infer(ctx, cfg, 16) if k[4] > 65536]
+        print(dtype, device, sorted({k[0] for k in big}))
+        ctx.close()
+''')
+    want = ["conv_patch_kernel", "conv_tile_kernel"]
+    assert out.splitlines() == ["%s %d %s" % (t, d, want) for t in ("bf16", "int8") for d in (0, 1)], out
