@@ -237,9 +237,10 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells), g.dr = make_fastdiv(a.R);
     // up to eight waves (16 are slower while there are other workgroups for the compute unit: 14 x 14 x 288 3x3 5.5 us, here
     // 4.8), each with at least one round of U steps; 16 for the longest reductions (7 x 7 x 720 3x3 11.3 us with 8, 8.0)
-    const int wk = std::max(1, std::min((g.nsteps + U - 1) / U, g.nsteps >= 192 ? 16 : 8));
-    const size_t lds = wk > 1 ? (size_t)wk * PT * 1024 : 0;
+    int wk = std::max(1, std::min((g.nsteps + U - 1) / U, g.nsteps >= 192 ? 16 : 8));
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);
+    while (wk > 1 && (long)per_xcd * 8 * 64 * wk >= 1l << 32) --wk;  // (a launch has fewer than 2^32 threads)
+    const size_t lds = wk > 1 ? (size_t)wk * PT * 1024 : 0;
     hipLaunchKernelGGL((conv_small_kernel<PT, U, 1024, TYPE>), dim3(per_xcd * 8), dim3(64 * wk), lds, s, a, g, q);
     return hipGetLastError();
 }
@@ -247,7 +248,7 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
 static bool small_fits(const ConvArgs &a, long es) {
     const long lim = (1l << 31) - 256;
     return a.C >= 8 && (a.C & 7) == 0 && (long)a.B * a.P * a.Q < lim && (long)a.B * a.H * a.W * a.C * es < lim &&
-           (long)a.R * a.R * a.CG * a.Kpad * (es == 4 && !a.in_f32 ? 32 : 16) < lim && ((a.K + 15) / 16) * (((long)a.B * a.P * a.Q + 15) / 16) < (1l << 30);
+           (long)a.R * a.R * a.CG * a.Kpad * (es == 4 && !a.in_f32 ? 32 : 16) < lim && ((a.K + 15) / 16) * (((long)a.B * a.P * a.Q + 15) / 16) < (1l << 26) - 8;
 }
 
 hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s) {

@@ -25,3 +25,17 @@ for dtype in ("bf16", "int8"):
 ''')
     want = ["conv_patch_kernel", "conv_tile_kernel"]
     assert out.splitlines() == ["%s %d %s" % (t, d, want) for t in ("bf16", "int8") for d in (0, 1)], out
+
+
+def test_float32_maps_of_many_gib_are_launched(tmp_path):
+    """A launch has fewer than 2^32 threads along a dimension.  A float32 layer with an output of 17 GiB (8.3 million pixels,
+    512 filters, 64 input channels) has to stay below it, whichever kernel it gets."""
+    out = run(tmp_path, '''
+arch = dataclasses.replace(A.tiny_arch(), n_classes=8, stage_base_out=[64, 512], stage_stride=[1, 1], stage_max_depth=[1, 1],
+                           stage_act=[A.ACT_RELU] * 2, stage_se=[0, 0], depth_drop_choices=[0], width_choices=[1.0], res_choices=[256])
+ctx = context(arch, "fp32")
+launches = infer(ctx, A.max_cfg(arch), 127)
+print([k[0] for k in launches], max(k[2] * k[3] for k in launches) < 1 << 32)
+ctx.close()
+''')
+    assert out.split("]")[1].strip() == "True", out
