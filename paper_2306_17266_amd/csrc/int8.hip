@@ -207,8 +207,8 @@ hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, 
         hipLaunchKernelGGL(conv_i8_direct_kernel, dim3(i8_blocks(M), (unsigned)((a.K + 31) / 32)), dim3(256), 0, s, a, q);
         return hipGetLastError();
     }
-    const bool chosen = patch_min_pixels != PATCH_MIN_PIXELS;  // (by the caller: then it decides by itself)
-    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 2048);
+    const bool chosen = patch_min_pixels != PATCH_AUTO;  // (by the caller: then it decides by itself)
+    const bool patch = patch_from(patch_min_pixels, M, (long)a.C * a.R * a.R >= 2048);
     hipError_t e = chosen && patch ? launch_conv_patch_i8(a, q, s) : hipErrorNotSupported;
     if (e != hipErrorNotSupported) return e;
     if (conv_small_is_faster(a, true)) return launch_conv_small_i8(a, q, s);

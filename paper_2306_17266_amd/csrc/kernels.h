@@ -103,8 +103,12 @@ const char *kernel_class_name(int kc);
 // Every launcher returns hipSuccess or the launch error.  bf16 = activations and weights are bf16.
 // launch_conv reports the kernel family it picked in *kc (may be null).
 // patch_min_pixels: dense 1x1 / 3x3 layers with at least that many output pixels (B * P * Q) go to the patch
-// kernel (conv_patch.hip) where it covers the shape; 0 = never; at the default only where it is the fastest.
-constexpr long PATCH_MIN_PIXELS = 3136;
+// kernel (conv_patch.hip) where it covers the shape; 0 = never; PATCH_AUTO: from 3136 pixels on where it is the fastest.
+constexpr long PATCH_AUTO = -1;
+inline bool patch_from(long min_pixels, long pixels, bool long_reduction) {
+    const long n = min_pixels == PATCH_AUTO ? 3136 : min_pixels;
+    return n > 0 && pixels >= n && (pixels >= 4 * n || long_reduction);
+}
 // finite_w: the layer's weights are all finite; if not, float32 layers and the input layer run in the kernel that skips
 // taps outside the image (in the others zero meets the tap's weight, and zero times infinity is NaN).
 hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w);  // dense conv and FC

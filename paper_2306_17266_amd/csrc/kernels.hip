@@ -529,10 +529,10 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
         *kc = KC_CONV_SMALL;
         return launch_conv_small(a, s);
     }
-    // A threshold set by the caller decides by itself; under the default the measured rules of the other kernels come first.
+    // A threshold set by the caller decides by itself; without one the measured rules of the other kernels come first.
     // (At the threshold only long reductions: short ones are quicker in the tile kernel.)
-    const bool chosen = patch_min_pixels != PATCH_MIN_PIXELS;
-    const bool patch = patch_min_pixels > 0 && M >= patch_min_pixels && (M >= 4 * patch_min_pixels || (long)a.C * a.R * a.R >= 1024);
+    const bool chosen = patch_min_pixels != PATCH_AUTO;
+    const bool patch = patch_from(patch_min_pixels, M, (long)a.C * a.R * a.R >= 1024);
     auto picked = [&](hipError_t e, int family) {
         if (e != hipErrorNotSupported) *kc = family;
         return e;

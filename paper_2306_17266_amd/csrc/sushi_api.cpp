@@ -96,7 +96,7 @@ struct sushi_ctx {
     int team_size() const { return team_wgs / (MAX_XCDS * teams_per_xcd); }  // workgroups of a team, if they spread evenly
     int spin_limit = 400000;
     void *static_buf = nullptr;  // this device's copy of the library's static scratch array (sushi_infer_static)
-    long patch_min_pixels = PATCH_MIN_PIXELS;  // SUSHI_OPT_PATCH_CONV_MIN_PIXELS
+    long patch_min_pixels = PATCH_AUTO;  // SUSHI_OPT_PATCH_CONV_MIN_PIXELS
     void *d_sweep = nullptr;  // SUSHI_OPT_COLD_SWEEP_MIB: scratch streamed through the caches before every query
     size_t sweep_bytes = 0;
     // exec mode 3 (team kernel): mailboxes in pinned host memory, per-team arenas, private stream

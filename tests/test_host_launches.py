@@ -39,3 +39,22 @@ print([k[0] for k in launches], max(k[2] * k[3] for k in launches) < 1 << 32)
 ctx.close()
 ''')
     assert out.split("]")[1].strip() == "True", out
+
+
+def test_patch_threshold_set_by_the_caller(tmp_path):
+    """SUSHI_OPT_PATCH_CONV_MIN_PIXELS decides by itself once it is set, at every value: one threshold more or less moves no
+    layer unless its pixel count lies between the two."""
+    out = run(tmp_path, '''
+arch = A.resnet_arch()
+cfg = A.max_cfg(arch, 224)
+for dtype in ("bf16", "int8"):
+    ctx = context(arch, dtype)
+    counts = []
+    for value in (None, 3135, 3136, 3137, 0):
+        if value is not None:
+            ctx.sushi_set_option(S.OPT_PATCH_CONV_MIN_PIXELS, value)
+        counts.append(sum(k[0] == "conv_patch_kernel" for k in infer(ctx, cfg, 17)))
+    print(counts[1] == counts[2] == counts[3] > counts[0] > 0, counts[4] == 0, counts)
+    ctx.close()
+''')
+    assert [line.split()[:2] for line in out.splitlines()] == [["True", "True"]] * 2, out
