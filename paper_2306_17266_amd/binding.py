@@ -410,7 +410,9 @@ class Sushi:
         return [(buf[i].op_index, buf[i].kernel_class, buf[i].ms, buf[i].bytes, buf[i].flops) for i in range(n.value)]
 
     def sushi_get_kernel_stats(self):
-        buf, n = (CKernelStats * 16)(), C.c_int(0)
-        _check(lib().sushi_get_kernel_stats(self._h, buf, 16, C.byref(n)), self._h)
+        n = C.c_int(0)
+        _check(lib().sushi_get_kernel_stats(self._h, None, 0, C.byref(n)), self._h)
+        buf = (CKernelStats * n.value)()
+        _check(lib().sushi_get_kernel_stats(self._h, buf, n.value, C.byref(n)), self._h)
         return [dict(name=buf[i].name.decode(), launches=buf[i].launches, total_ms=buf[i].total_ms,
                      bytes=buf[i].bytes, flops=buf[i].flops) for i in range(n.value)]

@@ -198,27 +198,28 @@ __global__ __launch_bounds__(256) void fc_i8_kernel(ConvArgs a, QuantArgs q) {
 
 static inline unsigned i8_blocks(long total) { return (unsigned)((total + 255) / 256); }
 
-hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, long patch_min_pixels) {
+hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, int *kc, long patch_min_pixels) {
     const long M = (long)a.B * a.P * a.Q;
     if ((a.K & 3) || M * a.K >= (1l << 31) - 256 || (long)a.B * a.H * a.W * a.C >= (1l << 31) - 256) return hipErrorInvalidValue;
     if ((long)a.R * a.R * a.CG * a.Kpad * 16 >= (1l << 31) - 256) return hipErrorInvalidValue;
     if (a.C < 8 || (a.C & 7)) {
         if (a.C > 4 || a.R * a.R > 49) return hipErrorInvalidValue;
+        *kc = KC_CONV_I8_DIRECT;
         hipLaunchKernelGGL(conv_i8_direct_kernel, dim3(i8_blocks(M), (unsigned)((a.K + 31) / 32)), dim3(256), 0, s, a, q);
         return hipGetLastError();
     }
     const bool chosen = patch_min_pixels != PATCH_AUTO;  // (by the caller: then it decides by itself)
     const bool patch = patch_from(patch_min_pixels, M, (long)a.C * a.R * a.R >= 2048);
-    hipError_t e = chosen && patch ? launch_conv_patch_i8(a, q, s) : hipErrorNotSupported;
-    if (e != hipErrorNotSupported) return e;
-    if (conv_small_is_faster(a, true)) return launch_conv_small_i8(a, q, s);
-    e = launch_conv_tile_i8(a, q, s, patch && !chosen);
-    if (e != hipErrorNotSupported) return e;
-    if (patch && !chosen) {
-        e = launch_conv_patch_i8(a, q, s);
-        if (e != hipErrorNotSupported) return e;
-    }
-    return launch_conv_small_i8(a, q, s);
+    auto picked = [&](hipError_t e, int family) {
+        if (e != hipErrorNotSupported) *kc = family;
+        return e;
+    };
+    hipError_t e = chosen && patch ? picked(launch_conv_patch_i8(a, q, s), KC_CONV_PATCH) : hipErrorNotSupported;
+    if (e == hipErrorNotSupported && conv_small_is_faster(a, true)) e = picked(launch_conv_small_i8(a, q, s), KC_CONV_SMALL);
+    if (e == hipErrorNotSupported) e = picked(launch_conv_tile_i8(a, q, s, patch && !chosen), KC_CONV_TILE);
+    if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch_i8(a, q, s), KC_CONV_PATCH);
+    if (e == hipErrorNotSupported) e = picked(launch_conv_small_i8(a, q, s), KC_CONV_SMALL);
+    return e;
 }
 
 hipError_t launch_fc_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {

@@ -83,25 +83,27 @@ struct PoolArgs {
 // Kernel families, for per-kernel accounting.
 enum KernelClass {
     KC_CONV_DIRECT = 0,   // conv_direct_kernel
-    KC_CONV_MFMA = 1,     // conv_mfma_kernel (whole-reduction waves)
+    KC_CONV_MFMA = 1,     // conv_mfma_kernel
     KC_CONV_SMALL = 2,    // conv_small_kernel
-    KC_DWCONV = 3,
+    KC_DW_ROWS = 3,       // dwconv_rows_kernel
     KC_MAXPOOL = 4,
     KC_GAP = 5,
     KC_GATE = 6,
     KC_STREAM = 7,  // sushi_stream_kernel (one launch per query)
     KC_TEAM = 8,    // sushi_team_kernel (persistent; one launch serves many queries)
     KC_CONV_PATCH = 9,  // conv_patch_kernel (large pixel counts; the input patch of a tile staged in LDS)
-    KC_CONV_I8 = 10,    // dense layers of the int8 mode
+    KC_CONV_I8_DIRECT = 10,  // conv_i8_direct_kernel (int8: the input layer)
     KC_I8_OTHER = 11,   // int8 mode: max-pool, pooled sums, classifier
     KC_STEM = 12,       // stem_mfma_kernel (bf16: the 3-channel input layer)
     KC_CONV_TILE = 13,  // conv_tile_kernel (64-filter tiles, the reduction split over wave groups)
-    KC_COUNT = 14
+    KC_DW_MFMA = 14,    // dw_mfma_kernel (depthwise on the matrix cores)
+    KC_DW = 15,         // dwconv_kernel (depthwise: float32, and tensors of 2 GiB and more)
+    KC_COUNT = 16
 };
 const char *kernel_class_name(int kc);
 
 // Every launcher returns hipSuccess or the launch error.  bf16 = activations and weights are bf16.
-// launch_conv reports the kernel family it picked in *kc (may be null).
+// Launchers that choose between kernels report the family they picked in *kc.
 // patch_min_pixels: dense 1x1 / 3x3 layers with at least that many output pixels (B * P * Q) go to the patch
 // kernel (conv_patch.hip) where it covers the shape; 0 = never; PATCH_AUTO: from 3136 pixels on where it is the fastest.
 constexpr long PATCH_AUTO = -1;
@@ -134,7 +136,7 @@ bool conv_small_is_faster(const ConvArgs &a, bool i8);  // than the tile kernel 
 // 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
 // other case.
 hipError_t launch_stem(const ConvArgs &a, hipStream_t s);
-hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s);
+hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc);
 hipError_t launch_maxpool(const PoolArgs &a, bool bf16, hipStream_t s);   // 3x3 stride 2 pad 1
 hipError_t launch_gap(const PoolArgs &a, bool bf16, hipStream_t s);       // [B][H][W][C] -> [B][C]
 hipError_t launch_gate(const PoolArgs &a, bool bf16, hipStream_t s);      // y = x * gate[b][c]
@@ -149,7 +151,7 @@ hipError_t launch_dwconv_mfma(const ConvArgs &a, hipStream_t s);
 
 // int8 mode (int8.hip): dense conv 1x1 / 3x3 on the int8 matrix cores (3 input channels: vector ALUs) with integer
 // requantisation, 3x3/2 max-pool on codes, exact int32 pooled sums, int64 classifier with float32 logits.
-hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, long patch_min_pixels);
+hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, int *kc, long patch_min_pixels);
 hipError_t launch_conv_patch_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s);  // conv_patch.hip
 hipError_t launch_fc_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s);
 hipError_t launch_maxpool_i8(const PoolArgs &a, hipStream_t s);

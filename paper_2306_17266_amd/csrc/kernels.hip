@@ -491,15 +491,14 @@ const char *kernel_class_name(int kc) {
     static const char *names[KC_COUNT] = {"conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel",
                                           "dwconv_rows_kernel", "maxpool_kernel",   "gap_kernel",
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
-                                          "conv_patch_kernel",  "conv_i8_kernel",      "int8_pool_fc_kernels",
-                                          "stem_mfma_kernel",   "conv_tile_kernel"};
+                                          "conv_patch_kernel",  "conv_i8_direct_kernel", "int8_pool_fc_kernels",
+                                          "stem_mfma_kernel",   "conv_tile_kernel",    "dw_mfma_kernel",
+                                          "dwconv_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 
 hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w) {
     const long M = (long)a.B * a.P * a.Q;
-    int dummy;
-    if (!kc) kc = &dummy;
     *kc = KC_CONV_DIRECT;
     const bool finite = finite_w || a.R == 1;
     if (bf16 && finite) {
@@ -557,13 +556,15 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
     return launch_mfma<64, 64>(a, s);
 }
 
-hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s) {
+hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc) {
     const long total = (long)a.B * a.P * a.Q * (a.K >> 3);
     if (bf16) {
+        *kc = KC_DW_MFMA;
         hipError_t e = launch_dwconv_mfma(a, s);
-        if (e == hipErrorNotSupported) e = launch_dwconv_rows(a, s);
+        if (e == hipErrorNotSupported) *kc = KC_DW_ROWS, e = launch_dwconv_rows(a, s);
         if (e != hipErrorNotSupported) return e;
     }
+    *kc = KC_DW;
     if (bf16)
         hipLaunchKernelGGL(dwconv_kernel<uint16_t>, dim3(blocks_for(total)), dim3(256), 0, s, a);
     else

@@ -456,8 +456,7 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
             switch (L.kind) {
                 case OP_CONV:
                     if (L.in_patch) a.x = input_dev;
-                    kc = KC_CONV_I8;
-                    e = launch_conv_i8(a, L.quant, st, c->patch_min_pixels);
+                    e = launch_conv_i8(a, L.quant, st, &kc, c->patch_min_pixels);
                     break;
                 case OP_FC:
                     if (L.out_patch) a.y = logits_dev;
@@ -486,8 +485,7 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
                 break;
             }
             case OP_DW:
-                kc = KC_DWCONV;
-                e = launch_dwconv(L.conv, c->bf16, st);
+                e = launch_dwconv(L.conv, c->bf16, st, &kc);
                 break;
             case OP_MAXPOOL:
                 kc = KC_MAXPOOL;

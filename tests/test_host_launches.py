@@ -58,3 +58,20 @@ for dtype in ("bf16", "int8"):
     ctx.close()
 ''')
     assert [line.split()[:2] for line in out.splitlines()] == [["True", "True"]] * 2, out
+
+
+def test_statistics_name_the_kernels_that_ran(tmp_path):
+    out = run(tmp_path, '''
+from collections import Counter
+POOL_FC = {"maxpool_i8_kernel", "gap_i8_kernel", "fc_i8_kernel"}
+for arch, dtype, batch, res in ((A.resnet_arch(), "bf16", 1, 224), (A.resnet_arch(), "bf16", 16, 224), (A.mbv3_arch(), "bf16", 1, 224),
+                                (A.mbv3_arch(), "bf16", 64, 224), (A.small_mbv3_arch(), "fp32", 2, 64), (A.resnet_arch(), "int8", 1, 224),
+                                (A.resnet_arch(), "int8", 48, 224)):
+    ctx = context(arch, dtype)
+    ctx.sushi_set_option(S.OPT_KERNEL_TIMING, 1)
+    ran = Counter("int8_pool_fc_kernels" if k[0] in POOL_FC else k[0] for k in infer(ctx, A.max_cfg(arch, res), batch))
+    told = Counter({k["name"]: k["launches"] for k in ctx.sushi_get_kernel_stats() if k["launches"]})
+    print(dtype, batch, "ok" if ran == told else (ran, told))
+    ctx.close()
+''')
+    assert all(line.endswith(" ok") for line in out.splitlines()) and len(out.splitlines()) == 7, out
