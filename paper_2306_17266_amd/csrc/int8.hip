@@ -37,6 +37,8 @@ __device__ __forceinline__ void store_codes(const ConvArgs &a, const QuantArgs &
 
 // Fewer than 8 input channels (the network input): one thread per output pixel, all filters of a group of up to 32;
 // the group's weights sit in LDS as int32 [tap * C + channel][32] (every thread reads the same word: a broadcast).
+// Bound by the multiply-adds on the vector ALUs: 48 images of 224 x 224 to 32 filters, 3x3/2, 49 us, one image 15.
+// (Requesting a patch's 27 codes at once lost at every batch size: 56 and 17 us; the other waves hide the loads' latency.)
 __global__ __launch_bounds__(256) void conv_i8_direct_kernel(ConvArgs a, QuantArgs q) {
     __shared__ int wl[49 * 4 * 32];
     const int f0 = blockIdx.y * 32;
@@ -57,28 +59,6 @@ __global__ __launch_bounds__(256) void conv_i8_direct_kernel(ConvArgs a, QuantAr
     int acc[32];
 #pragma unroll
     for (int f = 0; f < 32; ++f) acc[f] = 0;
-    if (a.R == 3 && a.C == 3) {
-        // a 3x3 patch of the image: its 27 codes are requested at once (tap by tap they were 27 round trips: 1 x 224 x 224
-        // 13.8 us, 16 images 24)
-        int xv[27];
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int h = pp * a.stride - a.pad + tap / 3, v = qq * a.stride - a.pad + tap % 3;
-            const bool ok = h >= 0 && h < a.H && v >= 0 && v < a.W;
-            const int8_t *xp = x + (((long)n * a.H + min(max(h, 0), a.H - 1)) * a.W + min(max(v, 0), a.W - 1)) * 3;
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) xv[tap * 3 + ch] = ok ? (int)xp[ch] - q.zx : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            const int4 *wr = reinterpret_cast<const int4 *>(wl + i * 32);
-#pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                const int4 wv = wr[g];
-                acc[4 * g] += xv[i] * wv.x, acc[4 * g + 1] += xv[i] * wv.y, acc[4 * g + 2] += xv[i] * wv.z, acc[4 * g + 3] += xv[i] * wv.w;
-            }
-        }
-    } else
     for (int tap = 0; tap < taps; ++tap) {
         const int h = pp * a.stride - a.pad + tap / a.R, v = qq * a.stride - a.pad + tap % a.R;
         if (h < 0 || h >= a.H || v < 0 || v >= a.W) continue;
