@@ -235,9 +235,12 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
     const int cells = (a.C + CPC - 1) / CPC;
     g.kcells = a.R * a.R * cells, g.nsteps = (g.kcells + 3) / 4;
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells), g.dr = make_fastdiv(a.R);
-    // up to eight waves (16 are slower while there are other workgroups for the compute unit: 14 x 14 x 288 3x3 5.5 us, here
-    // 4.8), each with at least one round of U steps; 16 for the longest reductions (7 x 7 x 720 3x3 11.3 us with 8, 8.0)
-    int wk = std::max(1, std::min((g.nsteps + U - 1) / U, g.nsteps >= 192 ? 16 : 8));
+    // Waves per tile, each with at least one round of U steps: as many as run at once.  A compute unit holds 16 of these
+    // waves, so 16 up to 256 tiles (7 x 7 x 576 3x3, 144 tiles: 4, 8, 16 waves 16.2, 10.2, 8.2 us in int8), 8 up to 512 and in
+    // bf16 768 (3 x 7 x 7 x 720 3x3, 450 tiles, bf16: 21.3, 13.2, 14.2), 4 beyond: there a tile with 8 takes two tiles' places
+    // (8 x 14 x 14 x 208 3x3, 1274 tiles, int8: 8.9, 11.2, 11.2).
+    const long tiles = (long)g.tiles_m * g.tiles_f;
+    int wk = std::max(1, std::min((g.nsteps + U - 1) / U, tiles <= 256 ? 16 : tiles <= (TYPE == ST_I8 ? 512 : 768) ? 8 : 4));
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);
     while (wk > 1 && (long)per_xcd * 8 * 64 * wk >= 1l << 32) --wk;  // (a launch has fewer than 2^32 threads)
     const size_t lds = wk > 1 ? (size_t)wk * PT * 1024 : 0;
