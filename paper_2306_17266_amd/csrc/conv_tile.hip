@@ -337,20 +337,30 @@ bool conv_small_is_faster(const ConvArgs &a, bool i8) {
     return work / (i8 ? 5000.0 : a.R == 1 ? 6500.0 : 8500.0) <= 0.4 + (steps + ks - 1) / ks * per_step + (a.R == 3 ? 1.0 : 0.0);
 }
 
-// Of the layers that the patch kernel covers as well (patch, stride 1) these stay there:
-//   3x3 with at least 128 of its tiles: one copy of the input serves nine taps (16 x 56 x 56 x 88: 15.6 us there, 26.2
-//       here; with 75 tiles, 16 x 14 x 14 x 360, 33.8 against 25.8);
+// Of the layers that the patch kernel covers as well (patch) these stay there:
+//   3x3 with stride 1 and at least 128 of its tiles: one copy of the input serves nine taps (16 x 56 x 56 x 88: 15.6 us
+//       there, 26.2 here; with 75 tiles, 16 x 14 x 14 x 360, 33.8 against 25.8);
+//   3x3 with stride 2 where its tiles are 128 filters wide and fill whole rounds of the chip, one on each compute unit, to
+//       0.85 and more (96 x 14 x 14 x 720, 222 tiles: 92 us there, 116 here; 61 x 28 x 28 x 360, 282 tiles, 92 against 76; in
+//       tiles of 96 filters, 61 x 56 x 56 x 176, 748 tiles, 81 against 65);
 //   bf16 1x1 of one step, or of two without a residual: all prologue and epilogue (64 x 112 x 112, 16 -> 96: 54 us there,
 //       110 here; 64 x 14 x 14, 80 -> 480: 8.8 against 10.8; with a residual, 16 x 56 x 56, 88 -> 256: 22.3 against 18.5);
+//   1x1 without a residual where its tiles, two on each compute unit, fill rounds to 0.85, in bf16 those of at most 96
+//       filters (96 x 14 x 14, 816 -> 288, 441 tiles: 24 us there, 29 here; 61 x 14 x 14, 816 -> 288, 282 tiles, 21 on both;
+//       in tiles of 128, 96 x 14 x 14, 1024 -> 360, 40 against 37);
 //   1x1 of many pixels where its tiles pad fewer filters (16 x 56 x 56, 256 -> 88: 11.3 us there, 16.1 here).
 template <bool I8>
 static bool tile_is_faster(const ConvArgs &a, bool patch) {
+    if (!patch) return true;
     const long M = (long)a.B * a.P * a.Q;
-    if (!patch || a.stride != 1) return true;
     const int pf = conv_patch_tile_filters(a.K);
-    if (a.R == 3) return ((M + 127) / 128) * ((a.K + pf - 1) / pf) < 128;
+    const long tiles = ((M + 127) / 128) * ((a.K + pf - 1) / pf);
+    auto full_rounds = [&](long per_round) { return tiles * 100 >= (tiles + per_round - 1) / per_round * per_round * 85; };
+    if (a.R == 3) return a.stride == 1 ? tiles < 128 : pf != 128 || !full_rounds(256);
+    if (a.stride != 1) return true;  // (not covered there)
     if (!I8 && (a.C <= 64 || (a.C <= 128 && !a.res))) return false;
-    return M <= 32768 || (a.K + 63) / 64 * 64 <= (a.K + pf - 1) / pf * pf;
+    if (M <= 32768) return a.res || (!I8 && pf == 128) || !full_rounds(512);
+    return (a.K + 63) / 64 * 64 <= (a.K + pf - 1) / pf * pf;
 }
 
 hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch) {
