@@ -187,17 +187,17 @@ static hipError_t launch_dw(const ConvArgs &a, hipStream_t s) {
 // serial load rounds, and the row-strip kernel of dwconv.hip has R of them (7x7 at 14 x 14 x 336, one image: 13.5 us,
 // here 4.8; 3x3: 5.2, here 3.8).  On larger maps 3x3 stays there (memory-bound, and the wider loads of that kernel win:
 // 21 us against 23 at 64 x 56 x 56 x 96), 5x5 and 7x7 come here (64 x 56 x 56 x 144 7x7: 78 us there, 50 here; 64 x 48 x
-// 48 x 144 5x5: 38 and 28), except where less than 0.7 of the strips is map and there are more strips than run at once
-// (5x5; 7x7: twice that): padding then costs what the matrix cores gain (us there and here: 5x5 48 x 10 x 10 x 480, 1.4
-// times the strips that run at once, 11.3 and 13.0, with 32 images 10.0 and 9.7; 7x7 96 x 14 x 14 x 672 / 2, 3.9 times,
-// 17.5 and 20.4, with 48 images 14.2 and 11.8).
+// 48 x 144 5x5: 38 and 28), except where less than 0.7 of the strips is map and the rest, counted in whole strips, comes
+// to a half (5x5) or 1.65 times (7x7) of what runs at once: that padding costs what the matrix cores gain (us there and
+// here: 5x5 48 x 10 x 10 x 480, 0.86 times, 11.3 and 13.0, with 16 images 0.29, 9.0 and 8.2; 7x7 96 x 14 x 14 x 672 / 2, 2.4
+// times, 17.5 and 20.4, with 48 images 1.2, 14.2 and 11.8).
 template <int R, int S, int T, int PD>
 static hipError_t pick_strip(const ConvArgs &a, hipStream_t s) {
     const long ctiles = (a.Q + 15) / 16, columns = a.B * ctiles * ((a.K + 15) / 16);
     if (columns * a.P <= 2048) return launch_dw<R, S, 1, R>(a, s);
     const long strips = (a.P + T - 1) / T;
-    const bool padded = (long)a.Q * a.P * 10 < ctiles * 16 * strips * T * 7;
-    if (R == 3 || (padded && columns * strips > (R == 5 ? 2048 : 4096))) return hipErrorNotSupported;
+    const double map = (double)a.Q * a.P / (double)(ctiles * 16 * strips * T);
+    if (R == 3 || (map < 0.7 && columns * strips * (1.0 - map) > (R == 5 ? 0.5 : 1.65) * 2048)) return hipErrorNotSupported;
     // T rows per strip re-read fewer input rows, one row per strip spreads a layer over more waves: the fewer input rows
     // in sequence, a strip's first loads counted as eight
     auto cost = [&](int rows) { return (columns * ((a.P + rows - 1) / rows) + 2047) / 2048 * ((rows - 1) * S + R + 8); };
