@@ -2,6 +2,7 @@
 documented limits and logs them instead of running them.  The code runs in a process of its own, which never loads the
 real runtime (so no torch there), with these helpers around it."""
 import os
+import pickle
 import subprocess
 import sys
 
@@ -44,14 +45,27 @@ def infer(ctx, cfg, batch):
         args = [int(v) for v in re.findall(r"L(?:[ib]|NS_\\w+?E)(\\d+)E", name[end:])]
         out.append((name[at.end():end], args, int(wgs), int(threads), int(lds)))
     return out
+
+
+def layers(arch, dtype, batch):
+    """The launches of the largest SubNet's query with what they compute: [(op of the plan, launch)]."""
+    ctx = context(arch, dtype)
+    cfg = A.max_cfg(arch)
+    ops, launches = S.sushi_team_plan(arch, cfg, batch, 32), infer(ctx, cfg, batch)
+    ctx.close()
+    assert len(ops) == len(launches)
+    return list(zip(ops, launches))
 ''' % ROOT
 
 
-def run(tmp_path, code):
-    """Runs PRELUDE and `code`; returns what it printed."""
+def run(tmp_path, code, data=None):
+    """Runs PRELUDE and `code` with `data` (anything pickle takes) as DATA; returns what it printed."""
     lib = os.path.join(str(tmp_path), "libamdhip64.so.7")
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-w", "-I/opt/rocm/include", "-Wl,-soname,libamdhip64.so.7",
                     "-Wl,--version-script=" + os.path.join(HERE, "fake_hip.map"), os.path.join(HERE, "fake_hip.cpp"), "-o", lib], check=True)
+    with open(os.path.join(str(tmp_path), "data"), "wb") as f:
+        pickle.dump(data, f)
+    code = "import pickle\nDATA = pickle.load(open(%r, 'rb'))\n" % os.path.join(str(tmp_path), "data") + code
     env = dict(os.environ, LD_LIBRARY_PATH=str(tmp_path))
     res = subprocess.run([sys.executable, "-c", PRELUDE + code], env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=120)
     assert res.returncode == 0, res.stdout

@@ -1,5 +1,8 @@
 """The per-layer kernels at the edges of their tiles, through small SuperNets built for it, against the CPU oracle.
 
+Where a kernel has no float32 or int8 variant the comparison is exact (small integers, see test_input_layer_exact); that
+the nets reach the kernels they are meant for is checked in test_host_launches.py.
+
 bf16 tolerance: every stored feature map is rounded to bf16 on both sides (relative error 2^-9 at most per value, at
 random), and a rounding that falls the other way moves a value by 2^-8; averaged over a map and summed over the channels
 of a classifier that stays below 2^-8 = 3.9e-3 of the logits for nets of a few layers."""
@@ -37,20 +40,19 @@ def _check(arch, cfg, batch, seed, tol, bf16=True):
         assert rel_l2(logits[n].cpu().numpy(), want[n]) <= tol, n
 
 
-def _chain(widths, strides, res, classes=64, channels=3):
-    """A Tiny-family net: 3x3 layers of the given widths and strides, pooling, classifier."""
+def _chain(widths, res, classes=64, channels=3):
+    """A Tiny-family net: 3x3 layers (stride 1) of the given widths, pooling, classifier."""
     n = len(widths)
     return dataclasses.replace(A.tiny_arch(), n_classes=classes, in_channels=channels, stage_base_out=list(widths),
-                               stage_stride=list(strides), stage_max_depth=[1] * n, stage_act=[A.ACT_RELU] * n,
+                               stage_stride=[1] * n, stage_max_depth=[1] * n, stage_act=[A.ACT_RELU] * n,
                                stage_se=[0] * n, depth_drop_choices=[0], width_choices=[1.0], res_choices=[res])
 
 
 # odd sizes: patch rows that start on odd elements, tensors of an odd number of elements (the general kernel), columns
 # outside on either side; 15 x 15 = one pixel short of a tile; widths of half a filter tile, a ragged one, several groups
-@pytest.mark.parametrize("res,stride,width,batch", [(8, 1, 8, 1), (9, 1, 24, 2), (9, 2, 16, 1), (15, 1, 32, 4), (33, 2, 40, 2), (31, 2, 72, 3),
-                                                     (12, 2, 16, 6), (224, 1, 16, 4)])
-def test_input_layer(res, stride, width, batch):
-    arch = _chain([width, 16], [stride, 2], res)
+@pytest.mark.parametrize("res,width,batch", [(8, 8, 1), (9, 24, 2), (9, 16, 1), (15, 32, 4), (33, 40, 2), (31, 72, 3), (12, 16, 6), (224, 16, 4)])
+def test_input_layer(res, width, batch):
+    arch = _chain([width, 16], res)
     _check(arch, A.max_cfg(arch), batch, 41, BF16_TOL)
 
 
@@ -60,7 +62,7 @@ def test_input_layer(res, stride, width, batch):
 def test_infinite_weight_outside_the_image(bf16, layer):
     import paper_2306_17266_amd as S
     from oracle import subnet_eval as E
-    arch = _chain([8, 16], [1, 1], 8)
+    arch = _chain([8, 16], 8)
     cfg = A.max_cfg(arch)
     table = S.sushi_describe_supernet(arch)
 
@@ -145,14 +147,106 @@ def _bottleneck(widths, strides, res, expand, classes=64):
                                width_choices=[1.0], expand_choices=[expand], res_choices=[res])
 
 
-# 60, 44 and 45 tiles of 64 x 64 with ragged pixels and filters; reductions of one step, of an odd number of steps and of 69
-# (split over one, two and four wave groups), not a multiple of a step; 1x1 and 3x3, both strides, with and without a residual;
-# int8: channel counts that are no multiple of a cell of 16, 128 tiles and more
-@pytest.mark.parametrize("arch,batch", [(_chain([24, 200, 72], [1, 1, 2], 15), 6), (_chain([24, 488, 72], [1, 1, 1], 15), 6),
-                                        (_chain([8, 264, 40], [2, 1, 1], 59), 1), (_bottleneck([264, 520], [1, 2], 60, 0.35), 5),
-                                        (_bottleneck([200, 328], [1, 2], 112, 0.2), 9)])
-@pytest.mark.parametrize("int8", [False, True])
-def test_tiled_layers(arch, batch, int8):
+# The input layer and the depthwise kernels output by output.  Images and weights are small integers, scales 1 and shifts
+# integers, every other layer copies its channels: all products, sums (below 256 per output, or even and below 512: the
+# bf16 stores too) are exact whatever their order, and the logits are the channels' averages.  An average times its pixel count is an integer
+# below 2^15, the head's two-term split of it carries 16 bits: rounded to the nearest it is the channel's exact sum.
+
+def _exact(arch, weights, x):
+    """weights(name, shape): integer tensors.  The logits of the library and of the oracle."""
+    import paper_2306_17266_amd as S
+    from oracle import subnet_eval as E
+    cfg = A.max_cfg(arch)
+    table = S.sushi_describe_supernet(arch)
+    tens = [np.ascontiguousarray(weights(name, s), dtype=np.float32) for name, s, _ in table]
+    want = E.forward(arch, E.name_weights(arch, tens), cfg, np.ascontiguousarray(x.transpose(0, 3, 1, 2)))
+    ctx = S.Sushi(0)
+    ctx.sushi_load_supernet(arch, T.flatten(tens), S.BF16)
+    logits = torch.full(want.shape, float("nan"), device="cuda", dtype=torch.float32)
+    ctx.sushi_infer(cfg, torch.from_numpy(x).cuda().to(torch.bfloat16), logits)
+    torch.cuda.synchronize()
+    ctx.close()
+    return logits.cpu().numpy().astype(np.float64), np.asarray(want, dtype=np.float64)
+
+
+def _copy(shape):
+    """1x1 (or centre of a larger kernel): output channel k is input channel k modulo their count."""
+    w = np.zeros(shape)
+    for k in range(shape[0]):
+        w[(k, k % shape[1]) + tuple(r // 2 for r in shape[2:])] = 1.0
+    return w
+
+
+# (resolution, stride, width, batch): patch rows from odd elements and columns outside on either side, tensors of an odd
+# number of elements (the general kernel), 15 x 15 = one pixel short of a tile, widths of half a filter tile, a ragged one and
+# several; from 131072 outputs on four pixel tiles per wave (134540 and 132940 end with a ragged one)
+INPUT_LAYERS = [(8, 1, 8, 1), (9, 1, 24, 2), (9, 1, 16, 1), (15, 1, 32, 4), (33, 1, 40, 2), (31, 1, 72, 4), (31, 1, 16, 140), (33, 1, 40, 128),
+                (8, 2, 8, 1), (9, 2, 24, 2), (9, 2, 16, 1), (30, 2, 32, 4), (33, 2, 40, 2), (31, 2, 72, 4), (12, 2, 16, 6), (33, 2, 16, 460), (33, 2, 40, 460)]
+
+
+def input_layer_net(res, stride, width):
+    """The input layer alone (stride 1), or before layers that copy its channels."""
+    return _chain([width], res, width) if stride == 1 else dataclasses.replace(depthwise_net(3, 1, 4, width), res_choices=[res])
+
+
+@pytest.mark.parametrize("res,stride,width,batch", INPUT_LAYERS)
+def test_input_layer_exact(res, stride, width, batch):
+    arch = input_layer_net(res, stride, width)
+    rng = np.random.default_rng(61)
+    x = rng.integers(-1, 3, (batch, res, res, 3)).astype(np.float32)
+
+    def weights(name, shape):
+        if name == "conv0.w":
+            return rng.integers(-1, 2, shape)
+        if name == "stem.w":
+            return 3 * rng.integers(-1, 2, shape)  # (h-swish leaves 0 and multiples of 3 as they are, ReLU'd)
+        if name.endswith(".scale"):
+            return np.ones(shape)
+        if name == "head.shift":
+            return np.full(shape, 4.0)  # (h-swish again)
+        return np.zeros(shape) if name == "first.pw.w" or not name.endswith(".w") else _copy(shape)
+
+    got, want = _exact(arch, weights, x)
+    pixels, shift = ((res - 1) // stride + 1) ** 2, 4.0 * (stride == 2)
+    np.testing.assert_array_equal(np.rint((got - shift) * pixels), np.rint((want - shift) * pixels))
+
+
+# (map, channels, batch): maps narrower than a column tile, of one, one past it and three; channel counts of half a group of 16,
+# 24, 40 and more; one-row strips (few images) and strips of several rows with a ragged last one; the row kernel (3x3, and narrow
+# maps of many images)
+DEPTHWISE = [(4, 8, 1), (15, 24, 2), (17, 40, 1), (33, 24, 1), (23, 144, 24), (16, 144, 24), (33, 40, 24), (5, 320, 220), (9, 144, 200)]
+
+
+def depthwise_net(kernel, stride, size, channels):
+    """Input layer (copies, two pixels to one), a block of the depthwise layer alone on a size x size map, head (copies)."""
+    return dataclasses.replace(_mobile(1, kernel, (stride,), A.ACT_RELU, 2 * size, channels), head_mid=channels, head_feat=channels,
+                               n_classes=channels)
+
+
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("stride", [1, 2])
+@pytest.mark.parametrize("size,channels,batch", DEPTHWISE)
+def test_depthwise_exact(kernel, stride, size, channels, batch):
+    arch = depthwise_net(kernel, stride, size, channels)
+    rng = np.random.default_rng(67)
+    # 0 or at least 3: h-swish leaves those as they are
+    x = rng.choice(np.array([0.0, 0.0, 0.0, 3.0], np.float32), (batch, 2 * size, 2 * size, 3)).astype(np.float32)
+
+    def weights(name, shape):
+        if name.endswith(".scale"):
+            return np.ones(shape)
+        if name == "s0b0.dw.w":
+            return rng.integers(-1, 2, shape)
+        if name == "head.shift":
+            return np.full(shape, 4.0)  # (h-swish again)
+        return np.zeros(shape) if name == "first.pw.w" or not name.endswith(".w") else _copy(shape)
+
+    got, want = _exact(arch, weights, x)
+    pixels = ((size - 1) // stride + 1) ** 2
+    np.testing.assert_array_equal(np.rint((got - 4.0) * pixels), np.rint((want - 4.0) * pixels))
+
+
+def _check_dense(arch, batch, int8):
     if int8:
         from tests.test_gpu_int8 import _check as check_int8
         check_int8(arch, [A.max_cfg(arch)], 47, batch)
@@ -160,15 +254,78 @@ def test_tiled_layers(arch, batch, int8):
         _check(arch, A.max_cfg(arch), batch, 47, 2 * BF16_TOL)  # (up to fourteen layers)
 
 
-# reductions of less than a step, of less than a round, of several rounds with a ragged last one and of 194 steps (16 waves);
-# pixel tiles of one to 16 pixels, both strides, residuals; a classifier whose class count is no multiple of 4; int8: cells
-# that straddle the channel count
-@pytest.mark.parametrize("arch,batch", [(_chain([8, 24, 200], [1, 2, 1], 9, 10), 1), (_chain([40, 688, 24], [2, 1, 1], 11, 37), 1),
-                                        (_bottleneck([208, 328], [1, 2], 60, 0.35), 1), (_bottleneck([72, 136], [1, 2], 44, 0.2), 3)])
+# Ragged pixels and filters; one, two and four wave groups; 1x1 and 3x3, both strides, with and without a residual; int8:
+# channel counts that are no multiple of a cell of 16, reductions of one step and of 33 (the last net: a 1x1 in four groups)
+TILED = [(_bottleneck([136, 1040], [1, 2], 112, 0.2), 9), (_bottleneck([136, 1040], [1, 2], 60, 0.6), 9), (_chain([8, 264, 40], 29), 6),
+         (_bottleneck([520, 264], [1, 2], 112, 0.2), 9), (_bottleneck([680], [2], 112, 0.2), 57), (_bottleneck([2056], [1], 60, 0.1), 7),
+         (_bottleneck([200, 328], [1, 2], 112, 0.2), 9)]
+
+
+@pytest.mark.parametrize("arch,batch", TILED)
+@pytest.mark.parametrize("int8", [False, True])
+def test_tiled_layers(arch, batch, int8):
+    _check_dense(arch, batch, int8)
+
+
+# reductions of less than a step, of less than a round, of several rounds with a ragged last one and of 194 steps; one to 16
+# waves; pixel tiles of one to 16 pixels, both strides, residuals; a classifier whose class count is no multiple of 4; int8: cells
+# that straddle the channel count; the last five: more tiles than run at once with 16 or 8 waves each
+FEW_PIXELS = [(_chain([8, 24, 200], 9, 10), 1), (_chain([40, 688, 24], 11, 37), 1),
+              (_bottleneck([208, 328], [1, 2], 60, 0.35), 1), (_bottleneck([72, 136], [1, 2], 44, 0.2), 3),
+              (_chain([24, 200, 72], 15), 6), (_chain([24, 488, 72], 15), 6), (_chain([8, 264, 40], 59), 1),
+              (_bottleneck([264, 520], [1, 2], 60, 0.35), 5), (_bottleneck([1640], [1], 28, 0.2), 12)]
+
+
+@pytest.mark.parametrize("arch,batch", FEW_PIXELS)
 @pytest.mark.parametrize("dtype", ["bf16", "int8", "fp32"])
 def test_few_pixels(arch, batch, dtype):
     if dtype == "fp32":
         # float32 sums of up to 6192 products against float64: 2^-24 per addition, at random 2^-24 sqrt(6192) = 4.7e-6
         _check(arch, A.max_cfg(arch), batch, 47, 1e-5, False)
     else:
-        test_tiled_layers(arch, batch, dtype == "int8")
+        _check_dense(arch, batch, dtype == "int8")
+
+
+# The patch kernel of the int8 mode on every layer it covers: tiles of 64, 96 and 128 filters, 1x1 with and without a residual,
+# 3x3 with both strides, ragged pixels and channel counts that are no multiple of a cell
+@pytest.mark.parametrize("arch,batch", [(_chain([24, 72, 200, 40], 29), 2), (_bottleneck([88, 264], [1, 2], 60, 0.35), 3)])
+def test_int8_patch_kernel(arch, batch):
+    import paper_2306_17266_amd as S
+    from oracle import int8_eval as Q
+    from tests.test_gpu_int8 import _problem, _run
+    from workloads import quant
+    cfg = A.max_cfg(arch)
+    ctx, qm = _problem(arch, 71)
+    ctx.sushi_set_option(S.OPT_PATCH_CONV_MIN_PIXELS, 1)
+    xq = quant.quantize_input(T.make_input(71, 0, batch, cfg.resolution, arch.in_channels, False))
+    got = _run(ctx, cfg, xq, arch.n_classes)
+    ctx.close()
+    np.testing.assert_array_equal(got, Q.forward_int8(arch, qm, cfg, np.ascontiguousarray(xq.transpose(0, 3, 1, 2))))
+
+
+# Maps of 2 GiB and more go to the kernels with 64-bit addresses.  An image's logits do not depend on the batch: four
+# images, repeated, against the same four alone.
+@pytest.mark.parametrize("kernel,dtype,batch,arch", [
+    ("conv_mfma_kernel", "bf16", 260, _chain([64, 64, 136, 24], 256)),
+    ("conv_direct_kernel", "fp32", 132, _chain([64, 40], 256)),
+    ("dwconv_kernel", "bf16", 260, _mobile(1, 5, (2,), A.ACT_HSWISH, 512, 64))])
+def test_maps_of_two_gib(kernel, dtype, batch, arch):
+    import paper_2306_17266_amd as S
+    cfg = A.max_cfg(arch)
+    bf16 = dtype == "bf16"
+    blob, _ = make_problem(arch, 73, bf16)
+    ctx = S.Sushi(0)
+    ctx.sushi_load_supernet(arch, blob, S.BF16 if bf16 else S.FP32)
+    x = torch.from_numpy(T.make_input(73, 0, 4, cfg.resolution, arch.in_channels, bf16)).cuda()
+    x = x.to(torch.bfloat16) if bf16 else x
+    want = torch.full((4, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32)
+    ctx.sushi_infer(cfg, x, want)
+    logits = torch.full((batch, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32)
+    ctx.sushi_set_option(S.OPT_KERNEL_TIMING, 1)
+    ctx.sushi_infer(cfg, x.repeat(batch // 4, 1, 1, 1), logits)
+    torch.cuda.synchronize()
+    assert kernel in [k["name"] for k in ctx.sushi_get_kernel_stats() if k["launches"]]
+    ctx.close()
+    want = want.cpu().numpy()
+    for n, got in enumerate(logits.cpu().numpy()):
+        assert rel_l2(got, want[n % 4]) <= (2 * BF16_TOL if bf16 else 1e-5), n

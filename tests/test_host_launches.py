@@ -75,3 +75,40 @@ for arch, dtype, batch, res in ((A.resnet_arch(), "bf16", 1, 224), (A.resnet_arc
     ctx.close()
 ''')
     assert all(line.endswith(" ok") for line in out.splitlines()) and len(out.splitlines()) == 7, out
+
+
+def _nets_of_gpu_tests():
+    from tests import test_gpu_layer_kernels as t
+    return dict(tiled=t.TILED, few=t.FEW_PIXELS, depthwise=[(t.depthwise_net(k, s, size, c), b) for k in (3, 5, 7) for s in (1, 2) for size, c, b in t.DEPTHWISE],
+                stem=[(t.input_layer_net(r, s, w), b) for r, s, w, b in t.INPUT_LAYERS])
+
+
+def test_nets_of_the_gpu_tests_reach_their_kernels(tmp_path):
+    """Every variant of the tile, few-pixel, depthwise and input-layer kernels that a full-size SubNet reaches is reached by a net
+    of test_gpu_layer_kernels.py."""
+    out = run(tmp_path, '''
+seen = {}
+for dtype in ("bf16", "int8", "fp32"):
+    tile, small = set(), set()
+    for arch, batch in DATA["tiled"] if dtype != "fp32" else ():
+        tile |= {(k[1][0], o["R"], o["stride"], o["res"]) for o, k in layers(arch, dtype, batch) if k[0] == "conv_tile_kernel"}
+    for arch, batch in DATA["few"]:
+        small |= {(k[3] // 64, o["R"], o["stride"], o["res"]) for o, k in layers(arch, dtype, batch) if k[0] == "conv_small_kernel" and o["kind"] == 0}
+    seen[dtype] = (tile, small)
+seen["dw"] = {(k[0], tuple(k[1])) for arch, batch in DATA["depthwise"] for o, k in layers(arch, "bf16", batch) if o["kind"] == 1}
+seen["stem"] = {(k[0], tuple(k[1]) if k[0] == "stem_mfma_kernel" else (), o["stride"]) for arch, batch in DATA["stem"]
+                for o, k in layers(arch, "bf16", batch)[:1]}
+print(repr(seen))
+''', _nets_of_gpu_tests())
+    seen = eval(out)
+    # (wave groups, taps per side, stride, residual)
+    tile = {(1, 1, 1, 0), (1, 1, 1, 1), (1, 1, 2, 0), (2, 1, 1, 0), (2, 1, 1, 1), (2, 1, 2, 0), (1, 3, 1, 0), (1, 3, 2, 0), (2, 3, 1, 0), (2, 3, 2, 0),
+            (4, 3, 1, 0), (4, 3, 2, 0)}
+    assert seen["bf16"][0] >= tile and seen["int8"][0] >= tile | {(4, 1, 1, 0)}, seen
+    for dtype in ("bf16", "int8", "fp32"):
+        small = seen[dtype][1]
+        assert {w for w, _, _, _ in small} >= {1, 2, 3, 4, 8, 16} and {(r, s, res) for _, r, s, res in small} >= {(1, 1, 0), (1, 1, 1), (1, 2, 0), (3, 1, 0), (3, 2, 0)}, small
+    want = {("dw_mfma_kernel", v) for v in ((3, 1, 1, 3), (3, 2, 1, 3), (5, 1, 1, 5), (5, 1, 8, 5), (5, 2, 1, 5), (5, 2, 4, 4), (7, 1, 1, 7), (7, 1, 7, 4),
+                                            (7, 2, 1, 7), (7, 2, 4, 3))}
+    assert seen["dw"] >= want and {(k, v[:2]) for k, v in seen["dw"]} >= {("dwconv_rows_kernel", (r, s)) for r in (3, 5, 7) for s in (1, 2)}, seen["dw"]
+    assert seen["stem"] == {("stem_mfma_kernel", v, s) for v in ((1, 1), (1, 4), (2, 1), (2, 4)) for s in (1, 2)} | {("conv_direct_kernel", (), s) for s in (1, 2)}, seen["stem"]
