@@ -1,16 +1,16 @@
-// Dense convolution and fully connected layers with few pixels (one image, per-image vectors), bf16 and int8, on the matrix
-// cores: latency decides, so a layer is spread over as many waves as it has work for.
+// Dense convolution and fully connected layers with few pixels (one image, per-image vectors), bf16, int8 and all of the
+// float32 mode, on the matrix cores: latency decides, so a layer is spread over as many waves as it has work for.
 //
-// A workgroup computes 16 filters x 16 PT pixels; its WK = blockDim.x / 64 waves (chosen by the host) share the
-// reduction.  The reduction is one flat sequence of 16-byte cells, k = tap * (cells per tap) + cell; a step is four cells,
-// one matrix instruction (16x16x32_bf16, 16x16x64_i8) per pixel tile, and wave w takes steps w, w + WK, ...  Operands come straight from memory
-// in operand order, U steps in flight in registers: a step's registers are requested again as soon as it is multiplied.
-// Every load is issued on every path, past the end of the buffer where there is nothing to load (zeros arrive): a load
-// under a branch would make the wait for one step a wait for all of them.  The partial sums are added in the order of the
-// waves through LDS; the epilogue's constants and the residual are on their way from the start.
+// A workgroup computes 16 filters x 16 pixels; its WK = blockDim.x / 64 waves (chosen by the host) share the reduction.
+// The reduction is one flat sequence of 16-byte cells, k = tap * (cells per tap) + cell; a step is four cells, one matrix
+// instruction (16x16x32_bf16, 16x16x64_i8; four 16x16x4_f32), and wave w takes steps w, w + WK, ...  Operands come straight
+// from memory in operand order, U steps in flight in registers: a step's registers are requested again as soon as it is
+// multiplied.  Every load is issued on every path, past the end of the buffer where there is nothing to load (zeros arrive):
+// a load under a branch would make the wait for one step a wait for all of them.  The partial sums are added in the order
+// of the waves through LDS; the epilogue's constants and the residual are on their way from the start.
 //
-// Bound by the number of serial load rounds and, with several pixel tiles, by the activation gather (a wave load touches
-// 16 pixels' cache lines).  Consecutive tiles run on one XCD and share the weight tile in its L2.
+// Bound by the number of serial load rounds and, with many tiles, by the activation gather (a wave load touches 16 pixels'
+// cache lines) and the index arithmetic of a step.  Consecutive tiles run on one XCD and share the weight tile in its L2.
 #include "kernels.h"
 #include "device_common.h"
 
@@ -39,37 +39,31 @@ struct SmallGeom {
 // products and sums; which channel a lane holds does not matter as long as both operands agree).
 enum SmallType { ST_BF16, ST_IN32, ST_I8, ST_F32 };
 
-template <int PT, int U, int MAXT, SmallType TYPE>
+template <int U, int MAXT, SmallType TYPE>
 __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom g, QuantArgs q) {
     constexpr bool IN32 = TYPE == ST_IN32, I8 = TYPE == ST_I8, F32 = TYPE == ST_F32;
-    extern __shared__ float cs_red[];  // [WK][PT][4][64]
+    extern __shared__ float cs_red[];  // [WK][4][64]
     const int WK = blockDim.x >> 6, lane = threadIdx.x & 63;
     const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kg = lane >> 4;
     const int ntiles = g.tiles_f * g.tiles_m, per_xcd = (ntiles + 7) >> 3;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= ntiles) return;
-    const int tf = tile / g.tiles_m, f0 = tf * 16, m0 = (tile - tf * g.tiles_m) * PT * 16;
+    const int tf = tile / g.tiles_m, f0 = tf * 16, m = (tile - tf * g.tiles_m) * 16 + l16;  // (this lane's pixel)
     constexpr int CPC = I8 ? 16 : F32 ? 4 : 8, ES = IN32 ? 4 : 16 / CPC;  // channels per cell, bytes per element
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C * ES), 0x00020000);
     const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.w), 0, (int)((long)a.R * a.R * a.CG * a.Kpad * (F32 ? 32 : 16)), 0x00020000);
 
-    int boff[PT], hw0[PT][2];
-    bool live[PT];
-#pragma unroll
-    for (int p = 0; p < PT; ++p) {
-        const int m = m0 + p * 16 + l16;
-        live[p] = m < g.M;
-        const int t = fdiv(live[p] ? m : 0, g.dq), qq = (live[p] ? m : 0) - t * a.Q;
-        const int n = fdiv(t, g.dp), pp = t - n * a.P;
-        hw0[p][0] = pp * a.stride - a.pad, hw0[p][1] = qq * a.stride - a.pad;
-        boff[p] = ((n * a.H + hw0[p][0]) * a.W + hw0[p][1]) * a.C * ES;
-    }
+    const bool live = m < g.M;
+    const int pq = fdiv(live ? m : 0, g.dq), qq = (live ? m : 0) - pq * a.Q;
+    const int n = fdiv(pq, g.dp), pp = pq - n * a.P;
+    const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
+    const int boff = ((n * a.H + h0) * a.W + w0) * a.C * ES;
     const int woff = (f0 + l16) * (F32 ? 32 : 16);  // (filters are padded to 16)
-    cs_u32x4 rb[U][PT], rb2[IN32 ? U : 1][PT], ra[U];
-    unsigned in[U];  // int8: bits 0 .. PT - 1: the cell of pixel tile p holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
+    cs_u32x4 rb[U], rb2[IN32 ? U : 1], ra[U];
+    unsigned in[U];  // int8: bit 0: the cell holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
     auto load_step = [&](int step, int u) {
         const int k = step * 4 + kg;
         const bool kv = k < g.kcells;
@@ -80,22 +74,19 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
         in[u] = (kv ? 256u : 0u) | (cg * CPC + 8 >= a.C ? 512u : 0u);
         const int wcell = F32 ? (tap * a.CG + (cg >> 1)) * a.Kpad * 32 + (cg & 1) * 16 : (tap * a.CG + cg) * a.Kpad * 16;
         ra[u] = __builtin_amdgcn_raw_buffer_load_b128(rw, kv ? woff + wcell : CS_OOB, 0, 0);
-#pragma unroll
-        for (int p = 0; p < PT; ++p) {
-            const bool ok = kv && live[p] && (unsigned)(hw0[p][0] + dr) < (unsigned)a.H && (unsigned)(hw0[p][1] + ds) < (unsigned)a.W;
-            const int o = ok ? boff[p] + off : CS_OOB;
-            rb[u][p] = __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0);
-            if (I8 && ok) in[u] |= 1u << p;
-            if (IN32) rb2[IN32 ? u : 0][p] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? o + 16 : CS_OOB, 0, 0);
-        }
+        const bool ok = kv && live && (unsigned)(h0 + dr) < (unsigned)a.H && (unsigned)(w0 + ds) < (unsigned)a.W;
+        const int o = ok ? boff + off : CS_OOB;
+        rb[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0);
+        if (I8 && ok) in[u] |= 1u;
+        if (IN32) rb2[IN32 ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? o + 16 : CS_OOB, 0, 0);
     };
-    // what this wave's first tile of the epilogue needs (wave t finishes pixel tile t): issued before the operands
+    // what the epilogue needs (wave 0 finishes the tile): issued before the operands
     const int fb = f0 + kg * 4;
     const bool vec = (a.K & 3) == 0;
     float sc[4] = {1.f, 1.f, 1.f, 1.f}, sh[4] = {};
     int mult[4] = {}, shift[4] = {1, 1, 1, 1}, bias[4] = {};
     cs_u32x2 res = {0u, 0u};
-    if (wk < PT || WK == 1) {
+    if (wk == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int f = min(fb + i, a.K - 1);
@@ -106,8 +97,7 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
                 sh[i] = a.shift[f];
             }
         }
-        const int m = m0 + wk * 16 + l16;
-        if (a.res && vec && !F32 && fb < a.K && m < g.M) {
+        if (a.res && vec && !F32 && fb < a.K && live) {
             if (I8)
                 res[0] = *reinterpret_cast<const unsigned *>(static_cast<const int8_t *>(a.res) + (long)m * a.K + fb);
             else
@@ -119,33 +109,28 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
     __builtin_amdgcn_sched_barrier(0);
 
     typedef typename std::conditional<I8, cs_i32x4, f32x4_t>::type acc_t;
-    acc_t acc[PT];
-#pragma unroll
-    for (int p = 0; p < PT; ++p) acc[p] = acc_t{0, 0, 0, 0};
+    acc_t acc = acc_t{0, 0, 0, 0};
     const unsigned zfill = (unsigned)(q.zx & 0xFF) * 0x01010101u;
     auto multiply = [&](int u) {
+        if constexpr (I8) {
+            // a cell of the frame holds the code of the real value 0 (the input's zero point) in its active channels,
+            // the upper half of a cell that straddles the SubNet's channel count zeros
+            cs_u32x4 b = rb[u];
+            if ((in[u] & 256u) && !(in[u] & 1u)) b = cs_u32x4{zfill, zfill, zfill, zfill};
+            if (in[u] & 512u) b[2] = 0u, b[3] = 0u;
+            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(cs_i32x4, ra[u]), __builtin_bit_cast(cs_i32x4, b), acc, 0, 0, 0);
+        } else if constexpr (F32) {
+            const f32x4_t w = __builtin_bit_cast(f32x4_t, ra[u]), x = __builtin_bit_cast(f32x4_t, rb[u]);
 #pragma unroll
-        for (int p = 0; p < PT; ++p) {
-            if constexpr (I8) {
-                // a cell of the frame holds the code of the real value 0 (the input's zero point) in its active channels,
-                // the upper half of a cell that straddles the SubNet's channel count zeros
-                cs_u32x4 b = rb[u][p];
-                if ((in[u] & 256u) && !(in[u] >> p & 1u)) b = cs_u32x4{zfill, zfill, zfill, zfill};
-                if (in[u] & 512u) b[2] = 0u, b[3] = 0u;
-                acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(cs_i32x4, ra[u]), __builtin_bit_cast(cs_i32x4, b), acc[p], 0, 0, 0);
-            } else if constexpr (F32) {
-                const f32x4_t w = __builtin_bit_cast(f32x4_t, ra[u]), x = __builtin_bit_cast(f32x4_t, rb[u][p]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[p] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], x[i], acc[p], 0, 0, 0);
-            } else if constexpr (IN32) {
-                const bf16x8_t w = __builtin_bit_cast(bf16x8_t, ra[u]);
-                Frag hi, lo;
-                split_f32x8(__builtin_bit_cast(uint4, rb[u][p]), __builtin_bit_cast(uint4, rb2[u][p]), &hi.u, &lo.u);
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hi.v, acc[p], 0, 0, 0);
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, lo.v, acc[p], 0, 0, 0);
-            } else {
-                acc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ra[u]), __builtin_bit_cast(bf16x8_t, rb[u][p]), acc[p], 0, 0, 0);
-            }
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], x[i], acc, 0, 0, 0);
+        } else if constexpr (IN32) {
+            const bf16x8_t w = __builtin_bit_cast(bf16x8_t, ra[u]);
+            Frag hi, lo;
+            split_f32x8(__builtin_bit_cast(uint4, rb[u]), __builtin_bit_cast(uint4, rb2[u]), &hi.u, &lo.u);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hi.v, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, lo.v, acc, 0, 0, 0);
+        } else {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ra[u]), __builtin_bit_cast(bf16x8_t, rb[u]), acc, 0, 0, 0);
         }
     };
     // rounds of U steps; the steps of the last round have no successor
@@ -161,36 +146,38 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
 #pragma unroll
     for (int u = 0; u < U; ++u) multiply(u);  // (steps past the end multiply zeros)
 
-    auto finish = [&](const acc_t s, int t, bool preloaded) {
-        const int m = m0 + t * 16 + l16;
-        if (fb >= a.K || m >= g.M) return;
-        const long o = (long)m * a.K + fb;
-        if constexpr (I8) {  // (K is a multiple of 4)
-            const int lo = a.act == 1 ? q.zy : -128;
-            unsigned packed = 0, r = res[0];
-            if (a.res && !preloaded) r = *reinterpret_cast<const unsigned *>(static_cast<const int8_t *>(a.res) + o);
+    if (WK > 1) {
+        reinterpret_cast<acc_t *>(cs_red)[wk * 64 + lane] = acc;
+        __syncthreads();
+        if (wk != 0) return;
+        acc = acc_t{0, 0, 0, 0};
+        for (int k = 0; k < WK; ++k) acc += reinterpret_cast<const acc_t *>(cs_red)[k * 64 + lane];
+    }
+    if (fb >= a.K || !live) return;
+    const long o = (long)m * a.K + fb;
+    if constexpr (I8) {  // (K is a multiple of 4)
+        const int lo = a.act == 1 ? q.zy : -128;
+        unsigned packed = 0;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                long long t64 = rr64((long long)(s[i] + bias[i]) * (long long)mult[i], shift[i]);
-                if (a.res) t64 += rr64((long long)((int)(int8_t)(r >> (8 * i)) - q.z_res) * (long long)q.m_res, q.sh_res);
-                t64 += q.zy;
-                const int c = (int)(t64 < lo ? lo : t64 > 127 ? 127 : t64);
-                packed |= (unsigned)(c & 0xFF) << (8 * i);
-            }
-            *reinterpret_cast<unsigned *>(static_cast<int8_t *>(a.y) + o) = packed;
-        } else {
+        for (int i = 0; i < 4; ++i) {
+            long long t64 = rr64((long long)(acc[i] + bias[i]) * (long long)mult[i], shift[i]);
+            if (a.res) t64 += rr64((long long)((int)(int8_t)(res[0] >> (8 * i)) - q.z_res) * (long long)q.m_res, q.sh_res);
+            t64 += q.zy;
+            const int c = (int)(t64 < lo ? lo : t64 > 127 ? 127 : t64);
+            packed |= (unsigned)(c & 0xFF) << (8 * i);
+        }
+        *reinterpret_cast<unsigned *>(static_cast<int8_t *>(a.y) + o) = packed;
+    } else {
         float v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = s[i] * sc[i] + sh[i];
+        for (int i = 0; i < 4; ++i) v[i] = acc[i] * sc[i] + sh[i];
         if (F32 && a.res) {
             for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += static_cast<const float *>(a.res)[o + i];
         } else if (a.res) {
-            const uint16_t *rp = static_cast<const uint16_t *>(a.res) + o;
             if (vec) {
-                const cs_u32x2 r = preloaded ? res : *reinterpret_cast<const cs_u32x2 *>(rp);
-                v[0] += bf2f(r[0] & 0xFFFFu), v[1] += bf2f(r[0] >> 16), v[2] += bf2f(r[1] & 0xFFFFu), v[3] += bf2f(r[1] >> 16);
+                v[0] += bf2f(res[0] & 0xFFFFu), v[1] += bf2f(res[0] >> 16), v[2] += bf2f(res[1] & 0xFFFFu), v[3] += bf2f(res[1] >> 16);
             } else {
-                for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += bf2f(rp[i]);
+                for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += bf2f(static_cast<const uint16_t *>(a.res)[o + i]);
             }
         }
 #pragma unroll
@@ -208,30 +195,15 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
             else
                 for (int i = 0; i < min(4, a.K - fb); ++i) yp[i] = (uint16_t)f2bf(v[i]);
         }
-        }
-    };
-    if (WK == 1) {
-#pragma unroll
-        for (int p = 0; p < PT; ++p) finish(acc[p], p, p == 0);
-        return;
-    }
-#pragma unroll
-    for (int p = 0; p < PT; ++p)
-        reinterpret_cast<acc_t *>(cs_red)[(wk * PT + p) * 64 + lane] = acc[p];
-    __syncthreads();
-    for (int t = wk; t < PT; t += WK) {
-        acc_t s = acc_t{0, 0, 0, 0};
-        for (int k = 0; k < WK; ++k) s += reinterpret_cast<const acc_t *>(cs_red)[(k * PT + t) * 64 + lane];
-        finish(s, t, t == wk);
     }
 }
 
-template <int PT, SmallType TYPE>
+template <SmallType TYPE>
 static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
-    constexpr int U = 4, CPC = TYPE == ST_I8 ? 16 : TYPE == ST_F32 ? 4 : 8;  // (two steps in flight cost up to 1 us, three with PT = 2 gain nothing)
+    constexpr int U = 4, CPC = TYPE == ST_I8 ? 16 : TYPE == ST_F32 ? 4 : 8;  // (two steps in flight cost up to 1 us)
     SmallGeom g;
     g.M = a.B * a.P * a.Q;
-    g.tiles_f = (a.K + 15) / 16, g.tiles_m = (g.M + 16 * PT - 1) / (16 * PT);
+    g.tiles_f = (a.K + 15) / 16, g.tiles_m = (g.M + 15) / 16;
     const int cells = (a.C + CPC - 1) / CPC;
     g.kcells = a.R * a.R * cells, g.nsteps = (g.kcells + 3) / 4;
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells), g.dr = make_fastdiv(a.R);
@@ -243,8 +215,8 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
     int wk = std::max(1, std::min((g.nsteps + U - 1) / U, tiles <= 256 ? 16 : tiles <= (TYPE == ST_I8 ? 512 : 768) ? 8 : 4));
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);
     while (wk > 1 && (long)per_xcd * 8 * 64 * wk >= 1l << 32) --wk;  // (a launch has fewer than 2^32 threads)
-    const size_t lds = wk > 1 ? (size_t)wk * PT * 1024 : 0;
-    hipLaunchKernelGGL((conv_small_kernel<PT, U, 1024, TYPE>), dim3(per_xcd * 8), dim3(64 * wk), lds, s, a, g, q);
+    const size_t lds = wk > 1 ? (size_t)wk * 1024 : 0;
+    hipLaunchKernelGGL((conv_small_kernel<U, 1024, TYPE>), dim3(per_xcd * 8), dim3(64 * wk), lds, s, a, g, q);
     return hipGetLastError();
 }
 
@@ -257,7 +229,7 @@ static bool small_fits(const ConvArgs &a, long es) {
 hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s) {
     if (!a.in_f32) {
         if (!small_fits(a, 2)) return hipErrorNotSupported;
-        return launch_small<1, ST_BF16>(a, QuantArgs{}, s);
+        return launch_small<ST_BF16>(a, QuantArgs{}, s);
     }
     // float32 vectors: rows in pieces below 2 GiB
     if (a.H * a.W != 1 || a.res || !a.out_f32) return hipErrorInvalidValue;
@@ -268,7 +240,7 @@ hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s) {
         part.x = static_cast<const float *>(a.x) + n * a.C;
         part.y = static_cast<float *>(a.y) + n * a.K;
         if (!small_fits(part, 4)) return hipErrorInvalidValue;
-        const hipError_t e = launch_small<1, ST_IN32>(part, QuantArgs{}, s);
+        const hipError_t e = launch_small<ST_IN32>(part, QuantArgs{}, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -276,12 +248,12 @@ hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s) {
 
 hipError_t launch_conv_small_f32(const ConvArgs &a, hipStream_t s) {
     if (!small_fits(a, 4)) return hipErrorNotSupported;
-    return launch_small<1, ST_F32>(a, QuantArgs{}, s);
+    return launch_small<ST_F32>(a, QuantArgs{}, s);
 }
 
 hipError_t launch_conv_small_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
     if (!small_fits(a, 1) || (a.K & 3)) return hipErrorInvalidValue;
-    return launch_small<1, ST_I8>(a, q, s);
+    return launch_small<ST_I8>(a, q, s);
 }
 
 }  // namespace sushi

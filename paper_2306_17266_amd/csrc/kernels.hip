@@ -1,13 +1,10 @@
 // Device kernels of the SubNet forward pass (gfx950 / CDNA4).  Layouts: see kernels.h.
 //
-// Dense convolutions and fully connected layers in bf16 run as implicit GEMMs on the matrix cores
-// (v_mfma_f32_16x16x32_bf16, float32 accumulation): filters are the MFMA rows, output pixels the
-// MFMA columns, so each lane ends up with four consecutive output channels of one pixel and the
-// channels-last store is an 8-byte write.  Both operands are read straight from global memory
-// in operand order (16 bytes per lane): the packed weight layout makes a 16 x 32 weight fragment
-// four 256-byte runs, and a channels-last activation row supplies 64 contiguous bytes per pixel.
-// Everything else (depthwise, pooling, squeeze-excite gating, the float32 mode) is bandwidth
-// work on the vector ALUs with 16- or 32-byte accesses per lane.
+// The general kernels: what conv_small.hip, conv_tile.hip, conv_patch.hip, stem.hip, dwconv.hip and dwconv_mfma.hip do not
+// cover, pooling, squeeze-excite gating, and the dispatch.  In the matrix-core kernels filters are the rows, output pixels the
+// columns, so each lane ends up with four consecutive output channels of one pixel and the channels-last store is an
+// 8-byte write; the packed weight layout makes a 16 x 32 weight fragment four 256-byte runs, and a channels-last activation
+// row supplies 64 contiguous bytes per pixel.
 #include "kernels.h"
 #include "device_common.h"
 
@@ -156,7 +153,7 @@ __device__ __forceinline__ void store_tile(const ConvArgs &a, const f32x4_t acc,
     }
 }
 
-// Large problems (many pixels and filters; batch 16): the classic shared-memory tiling.  A workgroup
+// Tensors of 2 GiB and more (64-bit addresses): the classic shared-memory tiling.  A workgroup
 // of four waves (2 x 2) computes BN filters x BM pixels with 32 x 32 x 16 MFMAs.  Per reduction step
 // (one tap, 32 channels) the BN x 32 weight tile and the BM x 32 activation tile are staged in LDS as
 // [8-channel group][row] 16-byte cells, so a wave's operand read is four contiguous 512-byte runs;
@@ -541,19 +538,9 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
     if (e == hipErrorNotSupported) e = picked(launch_conv_tile(a, s, patch && !chosen), KC_CONV_TILE);
     if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch(a, s), KC_CONV_PATCH);
     if (e != hipErrorNotSupported) return e;
-    // What none of them covers (tensors of 2 GiB and more, filter counts that are no multiple of 8): LDS-tiled workgroups,
-    // the largest tile that still yields two workgroups per compute unit; few tiles as above.
+    // What none of them covers: tensors of 2 GiB and more, weights of 1 GiB and more.
     *kc = KC_CONV_MFMA;
-    if (a.K > 64 && ((M + 127) / 128) * ((a.K + 127) / 128) >= 512) return launch_mfma<128, 128>(a, s);
-    if (((M + 127) / 128) * ((a.K + 63) / 64) >= 512) return launch_mfma<64, 128>(a, s);
-    if (((M + 63) / 64) * ((a.K + 63) / 64) < 384) {
-        e = launch_conv_small(a, s);
-        if (e != hipErrorNotSupported) {
-            *kc = KC_CONV_SMALL;
-            return e;
-        }
-    }
-    return launch_mfma<64, 64>(a, s);
+    return a.K > 64 ? launch_mfma<128, 128>(a, s) : launch_mfma<64, 128>(a, s);
 }
 
 hipError_t launch_dwconv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc) {
