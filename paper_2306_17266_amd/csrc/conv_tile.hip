@@ -27,7 +27,7 @@ typedef __attribute__((ext_vector_type(4))) int ct_i32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned ct_u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned ct_u32x2;
 constexpr int CT_OOB = 0x7FFFFFF0;
-constexpr int CT_FAR = 0x40000000;  // added to any offset into the weights (below 1 GiB) it lies past their end
+constexpr unsigned CT_FAR = 0x40000000u;  // added to any offset into the weights (below 1 GiB), also twice, it lies past their end
 
 struct TileGeom {
     int tiles_f, tiles_m;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
             }
         }
     }
-    const int woff = f0 + lane < a.Kpad ? (f0 + lane) * 16 : CT_FAR;
+    const unsigned woff = f0 + lane < a.Kpad ? (unsigned)(f0 + lane) * 16u : CT_FAR;
     const int k0 = grp * g.per * 8;  // first cell of this group
     ct_u32x4 ra[D][2], rb[D][NB];
     unsigned rin[D];  // int8: bits 0 .. NB - 1: the cell of pixel i holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
@@ -95,8 +95,8 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
             const int k = k0 + s * 8 + wave + 4 * i;
             const int tap = R == 1 ? 0 : fdiv(k, g.dcell);
             const int cg = k - tap * g.dcell.d;
-            const int off = k < g.kcells ? (tap * a.CG + cg) * a.Kpad * 16 : CT_FAR;
-            qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, woff + off, 0, 0);
+            const unsigned off = k < g.kcells ? (unsigned)((tap * a.CG + cg) * a.Kpad) * 16u : CT_FAR;
+            qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(woff + off), 0, 0);
         }
         const int k = k0 + s * 8 + bk;
         const bool live = k < g.kcells;

@@ -7,9 +7,10 @@
 // one: a lane loads the aligned words around its elements (buffer loads: beyond the tensor they return zeros) and
 // shifts them into place; elements outside the image are masked out.
 //
-// Bound by memory: the output map is five times the input.  One thread per pixel and four filters on the vector ALUs
-// (conv_direct_kernel, which keeps every other channel count) took 234 us for 61 images of 224 x 224 to 24 filters and
-// 151 us for 64 images to 16: every thread read its patch element by element.  Here: about 23 us each, 3.1 TB/s.
+// Bound by memory (with stride 2 the output map of 24 filters is twice the input).  One thread per pixel and four filters
+// on the vector ALUs (conv_direct_kernel, which keeps every other channel count) took 234 us for 61 images of 224 x 224 to 24
+// filters and 151 us for 64 images to 16: every thread read its patch element by element.  Here: 24 us (55 MB, 2.3 TB/s)
+// and 21 us (45 MB, 2.2 TB/s).
 #include "kernels.h"
 #include "device_common.h"
 

@@ -329,3 +329,32 @@ def test_maps_of_two_gib(kernel, dtype, batch, arch):
     want = want.cpu().numpy()
     for n, got in enumerate(logits.cpu().numpy()):
         assert rel_l2(got, want[n % 4]) <= (2 * BF16_TOL if bf16 else 1e-5), n
+
+
+# An input that starts one element into its buffer: aligned to its element type and no more.  Three and eight input channels (the
+# latter read in whole cells), few and many pixels.
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "int8"])
+@pytest.mark.parametrize("channels,res,batch", [(3, 9, 2), (8, 9, 1), (8, 30, 8)])
+def test_unaligned_input(dtype, channels, res, batch):
+    import paper_2306_17266_amd as S
+    arch = _chain([24, 40], res, channels=channels)
+    cfg = A.max_cfg(arch)
+    torch_type = {"bf16": torch.bfloat16, "fp32": torch.float32, "int8": torch.int8}[dtype]
+    if dtype == "int8":
+        from tests.test_gpu_int8 import _problem
+        ctx, _ = _problem(arch, 79)
+    else:
+        ctx = S.Sushi(0)
+        ctx.sushi_load_supernet(arch, make_problem(arch, 79, dtype == "bf16")[0], S.BF16 if dtype == "bf16" else S.FP32)
+    x = torch.from_numpy(T.make_input(79, 0, batch, res, channels, dtype == "bf16")).cuda()
+    x = torch.round(x * 32).clamp(-128, 127).to(torch_type) if dtype == "int8" else x.to(torch_type)
+    shifted = torch.empty(x.numel() + 8, device="cuda", dtype=torch_type)[1:1 + x.numel()].view(x.shape)
+    shifted.copy_(x)
+    out = []
+    for t in (x, shifted):
+        out.append(torch.full((batch, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32))
+        ctx.sushi_infer(cfg, t, out[-1])
+    torch.cuda.synchronize()
+    ctx.close()
+    # (the bf16 input layer has another kernel for odd addresses)
+    assert rel_l2(out[1].cpu().numpy(), out[0].cpu().numpy()) <= (BF16_TOL if dtype == "bf16" and channels == 3 else 0.0)
