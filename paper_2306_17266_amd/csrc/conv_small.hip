@@ -207,10 +207,10 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
     const int cells = (a.C + CPC - 1) / CPC;
     g.kcells = a.R * a.R * cells, g.nsteps = (g.kcells + 3) / 4;
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells), g.dr = make_fastdiv(a.R);
-    // Waves per tile, each with at least one round of U steps: as many as run at once.  A compute unit holds 16 of these
-    // waves, so 16 up to 256 tiles (7 x 7 x 576 3x3, 144 tiles: 4, 8, 16 waves 16.2, 10.2, 8.2 us in int8), 8 up to 512 and in
-    // bf16 768 (3 x 7 x 7 x 720 3x3, 450 tiles, bf16: 21.3, 13.2, 14.2), 4 beyond: there a tile with 8 takes two tiles' places
-    // (8 x 14 x 14 x 208 3x3, 1274 tiles, int8: 8.9, 11.2, 11.2).
+    // Waves per tile, each with at least one round of U steps: many while every compute unit has few tiles, fewer once a tile
+    // would take the places of others (of these waves a compute unit holds 20 in int8, 32 in bf16).  4, 8, 16 waves, us:
+    // 7 x 7 x 576 3x3, 144 tiles, int8 16.2, 10.2, 8.2; 3 x 7 x 7 x 720 3x3, 450 tiles, bf16 21.3, 13.2, 14.2; 8 x 14 x 14 x 208
+    // 3x3, 1274 tiles, int8 8.9, 11.2, 11.2.
     const long tiles = (long)g.tiles_m * g.tiles_f;
     int wk = std::max(1, std::min((g.nsteps + U - 1) / U, tiles <= 256 ? 16 : tiles <= (TYPE == ST_I8 ? 512 : 768) ? 8 : 4));
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);

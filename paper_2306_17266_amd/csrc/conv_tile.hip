@@ -325,8 +325,9 @@ static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStrea
 // grows with tiles x steps; this kernel's grows with the serial steps of one workgroup.  Fits in us to 45 layer shapes from
 // 1 x 7 x 7 to 32 x 7 x 7 and 1 x 112 x 112 (constants common to both left out): small = W / 6500 (bf16 1x1), W / 8500
 // (bf16 3x3), W / 5000 (int8) with W = 16 x 16 tiles x steps of four cells; tile = 0.4 + steps per group x 0.23, 0.42, 0.75
-// (int8 0.5, 0.75, 1.35) for one, two, four groups, and 1 for 3x3.  On both sides of the line: 2 x 28 x 28 x 176 3x3 9.9 us
-// small, 10.2 tile; 4 x 28 x 28 16.9 and 10.5; 1 x 56 x 56, 208 -> 56 3.5 and 4.5, 208 -> 128 5.3 and 4.5.
+// (int8 0.5, 0.75, 1.35) for one, two, four groups, and 1 for 3x3.  On both sides of the line (traces of whole queries): 2 x
+// 28 x 28 x 176 3x3 10.4 us small, 11.4 tile; 3 x 28 x 28 13.3 and 11.8; 1 x 56 x 56, 208 -> 56 4.8 and 5.4, 208 -> 128
+// 5.8 and 5.3.  Over 500 layers of both precisions the line costs 0.3 % over the better of the two.
 bool conv_small_is_faster(const ConvArgs &a, bool i8) {
     const double M = (double)a.B * a.P * a.Q;
     const int cells = a.R * a.R * ((a.C + (i8 ? 15 : 7)) / (i8 ? 16 : 8));

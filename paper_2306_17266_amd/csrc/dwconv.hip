@@ -1,4 +1,5 @@
-// Depthwise k x k convolution for the per-layer launch path (bf16, activations [B][H][W][C]).
+// Depthwise k x k convolution for the per-layer launch path on the vector ALUs (bf16, activations [B][H][W][C]): 3x3 on all
+// but small maps, larger kernels on narrow maps of many images; the rest runs in dwconv_mfma.hip, which draws the line.
 //
 // A thread produces a strip of DWR_T neighbouring outputs for one group of 8 channels: one below the other in a
 // column (stride 1) or side by side in a row (stride 2).  For every tap line across the strip it requests, in
