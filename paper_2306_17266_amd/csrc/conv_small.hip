@@ -7,7 +7,7 @@
 // from memory in operand order, U steps in flight in registers: a step's registers are requested again as soon as it is
 // multiplied.  Every load is issued on every path, past the end of the buffer where there is nothing to load (zeros arrive):
 // a load under a branch would make the wait for one step a wait for all of them.  The partial sums are added in the order
-// of the waves through LDS; the epilogue's constants and the residual are on their way from the start.
+// of the waves through LDS; the epilogue's constants and the residual are requested behind the first U steps.
 //
 // Bound by the number of serial load rounds and, with many tiles, by the activation gather (a wave load touches 16 pixels'
 // cache lines) and the index arithmetic of a step.  Consecutive tiles run on one XCD and share the weight tile in its L2.
@@ -22,7 +22,6 @@ namespace sushi {
 typedef __attribute__((ext_vector_type(4))) unsigned cs_u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned cs_u32x2;
 typedef __attribute__((ext_vector_type(4))) int cs_i32x4;
-constexpr int CS_OOB = 0x7FFFFFF0;
 
 struct SmallGeom {
     int tiles_f, tiles_m;
@@ -49,7 +48,7 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
     const int ntiles = g.tiles_f * g.tiles_m, per_xcd = (ntiles + 7) >> 3;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= ntiles) return;
-    const int tf = tile / g.tiles_m, f0 = tf * 16, m = (tile - tf * g.tiles_m) * 16 + l16;  // (this lane's pixel)
+    const int tf = tile / g.tiles_m, f0 = tf * 16, m0 = (tile - tf * g.tiles_m) * 16, m = m0 + l16;  // (m: this lane's pixel)
     constexpr int CPC = I8 ? 16 : F32 ? 4 : 8, ES = IN32 ? 4 : 16 / CPC;  // channels per cell, bytes per element
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C * ES), 0x00020000);
@@ -60,52 +59,55 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
     const int pq = fdiv(live ? m : 0, g.dq), qq = (live ? m : 0) - pq * a.Q;
     const int n = fdiv(pq, g.dp), pp = pq - n * a.P;
     const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
-    const int boff = ((n * a.H + h0) * a.W + w0) * a.C * ES;
-    const int woff = (f0 + l16) * (F32 ? 32 : 16);  // (filters are padded to 16)
+    const unsigned boff = (unsigned)(((n * a.H + h0) * a.W + w0) * a.C * ES);
+    const unsigned woff = (unsigned)(f0 + l16) * (F32 ? 32 : 16);  // (filters are padded to 16)
     cs_u32x4 rb[U], rb2[IN32 ? U : 1], ra[U];
     unsigned in[U];  // int8: bit 0: the cell holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
     auto load_step = [&](int step, int u) {
         const int k = step * 4 + kg;
-        const bool kv = k < g.kcells;
-        const int kk = kv ? k : 0;
-        const int tap = fdiv(kk, g.dcell), cg = kk - tap * g.dcell.d;
+        const int tap = fdiv(k, g.dcell), cg = k - tap * g.dcell.d;
         const int dr = fdiv(tap, g.dr), ds = tap - dr * a.R;
-        const int off = ((dr * a.W + ds) * a.C + cg * CPC) * ES;
-        in[u] = (kv ? 256u : 0u) | (cg * CPC + 8 >= a.C ? 512u : 0u);
-        const int wcell = F32 ? (tap * a.CG + (cg >> 1)) * a.Kpad * 32 + (cg & 1) * 16 : (tap * a.CG + cg) * a.Kpad * 16;
-        ra[u] = __builtin_amdgcn_raw_buffer_load_b128(rw, kv ? woff + wcell : CS_OOB, 0, 0);
-        const bool ok = kv && live && (unsigned)(h0 + dr) < (unsigned)a.H && (unsigned)(w0 + ds) < (unsigned)a.W;
-        const int o = ok ? boff + off : CS_OOB;
-        rb[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, o, 0, 0);
-        if (I8 && ok) in[u] |= 1u;
-        if (IN32) rb2[IN32 ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? o + 16 : CS_OOB, 0, 0);
+        const unsigned off = ((unsigned)(dr * a.W + ds) * (unsigned)a.C + (unsigned)cg * CPC) * ES;
+        const unsigned wcell = F32 ? (unsigned)(tap * a.CG + (cg >> 1)) * (unsigned)a.Kpad * 32 + (cg & 1) * 16
+                                   : (unsigned)(tap * a.CG + cg) * (unsigned)a.Kpad * 16;
+        const bool kv = k < g.kcells;
+        const bool ok = kv & live & ((unsigned)(h0 + dr) < (unsigned)a.H) & ((unsigned)(w0 + ds) < (unsigned)a.W);
+        ra[u] = __builtin_amdgcn_raw_buffer_load_b128(rw, offset_if(kv, woff + wcell), 0, 0);
+        rb[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, offset_if(ok, boff + off), 0, 0);
+        if (IN32) rb2[IN32 ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rx, offset_if(ok, boff + off + 16), 0, 0);
+        in[u] = (ok ? 1u : 0u) | (kv ? 256u : 0u) | (cg * CPC + 8 >= a.C ? 512u : 0u);
     };
-    // what the epilogue needs (wave 0 finishes the tile): issued before the operands
-    const int fb = f0 + kg * 4;
-    const bool vec = (a.K & 3) == 0;
-    float sc[4] = {1.f, 1.f, 1.f, 1.f}, sh[4] = {};
-    int mult[4] = {}, shift[4] = {1, 1, 1, 1}, bias[4] = {};
-    cs_u32x2 res = {0u, 0u};
-    if (wk == 0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int f = min(fb + i, a.K - 1);
-            if (I8) {  // (the zero-point term goes to the bias: minus z_x times the sum of the active weights)
-                mult[i] = q.qmult[f], shift[i] = q.qshift[f], bias[i] = q.qbias[f] - q.zx * q.wsum[f];
-            } else {
-                if (a.scale) sc[i] = a.scale[f];
-                sh[i] = a.shift[f];
-            }
-        }
-        if (a.res && vec && !F32 && fb < a.K && live) {
-            if (I8)
-                res[0] = *reinterpret_cast<const unsigned *>(static_cast<const int8_t *>(a.res) + (long)m * a.K + fb);
-            else
-                res = *reinterpret_cast<const cs_u32x2 *>(static_cast<const uint16_t *>(a.res) + (long)m * a.K + fb);
-        }
-    }
 #pragma unroll
     for (int u = 0; u < U; ++u) load_step(wk + u * WK, u);
+    // what the epilogue needs, requested by every wave (nothing arrives at those that do not finish the tile), behind the
+    // operands: constants of the lane's four filters, four values of the residual
+    const int fb = f0 + kg * 4;
+    const bool last = wk == 0;
+    cs_u32x4 cst[I8 ? 4 : 2];
+    {
+        const void *const src[4] = {I8 ? (const void *)q.qmult : (const void *)a.scale, I8 ? (const void *)q.qshift : (const void *)a.shift, q.qbias, q.wsum};
+#pragma unroll
+        for (int i = 0; i < (I8 ? 4 : 2); ++i)
+            cst[i] = __builtin_amdgcn_raw_buffer_load_b128(
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(src[i]), 0, src[i] ? a.K * 4 : 0, 0x00020000), offset_if(last, (unsigned)fb * 4), 0, 0);
+    }
+    const bool vec = (a.K & 3) == 0;
+    constexpr int OS = F32 ? 4 : I8 ? 1 : 2;  // bytes per element of the residual
+    cs_u32x4 res = {0u, 0u, 0u, 0u};
+    {
+        const int rows = min(16, g.M - m0);  // (the tile's own: a residual may be larger than a buffer can be)
+        const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(static_cast<const char *>(a.res)) + (a.res ? (long)m0 * a.K * OS : 0), 0, a.res && vec ? rows * a.K * OS : 0, 0x00020000);
+        const int o = offset_if(last & (fb < a.K), (unsigned)((l16 * a.K + fb) * OS));
+        if constexpr (F32) {
+            res = __builtin_amdgcn_raw_buffer_load_b128(rr, o, 0, 0);
+        } else if constexpr (I8) {
+            res[0] = __builtin_amdgcn_raw_buffer_load_b32(rr, o, 0, 0);
+        } else {
+            const cs_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rr, o, 0, 0);
+            res[0] = v[0], res[1] = v[1];
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);
 
     typedef typename std::conditional<I8, cs_i32x4, f32x4_t>::type acc_t;
@@ -160,7 +162,9 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
         unsigned packed = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            long long t64 = rr64((long long)(acc[i] + bias[i]) * (long long)mult[i], shift[i]);
+            // (the zero-point term goes to the bias: minus z_x times the sum of the active weights)
+            const int bias = (int)cst[I8 ? 2 : 0][i] - q.zx * (int)cst[I8 ? 3 : 0][i];
+            long long t64 = rr64((long long)(acc[i] + bias) * (long long)(int)cst[0][i], (int)cst[1][i]);
             if (a.res) t64 += rr64((long long)((int)(int8_t)(res[0] >> (8 * i)) - q.z_res) * (long long)q.m_res, q.sh_res);
             t64 += q.zy;
             const int c = (int)(t64 < lo ? lo : t64 > 127 ? 127 : t64);
@@ -168,16 +172,16 @@ __global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom 
         }
         *reinterpret_cast<unsigned *>(static_cast<int8_t *>(a.y) + o) = packed;
     } else {
+        const f32x4_t sc = a.scale ? __builtin_bit_cast(f32x4_t, cst[0]) : f32x4_t{1.f, 1.f, 1.f, 1.f}, sh = __builtin_bit_cast(f32x4_t, cst[1]);
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = acc[i] * sc[i] + sh[i];
-        if (F32 && a.res) {
-            for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += static_cast<const float *>(a.res)[o + i];
-        } else if (a.res) {
-            if (vec) {
-                v[0] += bf2f(res[0] & 0xFFFFu), v[1] += bf2f(res[0] >> 16), v[2] += bf2f(res[1] & 0xFFFFu), v[3] += bf2f(res[1] >> 16);
+        if (a.res) {
+            if (!vec) {
+                for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += F32 ? static_cast<const float *>(a.res)[o + i] : bf2f(static_cast<const uint16_t *>(a.res)[o + i]);
             } else {
-                for (int i = 0; i < min(4, a.K - fb); ++i) v[i] += bf2f(static_cast<const uint16_t *>(a.res)[o + i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] += F32 ? __uint_as_float(res[i]) : bf2f(i & 1 ? res[i >> 1] >> 16 : res[i >> 1] & 0xFFFFu);
             }
         }
 #pragma unroll

@@ -27,7 +27,6 @@ typedef __attribute__((ext_vector_type(4))) int ct_i32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned ct_u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned ct_u32x2;
 constexpr int CT_OOB = 0x7FFFFFF0;
-constexpr unsigned CT_FAR = 0x40000000u;  // added to any offset into the weights (below 1 GiB), also twice, it lies past their end
 
 struct TileGeom {
     int tiles_f, tiles_m;
@@ -64,8 +63,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     // what this thread stages: cell bk of pixels (gt >> 3) + 32 i (byte offset of the pixel's window, one bit per tap
     // inside the image), weight cells wave and wave + 4 of filter f0 + lane
     const int bk = gt & 7;
-    int boff[NB];
-    unsigned bmask[NB];
+    unsigned boff[NB], bmask[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int m = m0 + (gt >> 3) + 32 * i;
@@ -73,7 +71,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
         const int t = fdiv(live ? m : 0, g.dq), qq = (live ? m : 0) - t * a.Q;
         const int n = fdiv(t, g.dp), pp = t - n * a.P;
         const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
-        boff[i] = ((n * a.H + h0) * a.W + w0) * a.C * ES;
+        boff[i] = (unsigned)(((n * a.H + h0) * a.W + w0) * a.C * ES);
         bmask[i] = 0;
         if (R == 1) {
             bmask[i] = live ? 1u : 0u;
@@ -85,7 +83,8 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
             }
         }
     }
-    const unsigned woff = f0 + lane < a.Kpad ? (unsigned)(f0 + lane) * 16u : CT_FAR;
+    const unsigned woff = (unsigned)(f0 + lane) * 16u;
+    const bool wlive = f0 + lane < a.Kpad;
     const int k0 = grp * g.per * 8;  // first cell of this group
     ct_u32x4 ra[D][2], rb[D][NB];
     unsigned rin[D];  // int8: bits 0 .. NB - 1: the cell of pixel i holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
@@ -95,22 +94,21 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
             const int k = k0 + s * 8 + wave + 4 * i;
             const int tap = R == 1 ? 0 : fdiv(k, g.dcell);
             const int cg = k - tap * g.dcell.d;
-            const unsigned off = k < g.kcells ? (unsigned)((tap * a.CG + cg) * a.Kpad) * 16u : CT_FAR;
-            qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)(woff + off), 0, 0);
+            const unsigned off = (unsigned)(tap * a.CG + cg) * (unsigned)a.Kpad * 16u;
+            qa[i] = __builtin_amdgcn_raw_buffer_load_b128(rw, offset_if(wlive & (k < g.kcells), woff + off), 0, 0);
         }
         const int k = k0 + s * 8 + bk;
-        const bool live = k < g.kcells;
-        const int tap = R == 1 ? 0 : fdiv(live ? k : 0, g.dcell);
-        const int cg = (live ? k : 0) - tap * g.dcell.d;
+        const unsigned live = k < g.kcells ? 1u : 0u;
+        const int tap = R == 1 ? 0 : fdiv(k, g.dcell);
+        const int cg = k - tap * g.dcell.d;
         const int dr = R == 1 ? 0 : (tap * 11) >> 5, ds = tap - dr * R;  // (tap / 3 for tap < 9)
-        const int off = ((dr * a.W + ds) * a.C + cg * CPC) * ES;
-        in = live ? 256u : 0u;
-        if (I8 && cg * CPC + 8 >= a.C) in |= 512u;
+        const unsigned off = ((unsigned)(dr * a.W + ds) * (unsigned)a.C + (unsigned)cg * CPC) * ES;
+        in = live << 8 | (I8 && cg * CPC + 8 >= a.C ? 512u : 0u);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const bool ok = live && (bmask[i] >> tap & 1u);
-            qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? boff[i] + off : CT_OOB, 0, 0);
-            if (I8 && ok) in |= 1u << i;
+            const unsigned ok = bmask[i] >> (tap & 31) & live;
+            qb[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, offset_if(ok, boff[i] + off), 0, 0);
+            if (I8) in |= ok << i;
         }
     };
     // int8: a cell of the frame holds the code of the real value 0 (the input's zero point) in its active channels, the
@@ -297,7 +295,7 @@ static bool tile_covers(const ConvArgs &a) {
     if (a.in_f32 || a.out_f32 || (a.C & 7) || a.C < 8 || (a.K & 7) || a.K < 8) return false;
     if (!(a.R == 1 || a.R == 3) || a.pad != (a.R - 1) / 2 || a.stride < 1 || a.stride > 2 || a.Rmax != a.R) return false;
     const long M = (long)a.B * a.P * a.Q, lim = (1l << 31) - 4096;
-    return M * a.K * es < lim && (long)a.B * a.H * a.W * a.C * es < lim && (long)a.R * a.R * a.CG * a.Kpad * 16 < CT_FAR;
+    return M * a.K * es < lim && (long)a.B * a.H * a.W * a.C * es < lim && (long)a.R * a.R * a.CG * a.Kpad * 16 < (1l << 30);
 }
 
 // Wave groups per workgroup: a reduction is split where the tiles leave compute units without enough waves and each

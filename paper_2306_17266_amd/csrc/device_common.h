@@ -108,15 +108,25 @@ __device__ __forceinline__ float activate(float v, int act, int hsig) {
     return v;
 }
 
+// A buffer load's offset, or one past the end of every buffer below 2 GiB (zeros arrive).  Without a condition: `ok ? offset :
+// past` is compiled to a branch around the offset's arithmetic, and a load after a branch that may have skipped others waits
+// for all loads in flight.
+constexpr unsigned PAST_END = 0x7FFFFFF0u;
+__device__ __forceinline__ int offset_if(bool ok, unsigned offset) {
+    const unsigned m = 0u - (ok ? 1u : 0u);
+    return (int)((offset & m) | (PAST_END & ~m));
+}
+
 // Division of a non-negative int below 2^31 by a fixed divisor d: n / d = mulhi(n, mul) >> shr for d > 1
-// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1.  The host prepares (mul, shr).
+// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1 (mul = shr = 0, one = all bits; no branch).  The
+// host prepares (mul, shr, one).
 struct FastDiv {
-    unsigned mul, shr;
+    unsigned mul, shr, one;
     int d;
 };
 
 __host__ inline FastDiv make_fastdiv(int d) {
-    FastDiv f{0u, 0u, d};
+    FastDiv f{0u, 0u, d > 1 ? 0u : ~0u, d};
     if (d > 1) {
         int lg = 0;
         while ((1ll << lg) < d) ++lg;
@@ -128,7 +138,7 @@ __host__ inline FastDiv make_fastdiv(int d) {
 }
 
 __device__ __forceinline__ int fdiv(int n, const FastDiv &f) {
-    return f.d == 1 ? n : (int)(__umulhi((unsigned)n, f.mul) >> f.shr);
+    return (int)((__umulhi((unsigned)n, f.mul) >> f.shr) + ((unsigned)n & f.one));
 }
 
 }  // namespace sushi
