@@ -38,8 +38,8 @@ struct SmallGeom {
 // products and sums; which channel a lane holds does not matter as long as both operands agree).
 enum SmallType { ST_BF16, ST_IN32, ST_I8, ST_F32 };
 
-template <int U, int MAXT, SmallType TYPE>
-__global__ __launch_bounds__(MAXT) void conv_small_kernel(ConvArgs a, SmallGeom g, QuantArgs q) {
+template <int U, SmallType TYPE>
+__global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(ConvArgs a, SmallGeom g, QuantArgs q) {
     constexpr bool IN32 = TYPE == ST_IN32, I8 = TYPE == ST_I8, F32 = TYPE == ST_F32;
     extern __shared__ float cs_red[];  // [WK][4][64]
     const int WK = blockDim.x >> 6, lane = threadIdx.x & 63;
@@ -211,16 +211,15 @@ static hipError_t launch_small(const ConvArgs &a, const QuantArgs &q, hipStream_
     const int cells = (a.C + CPC - 1) / CPC;
     g.kcells = a.R * a.R * cells, g.nsteps = (g.kcells + 3) / 4;
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells), g.dr = make_fastdiv(a.R);
-    // Waves per tile, each with at least one round of U steps: many while every compute unit has few tiles, fewer once a tile
-    // would take the places of others (of these waves a compute unit holds 20 in int8, 32 in bf16).  4, 8, 16 waves, us:
-    // 7 x 7 x 576 3x3, 144 tiles, int8 16.2, 10.2, 8.2; 3 x 7 x 7 x 720 3x3, 450 tiles, bf16 21.3, 13.2, 14.2; 8 x 14 x 14 x 208
-    // 3x3, 1274 tiles, int8 8.9, 11.2, 11.2.
-    const long tiles = (long)g.tiles_m * g.tiles_f;
-    int wk = std::max(1, std::min((g.nsteps + U - 1) / U, tiles <= 256 ? 16 : tiles <= (TYPE == ST_I8 ? 512 : 768) ? 8 : 4));
+    // Waves per tile, each with at least one round of U steps: four.  More shorten the chain of rounds, but take the places of
+    // other tiles and have a longer sum through LDS.  4, 8, 16 waves, us: 7 x 7 x 720 3x3, 180 tiles of 203 steps, 9.2, 9.6, 10.4;
+    // 3 x 7 x 7 x 720, 450 tiles, 12.6, 12.6, 13.2; 16 x 7 x 7 x 264, 833 tiles of 75 steps, 9.6, 10.4, 12.1; over 330 layers of
+    // both precisions 3167, 3224, 3324.  Float32, four times the matrix instructions per step: eight up to 1024 tiles.
+    int wk = std::max(1, std::min((g.nsteps + U - 1) / U, TYPE == ST_F32 && (long)g.tiles_m * g.tiles_f <= 1024 ? 8 : 4));
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);
     while (wk > 1 && (long)per_xcd * 8 * 64 * wk >= 1l << 32) --wk;  // (a launch has fewer than 2^32 threads)
     const size_t lds = wk > 1 ? (size_t)wk * 1024 : 0;
-    hipLaunchKernelGGL((conv_small_kernel<U, 1024, TYPE>), dim3(per_xcd * 8), dim3(64 * wk), lds, s, a, g, q);
+    hipLaunchKernelGGL((conv_small_kernel<U, TYPE>), dim3(per_xcd * 8), dim3(64 * wk), lds, s, a, g, q);
     return hipGetLastError();
 }
 

@@ -267,9 +267,9 @@ def test_tiled_layers(arch, batch, int8):
     _check_dense(arch, batch, int8)
 
 
-# reductions of less than a step, of less than a round, of several rounds with a ragged last one and of 194 steps; one to 16
-# waves; pixel tiles of one to 16 pixels, both strides, residuals; a classifier whose class count is no multiple of 4; int8: cells
-# that straddle the channel count; the last five: more tiles than run at once with 16 or 8 waves each
+# reductions of less than a step, of less than a round, of several rounds with a ragged last one and of 194 steps; one to four
+# waves (float32: eight); pixel tiles of one to 16 pixels, both strides, residuals; a classifier whose class count is no multiple of 4; int8: cells
+# that straddle the channel count; the last five: several hundred to a thousand tiles
 FEW_PIXELS = [(_chain([8, 24, 200], 9, 10), 1), (_chain([40, 688, 24], 11, 37), 1),
               (_bottleneck([208, 328], [1, 2], 60, 0.35), 1), (_bottleneck([72, 136], [1, 2], 44, 0.2), 3),
               (_chain([24, 200, 72], 15), 6), (_chain([24, 488, 72], 15), 6), (_chain([8, 264, 40], 59), 1),
