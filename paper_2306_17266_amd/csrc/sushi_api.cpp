@@ -179,9 +179,13 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 size_t elem_size(const sushi_ctx *c) { return c->int8 ? 1 : c->bf16 ? 2 : 4; }
 
-// 0 for a finite value, NaN for an infinity or NaN.
-float finite_probe(float v) { return v * 0.f; }
-float finite_probe(uint16_t bf16) { return (bf16 & 0x7F80u) == 0x7F80u ? NAN : 0.f; }
+// 1 for an infinity or NaN, else 0 (integer compare and or: the loop over a filter vectorises).
+int not_finite(float v) {
+    int32_t u;
+    std::memcpy(&u, &v, 4);
+    return (u & 0x7FFFFFFF) > 0x7F7FFFFF;
+}
+int not_finite(uint16_t bf16) { return (bf16 & 0x7FFF) > 0x7F7F; }
 
 // Lays the SuperNet out for the device.  Dense/FC layer: [tap][channel group][filter, padded to 16][8];
 // depthwise: [tap in ring order][channel, padded to 16].  Scale/shift/bias: float32 runs, each
@@ -220,17 +224,18 @@ void pack_weights(SuperNet &sn, const float *blob, std::vector<T> &w, std::vecto
                 for (int k = 0; k < L.Kmax; ++k) dst[(size_t)t * L.Kpad + k] = cvt(src[((size_t)k * R + r) * R + s]);
             }
         } else {
-            for (int k = 0; k < L.Kmax; ++k)
+            const bool check = sizeof(T) == 4 || L.Cmax < 8;  // (the layers for which launch_conv asks)
+            const size_t n = (size_t)L.Cmax * R * R;
+            int bad = 0;
+            for (int k = 0; k < L.Kmax; ++k) {
+                const float *from = src + k * n;
                 for (int c = 0; c < L.Cmax; ++c)
                     for (int t = 0; t < R * R; ++t)
-                        dst[(((size_t)t * L.CG + c / 8) * L.Kpad + k) * 8 + (c & 7)] =
-                            cvt(src[((size_t)k * L.Cmax + c) * R * R + t]);
-        }
-        if (L.type != L_DW && (sizeof(T) == 4 || L.Cmax < 8)) {  // (what launch_conv asks for)
-            const size_t n = (size_t)L.Kmax * L.Cmax * R * R;
-            float sum = 0.f;  // NaN if one is not finite
-            for (size_t i = 0; i < n; ++i) sum += finite_probe(cvt(src[i]));
-            L.finite_w = sum == sum;
+                        dst[(((size_t)t * L.CG + c / 8) * L.Kpad + k) * 8 + (c & 7)] = cvt(from[(size_t)c * R * R + t]);
+                // (a pass of its own over the filter, still in the cache: inside the loop above it costs 12 ms of 100)
+                for (size_t i = 0; check && i < n; ++i) bad |= not_finite(cvt(from[i]));
+            }
+            L.finite_w = !bad;
         }
         if (L.has_scale) std::memcpy(&params[L.pk_scale], blob + L.blob_scale, sizeof(float) * L.Kmax);
         std::memcpy(&params[L.pk_shift], blob + L.blob_shift, sizeof(float) * L.Kmax);
