@@ -36,11 +36,13 @@ struct SmallGeom {
 // 16 bits of the input's mantissa instead of 8.
 // ST_F32: the float32 mode; a cell is half a stored group of eight channels, four v_mfma_f32_16x16x4_f32 per step (float32
 // products and sums; which channel a lane holds does not matter as long as both operands agree).
-enum SmallType { ST_BF16, ST_IN32, ST_I8, ST_F32 };
+// ST_GATED: bf16, 1x1; every operand cell is multiplied by its image's gates (float32) and rounded to bf16 again, which is what a
+// pass over the map would have stored.
+enum SmallType { ST_BF16, ST_IN32, ST_I8, ST_F32, ST_GATED };
 
 template <int U, SmallType TYPE>
 __global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(ConvArgs a, SmallGeom g, QuantArgs q) {
-    constexpr bool IN32 = TYPE == ST_IN32, I8 = TYPE == ST_I8, F32 = TYPE == ST_F32;
+    constexpr bool IN32 = TYPE == ST_IN32, I8 = TYPE == ST_I8, F32 = TYPE == ST_F32, GATED = TYPE == ST_GATED;
     extern __shared__ float cs_red[];  // [WK][4][64]
     const int WK = blockDim.x >> 6, lane = threadIdx.x & 63;
     const int wk = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -61,7 +63,10 @@ __global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(
     const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
     const unsigned boff = (unsigned)(((n * a.H + h0) * a.W + w0) * a.C * ES);
     const unsigned woff = (unsigned)(f0 + l16) * (F32 ? 32 : 16);  // (filters are padded to 16)
-    cs_u32x4 rb[U], rb2[IN32 ? U : 1], ra[U];
+    const __amdgpu_buffer_rsrc_t rg =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(q.gate), 0, GATED ? a.B * a.C * 4 : 0, 0x00020000);
+    const unsigned goff = (unsigned)(n * a.C) * 4u;
+    cs_u32x4 rb[U], rb2[IN32 ? U : 1], ra[U], rg0[GATED ? U : 1], rg1[GATED ? U : 1];
     unsigned in[U];  // int8: bit 0: the cell holds image; bit 8: a cell of the reduction; bit 9: its upper half is beyond C
     auto load_step = [&](int step, int u) {
         const int k = step * 4 + kg;
@@ -75,6 +80,10 @@ __global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(
         ra[u] = __builtin_amdgcn_raw_buffer_load_b128(rw, offset_if(kv, woff + wcell), 0, 0);
         rb[u] = __builtin_amdgcn_raw_buffer_load_b128(rx, offset_if(ok, boff + off), 0, 0);
         if (IN32) rb2[IN32 ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rx, offset_if(ok, boff + off + 16), 0, 0);
+        if (GATED) {
+            rg0[GATED ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rg, offset_if(ok, goff + (unsigned)cg * 32u), 0, 0);
+            rg1[GATED ? u : 0] = __builtin_amdgcn_raw_buffer_load_b128(rg, offset_if(ok, goff + (unsigned)cg * 32u + 16u), 0, 0);
+        }
         in[u] = (ok ? 1u : 0u) | (kv ? 256u : 0u) | (cg * CPC + 8 >= a.C ? 512u : 0u);
     };
 #pragma unroll
@@ -132,7 +141,8 @@ __global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, hi.v, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, lo.v, acc, 0, 0, 0);
         } else {
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ra[u]), __builtin_bit_cast(bf16x8_t, rb[u]), acc, 0, 0, 0);
+            const cs_u32x4 b = GATED ? gate_cell(rb[u], rg0[GATED ? u : 0], rg1[GATED ? u : 0]) : rb[u];
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, ra[u]), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
         }
     };
     // rounds of U steps; the steps of the last round have no successor
@@ -229,9 +239,16 @@ static bool small_fits(const ConvArgs &a, long es) {
            (long)a.R * a.R * a.CG * a.Kpad * (es == 4 && !a.in_f32 ? 32 : 16) < lim && ((a.K + 15) / 16) * (((long)a.B * a.P * a.Q + 15) / 16) < (1l << 26) - 8;
 }
 
-hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s) {
+bool conv_small_covers(const ConvArgs &a) { return !a.in_f32 && small_fits(a, 2); }
+
+hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s, const float *gate) {
     if (!a.in_f32) {
         if (!small_fits(a, 2)) return hipErrorNotSupported;
+        if (gate) {
+            QuantArgs q{};
+            q.gate = gate;
+            return launch_small<ST_GATED>(a, q, s);
+        }
         return launch_small<ST_BF16>(a, QuantArgs{}, s);
     }
     // float32 vectors: rows in pieces below 2 GiB

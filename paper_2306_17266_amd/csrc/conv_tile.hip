@@ -34,10 +34,13 @@ struct TileGeom {
     int kcells;  // cells of the reduction: taps * cells per tap
     int per;     // steps (of eight cells) per wave group
     int part;    // cell offset of the scale / shift (int8: multiplier, shift, bias) copies in LDS
+    int gates;   // cell offset of the gates of the tile's images in LDS
     FastDiv dq, dp, dcell;  // division by Q, P, cells per tap
 };
 
-template <int KS, int R, bool I8>
+// GATED (bf16, 1x1): every operand cell is multiplied by its image's gates (float32) on its way into LDS and rounded to bf16
+// again, which is what a pass over the map would have stored.
+template <int KS, int R, bool I8, bool GATED>
 __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, TileGeom g, QuantArgs q) {
     constexpr int ES = I8 ? 1 : 2, CPC = 16 / ES;  // bytes per element, channels per cell
     constexpr int BN = 64, BM = 64, SA = BN + 1, SB = BM + 1, NT = 256 * KS;
@@ -63,7 +66,8 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     // what this thread stages: cell bk of pixels (gt >> 3) + 32 i (byte offset of the pixel's window, one bit per tap
     // inside the image), weight cells wave and wave + 4 of filter f0 + lane
     const int bk = gt & 7;
-    unsigned boff[NB], bmask[NB];
+    unsigned boff[NB], bmask[NB], goff[GATED ? NB : 1];
+    const int n0 = GATED ? fdiv(fdiv(m0, g.dq), g.dp) : 0;  // first image of the tile
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         const int m = m0 + (gt >> 3) + 32 * i;
@@ -72,6 +76,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
         const int n = fdiv(t, g.dp), pp = t - n * a.P;
         const int h0 = pp * a.stride - a.pad, w0 = qq * a.stride - a.pad;
         boff[i] = (unsigned)(((n * a.H + h0) * a.W + w0) * a.C * ES);
+        if (GATED) goff[GATED ? i : 0] = (unsigned)g.gates + (unsigned)((live ? n - n0 : 0) * (a.C >> 2));
         bmask[i] = 0;
         if (R == 1) {
             bmask[i] = live ? 1u : 0u;
@@ -115,14 +120,18 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     // upper half of a cell that straddles the SubNet's channel count zeros
     const unsigned zfill = (unsigned)(q.zx & 0xFF) * 0x01010101u;
     uint4 *const base = ct_lds + grp * 2 * BUF;
-    auto store_step = [&](int buf, const ct_u32x4 *qa, const ct_u32x4 *qb, unsigned in) {
-        uint4 *dst = base + buf * BUF;
+    auto store_step = [&](int s, const ct_u32x4 *qa, const ct_u32x4 *qb, unsigned in) {
+        uint4 *dst = base + (s & 1) * BUF;
 #pragma unroll
         for (int i = 0; i < 2; ++i) dst[(wave + 4 * i) * SA + lane] = __builtin_bit_cast(uint4, qa[i]);
         dst += 8 * SA + bk * SB + (gt >> 3);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             ct_u32x4 v = qb[i];
+            if (GATED) {  // (cells past the last: zeros, times the gates of the last)
+                const uint4 *gc = ct_lds + goff[GATED ? i : 0] + 2 * min(k0 + s * 8 + bk, g.kcells - 1);
+                v = gate_cell(v, __builtin_bit_cast(ct_u32x4, gc[0]), __builtin_bit_cast(ct_u32x4, gc[1]));
+            }
             if (I8) {
                 if ((in & 256u) && !(in >> i & 1u)) v = ct_u32x4{zfill, zfill, zfill, zfill};
                 if (in & 512u) v[2] = 0u, v[3] = 0u;
@@ -151,6 +160,11 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     } else if (!a.scale) {
         cst[0] = make_uint4(0x3F800000u, 0x3F800000u, 0x3F800000u, 0x3F800000u);
     }
+    if (GATED) {
+        const int last = min(m0 + BM, g.M) - 1, cells = (fdiv(fdiv(last, g.dq), g.dp) - n0 + 1) * (a.C >> 2);
+        const uint4 *src = reinterpret_cast<const uint4 *>(q.gate + (long)n0 * a.C);
+        for (int k = tid; k < cells; k += NT) ct_lds[g.gates + k] = src[k];
+    }
     if (tid < BN / 4)
 #pragma unroll
         for (int i = 0; i < (I8 ? 3 : 2); ++i) ct_lds[g.part + i * (BN / 4) + tid] = cst[i];
@@ -159,6 +173,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
 #pragma unroll
     for (int k = 0; k < 16; ++k) acc[k] = 0;
 
+    if (GATED) __syncthreads();  // (the gates are there)
     store_step(0, ra[0], rb[0], rin[0]);
     __syncthreads();
     // one step: s is in LDS buffer s & 1, set d took it there and is free; the cells of step s + 1 are in set (d + 1) % D
@@ -173,7 +188,7 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
         }
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (decltype(load_tag)::value) load_step(s + D, ra[d], rb[d], rin[d]);
-        store_step((s + 1) & 1, ra[dn], rb[dn], rin[dn]);
+        store_step(s + 1, ra[dn], rb[dn], rin[dn]);
 #pragma unroll
         for (int h = 0; h < 4; ++h)
             if constexpr (I8)
@@ -267,7 +282,10 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     }
 }
 
-template <int KS, int R, bool I8>
+// Cells of the gates that a tile of 64 pixels may need: as many images as it can touch.
+static long tile_gate_cells(const ConvArgs &a) { return std::min((long)a.B, 62l / ((long)a.P * a.Q) + 2) * (a.C >> 2); }
+
+template <int KS, int R, bool I8, bool GATED = false>
 static hipError_t launch_tile(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
     constexpr int BM = 64, BUF = 8 * (65 + BM + 1), CPC = I8 ? 16 : 8;
     TileGeom g;
@@ -278,9 +296,10 @@ static hipError_t launch_tile(const ConvArgs &a, const QuantArgs &q, hipStream_t
     g.per = ((g.kcells + 7) / 8 + KS - 1) / KS;
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dcell = make_fastdiv(cells);
     g.part = std::max(KS * 2 * BUF, KS * BM * 17);
-    const size_t lds = ((size_t)g.part + (I8 ? 48 : 32)) * 16;
+    g.gates = g.part + (I8 ? 48 : 32);
+    const size_t lds = ((size_t)g.gates + (GATED ? tile_gate_cells(a) : 0)) * 16;
     static_assert((size_t)KS * 2 * BUF * 16 + 768 <= 160 * 1024 && (size_t)KS * BM * 17 * 16 + 768 <= 160 * 1024, "LDS of a compute unit");
-    auto kern = conv_tile_kernel<KS, R, I8>;
+    auto kern = conv_tile_kernel<KS, R, I8, GATED>;
     static LdsLimit limit;
     const hipError_t e = limit.raise(kern);
     if (e != hipSuccess) return e;
@@ -314,6 +333,10 @@ template <bool I8>
 static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStream_t s) {
     int steps;
     const int ks = tile_groups(a, I8, &steps);
+    if (!I8 && q.gate)
+        return ks == 4   ? launch_tile<4, 1, false, true>(a, q, s)
+               : ks == 2 ? launch_tile<2, 1, false, true>(a, q, s)
+                         : launch_tile<1, 1, false, true>(a, q, s);
     if (a.R == 1)
         return ks == 4 ? launch_tile<4, 1, I8>(a, q, s) : ks == 2 ? launch_tile<2, 1, I8>(a, q, s) : launch_tile<1, 1, I8>(a, q, s);
     return ks == 4 ? launch_tile<4, 3, I8>(a, q, s) : ks == 2 ? launch_tile<2, 3, I8>(a, q, s) : launch_tile<1, 3, I8>(a, q, s);
@@ -362,9 +385,13 @@ static bool tile_is_faster(const ConvArgs &a, bool patch) {
     return (a.K + 63) / 64 * 64 <= (a.K + pf - 1) / pf * pf;
 }
 
-hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch) {
+bool conv_tile_gated_covers(const ConvArgs &a) { return a.R == 1 && tile_covers<false>(a) && tile_gate_cells(a) * 16 <= 24 * 1024; }
+
+hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch, const float *gate) {
     if (!tile_covers<false>(a) || !tile_is_faster<false>(a, patch)) return hipErrorNotSupported;
-    return launch_tile_ks<false>(a, QuantArgs{}, s);
+    QuantArgs q{};
+    q.gate = gate;
+    return launch_tile_ks<false>(a, q, s);
 }
 
 hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch) {

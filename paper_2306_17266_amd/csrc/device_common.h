@@ -108,6 +108,18 @@ __device__ __forceinline__ float activate(float v, int act, int hsig) {
     return v;
 }
 
+// A cell of eight bf16 values times eight float32 gates, rounded to bf16.
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
+__device__ __forceinline__ u32x4_t gate_cell(u32x4_t x, u32x4_t g0, u32x4_t g1) {
+    u32x4_t o;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const u32x4_t g = i < 2 ? g0 : g1;
+        o[i] = pack_bf16x2(bf2f(x[i] & 0xFFFFu) * __uint_as_float(g[2 * (i & 1)]), bf2f(x[i] >> 16) * __uint_as_float(g[2 * (i & 1) + 1]));
+    }
+    return o;
+}
+
 // A buffer load's offset, or one past the end of every buffer below 2 GiB (zeros arrive).  Without a condition: `ok ? offset :
 // past` is compiled to a branch around the offset's arithmetic, and a load after a branch that may have skipped others waits
 // for all loads in flight.

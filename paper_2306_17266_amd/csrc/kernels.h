@@ -60,7 +60,17 @@ struct ConvArgs {
                          // head vectors); the kernels split it into two bf16 terms (value = hi + lo) on the fly
 };
 
-// What an int8 layer needs beyond ConvArgs / PoolArgs (int8.hip).  Weights are then
+// The two fully connected layers of a squeeze-excite block (squeeze_excite.hip).
+struct SeGateArgs {
+    const float *pooled;  // [B][parts][C]: their sum over the parts, times inv, is the block's input
+    const void *w1, *w2;  // packed bf16 weights [cell of 8 inputs][filter (padded)][8]
+    const float *b1, *b2;
+    float *gate;  // [B][C]
+    int B, C, red, Kpad1, Kpad2, parts;
+    float inv;
+};
+
+// What an int8 layer needs beyond ConvArgs / PoolArgs (int8.hip), and the gates of a bf16 layer.  An int8 layer's weights are
 // [tap][channel group of 16][filter (padded to 16)][16] and ConvArgs::CG counts the stored groups of 16.
 struct QuantArgs {
     const int32_t *qmult;   // per filter: requantisation multiplier (classifier: bit pattern of a float32 factor)
@@ -70,6 +80,7 @@ struct QuantArgs {
     int zx, zy;             // zero points of the input and the output tensor (pooling: zx of the pooled map)
     int m_res, sh_res, z_res;  // residual: multiplier, shift, zero point
     int pool_hw;            // classifier: pixels the pooling before it summed over
+    const float *gate;      // (bf16, 1x1: [B][C] multipliers of the input, value * gate rounded to bf16; null: none)
 };
 
 struct PoolArgs {
@@ -98,7 +109,8 @@ enum KernelClass {
     KC_CONV_TILE = 13,  // conv_tile_kernel (64-filter tiles, the reduction split over wave groups)
     KC_DW_MFMA = 14,    // dw_mfma_kernel (depthwise on the matrix cores)
     KC_DW = 15,         // dwconv_kernel (depthwise: float32, and tensors of 2 GiB and more)
-    KC_COUNT = 16
+    KC_SE_GATE = 16,    // se_gate_kernel (both fully connected layers of a squeeze-excite block)
+    KC_COUNT = 17
 };
 const char *kernel_class_name(int kc);
 
@@ -114,6 +126,7 @@ inline bool patch_from(long min_pixels, long pixels, bool long_reduction) {
 // finite_w: the layer's weights are all finite; if not, float32 layers and the input layer run in the kernel that skips
 // taps outside the image (in the others zero meets the tap's weight, and zero times infinity is NaN).
 hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w);  // dense conv and FC
+hipError_t launch_gated_conv(const ConvArgs &a, const float *gate, hipStream_t s, int *kc);  // (gated_conv_covers)
 
 // Dense 1x1 (stride 1) and 3x3 (stride 1 or 2) convolution, bf16, C and K multiples of 8, tensors below 2 GiB: the
 // patch kernel (conv_patch.hip).  Returns hipErrorNotSupported (nothing launched) for any other case.
@@ -123,15 +136,23 @@ int conv_patch_tile_filters(int K);  // filters of one of its tiles for a layer 
 // Dense 1x1 and 3x3 convolution (stride 1 or 2), C and K multiples of 8, tensors below 2 GiB: the tile kernel
 // (conv_tile.hip).  patch: the patch kernel would take the layer otherwise.  Returns hipErrorNotSupported (nothing
 // launched) for any other case and where another kernel is the faster one.
-hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch);
+hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch, const float *gate = nullptr);
+bool conv_tile_gated_covers(const ConvArgs &a);
 hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
 
 // Dense convolution of few pixels and fully connected layers, C a multiple of 8 (conv_small.hip).  bf16 and float32:
 // return hipErrorNotSupported (nothing launched) for tensors of 2 GiB and more.
-hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s);
+hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s, const float *gate = nullptr);
+bool conv_small_covers(const ConvArgs &a);  // (bf16)
 hipError_t launch_conv_small_f32(const ConvArgs &a, hipStream_t s);  // the float32 mode
 hipError_t launch_conv_small_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s);
 bool conv_small_is_faster(const ConvArgs &a, bool i8);  // than the tile kernel (conv_tile.hip)
+
+// Squeeze-excite in two launches behind the pooling: the gates (squeeze_excite.hip), then the 1x1 layer behind the block with
+// its gates (conv_small.hip, conv_tile.hip).  The covers functions say whether a layer can go that way.
+bool se_gate_covers(const SeGateArgs &a);
+hipError_t launch_se_gate(const SeGateArgs &a, hipStream_t s);
+bool gated_conv_covers(const ConvArgs &a);
 
 // 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
 // other case.

@@ -491,8 +491,20 @@ const char *kernel_class_name(int kc) {
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
                                           "conv_patch_kernel",  "conv_i8_direct_kernel", "int8_pool_fc_kernels",
                                           "stem_mfma_kernel",   "conv_tile_kernel",    "dw_mfma_kernel",
-                                          "dwconv_kernel"};
+                                          "dwconv_kernel",      "se_gate_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
+}
+
+bool gated_conv_covers(const ConvArgs &a) {
+    return a.R == 1 && a.stride == 1 && !a.in_f32 && !a.out_f32 && conv_small_covers(a) && conv_tile_gated_covers(a) &&
+           (long)a.B * a.C * 4 < (1l << 31) - 256;
+}
+
+hipError_t launch_gated_conv(const ConvArgs &a, const float *gate, hipStream_t s, int *kc) {
+    if (!gated_conv_covers(a)) return hipErrorInvalidValue;
+    const bool small = conv_small_is_faster(a, false);
+    *kc = small ? KC_CONV_SMALL : KC_CONV_TILE;
+    return small ? launch_conv_small(a, s, gate) : launch_conv_tile(a, s, false, gate);
 }
 
 hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, long patch_min_pixels, bool finite_w) {

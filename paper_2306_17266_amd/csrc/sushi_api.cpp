@@ -23,10 +23,14 @@ using namespace sushi;
 
 namespace {
 
+enum StepKind { STEP_SE_GATE = 16 };  // launches that are not one op of the plan (Launch::kind, beyond OpKind)
+
 struct Launch {
     int kind;
+    int op = 0;  // the (first) op of the plan that it runs
     ConvArgs conv{};
     PoolArgs pool{};
+    SeGateArgs se{};
     QuantArgs quant{};  // int8 mode
     int in_patch = 0, out_patch = 0;  // 1 = pointer is the caller's input / logits buffer
     bool finite_w = true;             // SuperLayer::finite_w
@@ -34,7 +38,8 @@ struct Launch {
 
 struct CachedPlan {
     Plan plan;
-    std::vector<Launch> launches;
+    std::vector<Launch> launches;  // one per op
+    std::vector<Launch> steps;     // the same with ops fused (bf16 mode); exec modes 0 and 1 run these
     uint64_t weight_bytes = 0;
     double alg_bytes = 0.0, alg_flops = 0.0;  // algorithmic traffic and arithmetic of the whole query
     double vec_norm2 = 0.0;           // sum K^2 + C^2 over layers
@@ -315,12 +320,46 @@ void *buf_ptr(sushi_ctx *c, const BufBase &bb, int id, bool small) {
     return small ? bb.block + N_BIG_BUFS * bb.big_bytes + id * bb.small_bytes : bb.block + id * bb.big_bytes;
 }
 
+// cp.steps from cp.launches.  A squeeze-excite block (pooling, two fully connected layers, gating, the 1x1 layer behind it):
+// both fully connected layers in one launch, the gating in the 1x1 layer's operand reads.  Nobody else reads the hidden
+// vector or the gated map.
+void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
+    cp.steps.clear();
+    if (!c->bf16 || c->int8) return;
+    const std::vector<Launch> &in = cp.launches;
+    const std::vector<Op> &ops = cp.plan.ops;
+    for (size_t i = 0; i < in.size(); ++i) {
+        if (i + 3 < in.size() && ops[i].kind == OP_FC && ops[i].act == SUSHI_ACT_RELU && ops[i + 1].kind == OP_FC && ops[i + 1].hsigmoid &&
+            ops[i + 2].kind == OP_GATE && ops[i + 3].kind == OP_CONV && ops[i + 3].in_buf == ops[i + 2].out_buf &&
+            ops[i + 1].in_buf == ops[i].out_buf && ops[i + 2].gate_buf == ops[i + 1].out_buf) {
+            const ConvArgs &f1 = in[i].conv, &f2 = in[i + 1].conv;
+            Launch S, P = in[i + 3];
+            S.kind = STEP_SE_GATE;
+            S.op = (int)i;
+            S.se = SeGateArgs{static_cast<const float *>(f1.x), f1.w, f2.w, f1.shift, f2.shift, static_cast<float *>(f2.y),
+                          f1.B, f1.C, f1.K, f1.Kpad, f2.Kpad, 1, 1.0f};
+            P.conv.x = in[i + 2].pool.x;
+            P.quant.gate = S.se.gate;
+            P.op = (int)i + 2;
+            if (se_gate_covers(S.se) && gated_conv_covers(P.conv)) {
+                cp.steps.push_back(S);
+                cp.steps.push_back(P);
+                i += 3;
+                continue;
+            }
+        }
+        cp.steps.push_back(in[i]);
+    }
+    if (cp.steps.size() == in.size()) cp.steps.clear();
+}
+
 // Turns a plan into launch records with device pointers bound.
 void bind_plan(sushi_ctx *c, CachedPlan &cp, const BufBase &bb = BufBase()) {
     const size_t es = elem_size(c);
     for (const Op &op : cp.plan.ops) {
         Launch L;
         L.kind = op.kind;
+        L.op = (int)cp.launches.size();
         if (op.kind == OP_CONV || op.kind == OP_DW || op.kind == OP_FC) {
             const SuperLayer &S = c->sn.layers[op.layer];
             ConvArgs &a = L.conv;
@@ -367,6 +406,7 @@ void bind_plan(sushi_ctx *c, CachedPlan &cp, const BufBase &bb = BufBase()) {
         }
         cp.launches.push_back(L);
     }
+    fuse_steps(c, cp);
     cp.weight_bytes = 0;
     cp.vec_norm2 = 0.0;
     for (const sushi_layer_dims &d : cp.plan.dims) {
@@ -403,8 +443,13 @@ void launch_cost(const sushi_ctx *c, const Launch &L, double *bytes, double *flo
         const double in = (double)a.B * a.H * a.W * a.C, out = (double)a.B * a.P * a.Q * a.K;
         const double taps = (double)a.R * a.R;
         const double wts = L.kind == OP_DW ? a.K * taps : (double)a.K * a.C * taps;
-        *bytes = in * (a.in_f32 ? 4.0 : es) + (wts + (a.res ? out : 0.0)) * es + out * (a.out_f32 ? 4.0 : es) + 8.0 * a.K;
+        *bytes = in * (a.in_f32 ? 4.0 : es) + (L.quant.gate ? 4.0 * a.B * a.C : 0.0) + (wts + (a.res ? out : 0.0)) * es + out * (a.out_f32 ? 4.0 : es) + 8.0 * a.K;
         *flops = 2.0 * out * (L.kind == OP_DW ? taps : a.C * taps);
+    } else if (L.kind == STEP_SE_GATE) {
+        const SeGateArgs &a = L.se;
+        const double wts = 2.0 * a.C * a.red;
+        *bytes = wts * es + 4.0 * (a.C + a.red) + 4.0 * a.B * a.C * (a.parts + 1.0);
+        *flops = 2.0 * wts * a.B;
     } else {
         const PoolArgs &a = L.pool;
         const double in = (double)a.B * a.H * a.W * a.C;
@@ -446,10 +491,10 @@ hipError_t drain_timing(sushi_ctx *c) {
 hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, void *logits_dev, hipStream_t st) {
     const bool timed = c->timing && st == c->stream;
     hipError_t e = hipSuccess;
-    int op_index = -1;
-    for (Launch &L : cp.launches) {
+    // (a patch threshold set by the caller is about single layers)
+    for (const Launch &L : c->patch_min_pixels == PATCH_AUTO && !cp.steps.empty() ? cp.steps : cp.launches) {
         sushi_ctx::Pending pend{};
-        pend.op_index = ++op_index;
+        pend.op_index = L.op;
         if (timed) {
             if ((e = get_event(c, &pend.a)) != hipSuccess || (e = get_event(c, &pend.b)) != hipSuccess) return e;
             if ((e = hipEventRecord(pend.a, st)) != hipSuccess) return e;
@@ -486,7 +531,7 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
                 ConvArgs a = L.conv;
                 if (L.in_patch) a.x = input_dev;
                 if (L.out_patch) a.y = logits_dev;
-                e = launch_conv(a, c->bf16, st, &kc, c->patch_min_pixels, L.finite_w);
+                e = L.quant.gate ? launch_gated_conv(a, L.quant.gate, st, &kc) : launch_conv(a, c->bf16, st, &kc, c->patch_min_pixels, L.finite_w);
                 break;
             }
             case OP_DW:
@@ -503,6 +548,10 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
             case OP_GATE:
                 kc = KC_GATE;
                 e = launch_gate(L.pool, c->bf16, st);
+                break;
+            case STEP_SE_GATE:
+                kc = KC_SE_GATE;
+                e = launch_se_gate(L.se, st);
                 break;
             default:
                 e = hipErrorInvalidValue;
