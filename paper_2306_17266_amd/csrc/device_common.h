@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "kernels.h"
+
 namespace sushi {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
@@ -127,26 +129,6 @@ constexpr unsigned PAST_END = 0x7FFFFFF0u;
 __device__ __forceinline__ int offset_if(bool ok, unsigned offset) {
     const unsigned m = 0u - (ok ? 1u : 0u);
     return (int)((offset & m) | (PAST_END & ~m));
-}
-
-// Division of a non-negative int below 2^31 by a fixed divisor d: n / d = mulhi(n, mul) >> shr for d > 1
-// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1 (mul = shr = 0, one = all bits; no branch).  The
-// host prepares (mul, shr, one).
-struct FastDiv {
-    unsigned mul, shr, one;
-    int d;
-};
-
-__host__ inline FastDiv make_fastdiv(int d) {
-    FastDiv f{0u, 0u, d > 1 ? 0u : ~0u, d};
-    if (d > 1) {
-        int lg = 0;
-        while ((1ll << lg) < d) ++lg;
-        const int p = 31 + lg;
-        f.mul = (unsigned)(((1ull << p) + (unsigned long long)d - 1) / (unsigned long long)d);
-        f.shr = (unsigned)(p - 32);
-    }
-    return f;
 }
 
 __device__ __forceinline__ int fdiv(int n, const FastDiv &f) {

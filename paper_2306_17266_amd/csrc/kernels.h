@@ -41,6 +41,26 @@ public:
     }
 };
 
+// Division of a non-negative int below 2^31 by a fixed divisor d: n / d = mulhi(n, mul) >> shr for d > 1
+// (mul = ceil(2^(31 + ceil(log2 d)) / d) fits 32 bits), n itself for d = 1 (mul = shr = 0, one = all bits; no branch).  The
+// host prepares (mul, shr, one).
+struct FastDiv {
+    unsigned mul, shr, one;
+    int d;
+};
+
+__host__ inline FastDiv make_fastdiv(int d) {
+    FastDiv f{0u, 0u, d > 1 ? 0u : ~0u, d};
+    if (d > 1) {
+        int lg = 0;
+        while ((1ll << lg) < d) ++lg;
+        const int p = 31 + lg;
+        f.mul = (unsigned)(((1ull << p) + (unsigned long long)d - 1) / (unsigned long long)d);
+        f.shr = (unsigned)(p - 32);
+    }
+    return f;
+}
+
 struct ConvArgs {
     const void *x;       // input activations
     void *y;             // output activations
@@ -58,6 +78,33 @@ struct ConvArgs {
     int out_f32;         // store float32 regardless of the activation type
     int in_f32;          // bf16 mode: the input is a float32 vector per image (pooled features, squeeze-excite and
                          // head vectors); the kernels split it into two bf16 terms (value = hi + lo) on the fly
+};
+
+// 1x1 expansion and the depthwise layer behind it (expand_dw.hip).
+struct ExpandDwArgs {
+    const void *x;          // [B][H][W][C]
+    void *y;                // [B][P][Q][K]
+    const void *w1, *w2;    // packed dense and depthwise weights
+    const float *scale1, *shift1, *scale2, *shift2;
+    float *pool;            // [B][ExpandDwGeom::parts][K] partial sums of the output over an image, or null
+    int B, H, W, C, K, P, Q;
+    int R, stride;          // of the depthwise layer
+    int Kpad1, Kpad2, act;  // (the same activation behind both)
+};
+
+// How a layer pair is cut into tiles; depends on the shapes alone.
+struct ExpandDwGeom {
+    int tx, ty;           // tiles of an image along x and y
+    int bx, by, im;       // blocks of a tile along x and y, images of a tile (several only where an image is one tile)
+    int ns, ng;           // matrix columns set aside for an image; groups of 16 columns
+    int rp, rh, pp;       // plane: bytes of a row, rows of an image, bytes in all
+    int r0, rows, qw;     // first row of an image's region that may lie in the image, how many; quads of a row
+    int nq;               // quads of a tile
+    int total, workers;   // tiles over all images; workgroups that share them (times channel blocks)
+    int groups;           // channel blocks
+    int parts;            // of ExpandDwArgs::pool
+    int out, tab;         // LDS offsets of the outputs (first: the taps) and of the tables
+    FastDiv dqw, drows, dper, dtx, dbx, dtw, dth;  // division by qw, rows, tx * ty, tx, bx, outputs of a tile's row, of its column
 };
 
 // The two fully connected layers of a squeeze-excite block (squeeze_excite.hip).
@@ -110,7 +157,8 @@ enum KernelClass {
     KC_DW_MFMA = 14,    // dw_mfma_kernel (depthwise on the matrix cores)
     KC_DW = 15,         // dwconv_kernel (depthwise: float32, and tensors of 2 GiB and more)
     KC_SE_GATE = 16,    // se_gate_kernel (both fully connected layers of a squeeze-excite block)
-    KC_COUNT = 17
+    KC_EXPAND_DW = 17,  // expand_dw_kernel (1x1 expansion and depthwise layer)
+    KC_COUNT = 18
 };
 const char *kernel_class_name(int kc);
 
@@ -153,6 +201,11 @@ bool conv_small_is_faster(const ConvArgs &a, bool i8);  // than the tile kernel 
 bool se_gate_covers(const SeGateArgs &a);
 hipError_t launch_se_gate(const SeGateArgs &a, hipStream_t s);
 bool gated_conv_covers(const ConvArgs &a);
+
+// An inverted-residual block's expansion and depthwise layer in one launch (expand_dw.hip).
+bool expand_dw_covers(const ExpandDwArgs &a);
+ExpandDwGeom expand_dw_geom(const ExpandDwArgs &a);
+hipError_t launch_expand_dw(const ExpandDwArgs &a, const ExpandDwGeom &g, hipStream_t s);
 
 // 3x3 convolution of a 3-channel bf16 image (stem.hip).  Returns hipErrorNotSupported (nothing launched) for any
 // other case.

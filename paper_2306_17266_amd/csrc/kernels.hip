@@ -491,7 +491,7 @@ const char *kernel_class_name(int kc) {
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
                                           "conv_patch_kernel",  "conv_i8_direct_kernel", "int8_pool_fc_kernels",
                                           "stem_mfma_kernel",   "conv_tile_kernel",    "dw_mfma_kernel",
-                                          "dwconv_kernel",      "se_gate_kernel"};
+                                          "dwconv_kernel",      "se_gate_kernel",     "expand_dw_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 

@@ -105,16 +105,30 @@ __global__ __launch_bounds__(SE_THREADS) void se_gate_kernel(SeGateArgs a, int c
     const int per = nimg == 1 ? SE_THREADS : SE_THREADS / SE_IMAGES, j = tid / per, t0 = tid - j * per;
     const float bias1 = tid < a.red ? a.b1[tid] : 0.f, bias2 = tid < nc ? a.b2[c0 + tid] : 0.f;
     const float *src = a.pooled + (long)min(n0 + j, a.B - 1) * a.parts * a.C;
-    for (int ch = t0; ch < a.C; ch += 8 * per) {
-        float x[8];
+    if (a.parts <= 2) {  // eight channels' loads in flight, or sixteen parts of one
+        for (int ch = t0; ch < a.C; ch += 8 * per) {
+            float x[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = src[min(ch + u * per, a.C - 1)];
-        for (int t = 1; t < a.parts; ++t)
+            for (int u = 0; u < 8; ++u) x[u] = src[min(ch + u * per, a.C - 1)];
+            if (a.parts == 2)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] += src[(long)t * a.C + min(ch + u * per, a.C - 1)];
+                for (int u = 0; u < 8; ++u) x[u] += src[a.C + min(ch + u * per, a.C - 1)];
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (ch + u * per < a.C && j < ni) se_split(x[u] * a.inv, v1, p1, j, ch + u * per);
+            for (int u = 0; u < 8; ++u)
+                if (ch + u * per < a.C && j < ni) se_split(x[u] * a.inv, v1, p1, j, ch + u * per);
+        }
+    } else {
+        for (int ch = t0; ch < a.C; ch += per) {
+            float s = 0.f;
+            for (int t = 0; t < a.parts; t += 16) {
+                float x[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) x[u] = src[(long)min(t + u, a.parts - 1) * a.C + ch];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) s += t + u < a.parts ? x[u] : 0.f;
+            }
+            if (j < ni) se_split(s * a.inv, v1, p1, j, ch);
+        }
     }
     // Inputs past the end are zeros.  (Columns of images that are not there hold anything: columns do not meet.)
     if (tid < 16 * 32) {

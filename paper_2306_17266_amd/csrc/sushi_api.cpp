@@ -23,7 +23,7 @@ using namespace sushi;
 
 namespace {
 
-enum StepKind { STEP_SE_GATE = 16 };  // launches that are not one op of the plan (Launch::kind, beyond OpKind)
+enum StepKind { STEP_SE_GATE = 16, STEP_EXPAND_DW = 17 };  // launches that are not one op of the plan (Launch::kind, beyond OpKind)
 
 struct Launch {
     int kind;
@@ -31,6 +31,8 @@ struct Launch {
     ConvArgs conv{};
     PoolArgs pool{};
     SeGateArgs se{};
+    ExpandDwArgs xdw{};
+    ExpandDwGeom xdw_geom{};
     QuantArgs quant{};  // int8 mode
     int in_patch = 0, out_patch = 0;  // 1 = pointer is the caller's input / logits buffer
     bool finite_w = true;             // SuperLayer::finite_w
@@ -320,7 +322,8 @@ void *buf_ptr(sushi_ctx *c, const BufBase &bb, int id, bool small) {
     return small ? bb.block + N_BIG_BUFS * bb.big_bytes + id * bb.small_bytes : bb.block + id * bb.big_bytes;
 }
 
-// cp.steps from cp.launches.  A squeeze-excite block (pooling, two fully connected layers, gating, the 1x1 layer behind it):
+// cp.steps from cp.launches.  A 1x1 expansion and the depthwise layer behind it, with the sums of a pooling behind that: one
+// launch (nobody else reads the expanded map).  A squeeze-excite block (pooling, two fully connected layers, gating, the 1x1 layer behind it):
 // both fully connected layers in one launch, the gating in the 1x1 layer's operand reads.  Nobody else reads the hidden
 // vector or the gated map.
 void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
@@ -328,25 +331,61 @@ void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
     if (!c->bf16 || c->int8) return;
     const std::vector<Launch> &in = cp.launches;
     const std::vector<Op> &ops = cp.plan.ops;
+    // ops i .. i + 3 as two launches; pooled: the sums to start from (null: what op i reads)
+    auto squeeze_excite = [&](size_t i, const float *pooled, int parts, float inv, Launch &S, Launch &P) {
+        if (!(i + 3 < in.size() && ops[i].kind == OP_FC && ops[i].act == SUSHI_ACT_RELU && ops[i + 1].kind == OP_FC && ops[i + 1].hsigmoid &&
+              ops[i + 2].kind == OP_GATE && ops[i + 3].kind == OP_CONV && ops[i + 3].in_buf == ops[i + 2].out_buf &&
+              ops[i + 1].in_buf == ops[i].out_buf && ops[i + 2].gate_buf == ops[i + 1].out_buf))
+            return false;
+        const ConvArgs &f1 = in[i].conv, &f2 = in[i + 1].conv;
+        S = Launch();
+        S.kind = STEP_SE_GATE;
+        S.op = (int)i;
+        S.se = SeGateArgs{pooled ? pooled : static_cast<const float *>(f1.x), f1.w, f2.w, f1.shift, f2.shift, static_cast<float *>(f2.y),
+                          f1.B, f1.C, f1.K, f1.Kpad, f2.Kpad, parts, inv};
+        P = in[i + 3];
+        P.conv.x = in[i + 2].pool.x;
+        P.quant.gate = S.se.gate;
+        P.op = (int)i + 2;
+        return se_gate_covers(S.se) && gated_conv_covers(P.conv);
+    };
     for (size_t i = 0; i < in.size(); ++i) {
-        if (i + 3 < in.size() && ops[i].kind == OP_FC && ops[i].act == SUSHI_ACT_RELU && ops[i + 1].kind == OP_FC && ops[i + 1].hsigmoid &&
-            ops[i + 2].kind == OP_GATE && ops[i + 3].kind == OP_CONV && ops[i + 3].in_buf == ops[i + 2].out_buf &&
-            ops[i + 1].in_buf == ops[i].out_buf && ops[i + 2].gate_buf == ops[i + 1].out_buf) {
-            const ConvArgs &f1 = in[i].conv, &f2 = in[i + 1].conv;
-            Launch S, P = in[i + 3];
-            S.kind = STEP_SE_GATE;
-            S.op = (int)i;
-            S.se = SeGateArgs{static_cast<const float *>(f1.x), f1.w, f2.w, f1.shift, f2.shift, static_cast<float *>(f2.y),
-                          f1.B, f1.C, f1.K, f1.Kpad, f2.Kpad, 1, 1.0f};
-            P.conv.x = in[i + 2].pool.x;
-            P.quant.gate = S.se.gate;
-            P.op = (int)i + 2;
-            if (se_gate_covers(S.se) && gated_conv_covers(P.conv)) {
-                cp.steps.push_back(S);
-                cp.steps.push_back(P);
-                i += 3;
+        if (i + 1 < in.size() && ops[i].kind == OP_CONV && ops[i].r == 1 && ops[i].stride == 1 && ops[i].res_buf == BUF_NONE && !ops[i].in_small &&
+            ops[i + 1].kind == OP_DW && ops[i + 1].in_buf == ops[i].out_buf) {
+            const ConvArgs &e = in[i].conv, &d = in[i + 1].conv;
+            Launch X;
+            X.kind = STEP_EXPAND_DW;
+            X.op = (int)i;
+            X.in_patch = in[i].in_patch;
+            X.xdw = ExpandDwArgs{e.x, d.y, e.w, d.w, e.scale, e.shift, d.scale, d.shift, nullptr, e.B, e.H, e.W, e.C, d.K, d.P, d.Q, d.R, d.stride, e.Kpad, d.Kpad, e.act};
+            if (e.act == d.act && expand_dw_covers(X.xdw)) {
+                Launch S, P;
+                if (i + 2 < in.size() && ops[i + 2].kind == OP_GAP && ops[i + 2].in_buf == ops[i + 1].out_buf) {
+                    // with the pooling's sums, which go where the expanded map would have been
+                    X.xdw.pool = static_cast<float *>(e.y);
+                    X.xdw_geom = expand_dw_geom(X.xdw);
+                    const int parts = X.xdw_geom.parts;
+                    if ((long)e.H * e.W >= 2l * parts && squeeze_excite(i + 3, X.xdw.pool, parts, 1.0f / (float)(d.P * d.Q), S, P)) {
+                        cp.steps.push_back(X);
+                        cp.steps.push_back(S);
+                        cp.steps.push_back(P);
+                        i += 6;
+                        continue;
+                    }
+                    X.xdw.pool = nullptr;
+                }
+                X.xdw_geom = expand_dw_geom(X.xdw);
+                cp.steps.push_back(X);
+                i += 1;
                 continue;
             }
+        }
+        Launch S, P;
+        if (ops[i].kind == OP_FC && squeeze_excite(i, nullptr, 1, 1.0f, S, P)) {
+            cp.steps.push_back(S);
+            cp.steps.push_back(P);
+            i += 3;
+            continue;
         }
         cp.steps.push_back(in[i]);
     }
@@ -445,6 +484,11 @@ void launch_cost(const sushi_ctx *c, const Launch &L, double *bytes, double *flo
         const double wts = L.kind == OP_DW ? a.K * taps : (double)a.K * a.C * taps;
         *bytes = in * (a.in_f32 ? 4.0 : es) + (L.quant.gate ? 4.0 * a.B * a.C : 0.0) + (wts + (a.res ? out : 0.0)) * es + out * (a.out_f32 ? 4.0 : es) + 8.0 * a.K;
         *flops = 2.0 * out * (L.kind == OP_DW ? taps : a.C * taps);
+    } else if (L.kind == STEP_EXPAND_DW) {
+        const ExpandDwArgs &a = L.xdw;
+        const double in = (double)a.B * a.H * a.W, out = (double)a.B * a.P * a.Q * a.K, taps = (double)a.R * a.R;
+        *bytes = (in * a.C + out + (double)a.K * (a.C + taps)) * es + 16.0 * a.K;
+        *flops = 2.0 * (in * a.C * a.K + out * taps);
     } else if (L.kind == STEP_SE_GATE) {
         const SeGateArgs &a = L.se;
         const double wts = 2.0 * a.C * a.red;
@@ -549,6 +593,13 @@ hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, v
                 kc = KC_GATE;
                 e = launch_gate(L.pool, c->bf16, st);
                 break;
+            case STEP_EXPAND_DW: {
+                ExpandDwArgs a = L.xdw;
+                if (L.in_patch) a.x = input_dev;
+                kc = KC_EXPAND_DW;
+                e = launch_expand_dw(a, L.xdw_geom, st);
+                break;
+            }
             case STEP_SE_GATE:
                 kc = KC_SE_GATE;
                 e = launch_se_gate(L.se, st);

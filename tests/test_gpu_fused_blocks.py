@@ -63,3 +63,40 @@ def _check(arch, batch, kernels, seed=83):
                                                     (6, 160, 12, 64), (6, 24, 62, 9)])
 def test_squeeze_excite(expand, width, res, batch):
     _check(block_net(expand, 3, (2, 2) if res == 8 else (1, 2), A.ACT_HSWISH, res, width), batch, {"se_gate_kernel"})
+
+
+# Expansion and depthwise layer in one launch: every kernel size and stride; input channels of one to five reduction steps, ending
+# inside one (8, 24, 40, 72, 120, 160); expanded channels that end inside a block of 32 (24, 72, 120, 240); maps smaller than the
+# kernel, of one tile, one pixel past it and of several, odd ones; one image and many tiles per workgroup; with the pooling's sums
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("expand,width,strides,res,batch,se", [
+    (3, 8, (1, 2), 8, 1, 0), (3, 24, (1, 2), 28, 2, 0), (6, 40, (2, 1), 66, 1, 1), (3, 72, (1, 2), 34, 3, 1), (2, 120, (1, 2), 30, 1, 0), (6, 160, (1, 2), 14, 2, 1),
+    (3, 24, (2, 1), 112, 3, 1), (6, 8, (2, 2), 8, 70, 1), (4, 24, (1, 2), 62, 30, 0)])
+def test_expand_depthwise(kernel, expand, width, strides, res, batch, se):
+    _check(block_net(expand, kernel, strides, A.ACT_HSWISH if kernel == 5 else A.ACT_RELU, res, width, se), batch, {"expand_dw_kernel"})
+
+
+# Expanded values that overflow to infinity at a few pixels of two channels, depthwise weights all negative there: minus infinity,
+# which ReLU makes 0, at the outputs that use them, and what the single layers give elsewhere
+@pytest.mark.parametrize("kernel", [3, 5, 7])
+@pytest.mark.parametrize("strides,res", [((1, 2), 20), ((2, 1), 70)])
+def test_expand_depthwise_infinite_values(kernel, strides, res):
+    import paper_2306_17266_amd as S
+    arch = block_net(3, kernel, strides, A.ACT_RELU, res, 16, 0)
+    table = S.sushi_describe_supernet(arch)
+    tens = T.make_weights([(s, k) for _, s, k in table], 89, True)
+    for (name, _, _), t in zip(table, tens):
+        if name == "s0b0.expand.scale":
+            t[[5, 38]] = 3e38
+        elif name == "s0b0.expand.shift":
+            t[[5, 38]] = -3e38
+        elif name == "s0b0.dw.shift":
+            t[[5, 38]] = 0.0
+        elif name == "s0b0.dw.w":
+            t[[5, 38]] = -np.abs(t[[5, 38]]) - 0.01
+    x = torch.from_numpy(T.make_input(89, 0, 2, res, arch.in_channels, True)).cuda().to(torch.bfloat16)
+    got, _ = _logits(arch, T.flatten(tens), x, True)
+    want, _ = _logits(arch, T.flatten(tens), x, False)
+    assert np.isfinite(want).all()
+    for n in range(2):
+        assert rel_l2(got[n], want[n]) <= TOL, n
