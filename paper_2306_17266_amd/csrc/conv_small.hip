@@ -194,8 +194,10 @@ __global__ __launch_bounds__(TYPE == ST_F32 ? 512 : 256) void conv_small_kernel(
                 for (int i = 0; i < 4; ++i) v[i] += F32 ? __uint_as_float(res[i]) : bf2f(i & 1 ? res[i >> 1] >> 16 : res[i >> 1] & 0xFFFFu);
             }
         }
+        with_activation(a.act, a.hsigmoid, [&](auto act) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = activate(v[i], a.act, a.hsigmoid);
+            for (int i = 0; i < 4; ++i) v[i] = activate_as<decltype(act)::value>(v[i]);
+        });
         if (F32 || a.out_f32) {
             float *yp = static_cast<float *>(a.y) + o;
             if (vec)

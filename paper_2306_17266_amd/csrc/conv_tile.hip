@@ -236,6 +236,8 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     }
     __syncthreads();
     const uint4 *const ss = ct_lds + g.part;
+    float sc[8], sh[8];
+    if constexpr (!I8) load8(reinterpret_cast<const float *>(ss) + cc * 8, sc), load8(reinterpret_cast<const float *>(ss) + BN + cc * 8, sh);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         const int idx = tid + NT * e;
@@ -269,14 +271,16 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
                 v[0] += lo.x, v[1] += lo.y, v[2] += lo.z, v[3] += lo.w;
                 v[4] += hi.x, v[5] += hi.y, v[6] += hi.z, v[7] += hi.w;
             }
-            const float *sc = reinterpret_cast<const float *>(ss) + cc * 8, *sh = sc + BN;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 v[i] = v[i] * sc[i] + sh[i];
                 if (a.res) v[i] += bf2f(i & 1 ? res[e][i >> 1] >> 16 : res[e][i >> 1] & 0xFFFFu);
-                v[i] = activate(v[i], a.act, a.hsigmoid);
             }
-            const ct_u32x4 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
+            ct_u32x4 o;
+            with_activation(a.act, a.hsigmoid, [&](auto act) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = pack_bf16x2(activate_as<decltype(act)::value>(v[2 * i]), activate_as<decltype(act)::value>(v[2 * i + 1]));
+            });
             __builtin_amdgcn_raw_buffer_store_b128(o, ry, ooff[e], 0, 0);
         }
     }

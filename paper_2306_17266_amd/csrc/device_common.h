@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -120,6 +121,26 @@ __device__ __forceinline__ u32x4_t gate_cell(u32x4_t x, u32x4_t g0, u32x4_t g1) 
         o[i] = pack_bf16x2(bf2f(x[i] & 0xFFFFu) * __uint_as_float(g[2 * (i & 1)]), bf2f(x[i] >> 16) * __uint_as_float(g[2 * (i & 1) + 1]));
     }
     return o;
+}
+
+// activate() with the activation as a constant (3: hard sigmoid), and a call of f with it.  One branch around an epilogue: with
+// activate() per element the compiler makes four branches for each, 100 clocks and more (conv_tile_kernel, 16 x 14 x 14 x
+// 360, 1x1 -> 1024 with residual: 12.6 us, 11.2 without them).
+template <int ACT>
+__device__ __forceinline__ float activate_as(float v) {
+    return ACT == 3 ? fminf(fmaxf(v + 3.0f, 0.0f), 6.0f) * (1.0f / 6.0f) : ACT == 2 ? v * fminf(fmaxf(v + 3.0f, 0.0f), 6.0f) * (1.0f / 6.0f) : ACT == 1 ? fmaxf(v, 0.0f) : v;
+}
+
+template <typename F>
+__device__ __forceinline__ void with_activation(int act, int hsig, F f) {
+    if (hsig)
+        f(std::integral_constant<int, 3>{});
+    else if (act == 1)
+        f(std::integral_constant<int, 1>{});
+    else if (act == 2)
+        f(std::integral_constant<int, 2>{});
+    else
+        f(std::integral_constant<int, 0>{});
 }
 
 // A buffer load's offset, or one past the end of every buffer below 2 GiB (zeros arrive).  Without a condition: `ok ? offset :

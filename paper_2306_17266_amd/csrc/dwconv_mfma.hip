@@ -138,8 +138,11 @@ __global__ __launch_bounds__(256, 2) void dw_mfma_kernel(ConvArgs a, DwTasks t) 
         const int f = c0 + kg * 4;
         const bool mine = q < a.Q && f < a.K;
         auto finish = [&](int p, float s0, float s1, float s2, float s3) {
-            const float v0 = activate(s0 * sc.x + sh.x, a.act, 0), v1 = activate(s1 * sc.y + sh.y, a.act, 0);
-            const float v2 = activate(s2 * sc.z + sh.z, a.act, 0), v3 = activate(s3 * sc.w + sh.w, a.act, 0);
+            float v0 = s0 * sc.x + sh.x, v1 = s1 * sc.y + sh.y, v2 = s2 * sc.z + sh.z, v3 = s3 * sc.w + sh.w;
+            with_activation(a.act, 0, [&](auto act) {
+                constexpr int ACT = decltype(act)::value;
+                v0 = activate_as<ACT>(v0), v1 = activate_as<ACT>(v1), v2 = activate_as<ACT>(v2), v3 = activate_as<ACT>(v3);
+            });
             *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.y) + (((long)n * a.P + p) * a.Q + q) * a.K + f) =
                 make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
         };

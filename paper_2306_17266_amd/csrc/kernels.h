@@ -188,6 +188,11 @@ hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch, const 
 bool conv_tile_gated_covers(const ConvArgs &a);
 hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
 
+// 3x3 with stride 1 and long reductions: the tile kernel's form with a reduction split over waves (conv_ksplit.hip); patch as
+// above.  Returns hipErrorNotSupported (nothing launched) for any other case and where another kernel is the faster one.
+hipError_t launch_conv_ksplit(const ConvArgs &a, hipStream_t s, bool patch);
+hipError_t launch_conv_ksplit_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
+
 // Dense convolution of few pixels and fully connected layers, C a multiple of 8 (conv_small.hip).  bf16 and float32:
 // return hipErrorNotSupported (nothing launched) for tensors of 2 GiB and more.
 hipError_t launch_conv_small(const ConvArgs &a, hipStream_t s, const float *gate = nullptr);

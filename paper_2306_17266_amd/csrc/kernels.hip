@@ -548,6 +548,7 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
         return e;
     };
     hipError_t e = chosen && patch ? picked(launch_conv_patch(a, s), KC_CONV_PATCH) : hipErrorNotSupported;
+    if (e == hipErrorNotSupported) e = picked(launch_conv_ksplit(a, s, patch && !chosen), KC_CONV_TILE);
     if (e == hipErrorNotSupported && conv_small_is_faster(a, false)) e = picked(launch_conv_small(a, s), KC_CONV_SMALL);
     if (e == hipErrorNotSupported) e = picked(launch_conv_tile(a, s, patch && !chosen), KC_CONV_TILE);
     if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch(a, s), KC_CONV_PATCH);

@@ -92,8 +92,10 @@ __global__ __launch_bounds__(256) void stem_mfma_kernel(ConvArgs a, int tiles_m)
             const f32x4_t d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i].v, fb.v, f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
             const int f = f0 + i * 16 + kg * 4;
             float v[4];
+            with_activation(a.act, a.hsigmoid, [&](auto act) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = activate(d[k] * sc[i][k] + sh[i][k], a.act, a.hsigmoid);
+                for (int k = 0; k < 4; ++k) v[k] = activate_as<decltype(act)::value>(d[k] * sc[i][k] + sh[i][k]);
+            });
             if (m < M && f < a.K)
                 *reinterpret_cast<uint2 *>(static_cast<uint16_t *>(a.y) + (long)m * a.K + f) =
                     make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
