@@ -30,6 +30,7 @@ constexpr int CT_OOB = 0x7FFFFFF0;
 
 struct TileGeom {
     int tiles_f, tiles_m;
+    TileOrder order;
     int M;       // B * P * Q
     int kcells;  // cells of the reduction: taps * cells per tap
     int per;     // steps (of eight cells) per wave group
@@ -56,7 +57,8 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     const int ntiles = g.tiles_f * g.tiles_m, per_xcd = (ntiles + 7) >> 3;
     const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (tile >= ntiles) return;
-    const int tf = tile / g.tiles_m, tm = tile - tf * g.tiles_m;
+    int tf, tm;
+    tile_place(tile, g.order, &tf, &tm);
     const int f0 = tf * BN, m0 = tm * BM;
     const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C * ES), 0x00020000);
@@ -286,6 +288,17 @@ __global__ __launch_bounds__(256 * KS, 4) void conv_tile_kernel(ConvArgs a, Tile
     }
 }
 
+// Filters fast?  3x3 where the input is larger than the weights; 1x1 in bf16 where it is ten times as large (stride 2: and the reduction
+// long); from about one tile per compute unit on.  In whole queries, pixels and filters fast, us: 16 x 56 x 56 x 176 3x3/2 25.3 and
+// 22.1; 61 x 14 x 14, 256 -> 1024 23.7 and 20.0; 16 x 28 x 28, 512 -> 176 10.9 and 9.4; on the other side 16 x 14 x 14, 1024 -> 720
+// 14.7 and 15.9; 16 x 56 x 56, 256 -> 512 /2 13.7 and 16.2; int8 16 x 28 x 28, 176 -> 512 11.8 and 13.9.
+static bool tile_filters_fast(const ConvArgs &a, bool i8, long tiles) {
+    const long M = (long)a.B * a.P * a.Q;
+    if (tiles <= 192) return false;
+    if (a.R == 3) return (long)a.B * a.H * a.W > 9l * a.K;
+    return !i8 && M >= 10l * a.K && (a.stride == 1 || a.C >= 512);
+}
+
 // Cells of the gates that a tile of 64 pixels may need: as many images as it can touch.
 static long tile_gate_cells(const ConvArgs &a) { return std::min((long)a.B, 62l / ((long)a.P * a.Q) + 2) * (a.C >> 2); }
 
@@ -295,6 +308,7 @@ static hipError_t launch_tile(const ConvArgs &a, const QuantArgs &q, hipStream_t
     TileGeom g;
     g.M = a.B * a.P * a.Q;
     g.tiles_f = (a.K + 63) / 64, g.tiles_m = (g.M + BM - 1) / BM;
+    g.order = tile_order(tile_filters_fast(a, I8, (long)g.tiles_f * g.tiles_m), g.tiles_f, g.tiles_m);
     const int cells = (a.C + CPC - 1) / CPC;
     g.kcells = R * R * cells;
     g.per = ((g.kcells + 7) / 8 + KS - 1) / KS;

@@ -156,4 +156,11 @@ __device__ __forceinline__ int fdiv(int n, const FastDiv &f) {
     return (int)((__umulhi((unsigned)n, f.mul) >> f.shr) + ((unsigned)n & f.one));
 }
 
+// Tile number -> (filter tile, pixel tile).
+__device__ __forceinline__ void tile_place(int tile, const TileOrder &o, int *tf, int *tm) {
+    const int slow = fdiv(tile, o.fast), fast = tile - slow * o.fast.d;
+    *tf = o.filters_fast ? fast : slow;
+    *tm = o.filters_fast ? slow : fast;
+}
+
 }  // namespace sushi

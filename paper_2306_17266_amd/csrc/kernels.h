@@ -61,6 +61,13 @@ __host__ inline FastDiv make_fastdiv(int d) {
     return f;
 }
 
+// Order of a dense layer's tiles: consecutive tiles run on one XCD (one of eight equal ranges each).  With pixels fast an XCD reads
+// the whole input and an eighth of the weights, with filters fast an eighth of the input and all weights.
+struct TileOrder {
+    int filters_fast;
+    FastDiv fast;  // division by the tiles along the fast axis
+};
+
 struct ConvArgs {
     const void *x;       // input activations
     void *y;             // output activations
@@ -137,6 +144,10 @@ struct PoolArgs {
     int B, H, W, C, P, Q;
     int out_f32;        // OP_GAP in bf16 mode: store the averages as float32
 };
+
+inline TileOrder tile_order(bool filters_fast, int tiles_f, int tiles_m) {
+    return TileOrder{filters_fast ? 1 : 0, make_fastdiv(filters_fast ? tiles_f : tiles_m)};
+}
 
 // Kernel families, for per-kernel accounting.
 enum KernelClass {
