@@ -12,6 +12,15 @@
 
 namespace sushi {
 
+// activate() as selects, for the depthwise units.  Those are bound by vector instructions and compute eight channels per
+// output, and the uniform branches that activate() becomes around each of the eight cost more than computing both
+// activations does: a stream of MobileNet-V3 queries 16.04 -> 15.19 ms.  The units with matrix products keep activate(): they
+// hold four values per lane, and with selects a stream of ResNet50 queries at batch 16 takes 48.15 instead of 47.64 ms.
+__device__ __forceinline__ float activate_select(float v, int act) {
+    const float h = v * fminf(fmaxf(v + 3.0f, 0.0f), 6.0f) * (1.0f / 6.0f), r = act == 1 ? fmaxf(v, 0.0f) : v;
+    return act == 2 ? h : r;
+}
+
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 // Pointers read from a descriptor are generic to the compiler; weights are known to be in device memory.
@@ -1284,7 +1293,7 @@ __device__ __forceinline__ void dwconv_units(const ConvArgs &a, int rank, int nr
         load8(a.scale + c, sc);
         load8(a.shift + c, sh);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = activate(acc[j] * sc[j] + sh[j], a.act, 0);
+        for (int j = 0; j < 8; ++j) acc[j] = activate_select(acc[j] * sc[j] + sh[j], a.act);
         act_st16<ST>(ry, out_cell(a, n, cg, pp * a.Q + qq), pack8(acc));
     }
 }
@@ -1401,7 +1410,7 @@ __device__ __forceinline__ void dw_tiled_units(const DevOp &op, float *lds, int 
                 for (int k = 0; k < IT; ++k) {
                     const int q = qb * IT + k;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) acc[k][j] = activate(acc[k][j] * sc[j] + sh[j], a.act, 0);
+                    for (int j = 0; j < 8; ++j) acc[k][j] = activate_select(acc[k][j] * sc[j] + sh[j], a.act);
                     act_st16<ST>(ry, q < a.Q ? out_cell(a, n, cg0 + cb, (p0 + pr) * a.Q + q) : (int)OOB_OFFSET, pack8(acc[k]));
                 }
             }
@@ -1480,7 +1489,7 @@ __device__ __forceinline__ void dw_direct_units(const DevOp &op, int rank, int n
         for (int k = 0; k < IT; ++k) {
             const int pr = pb * IT + k;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[k][j] = activate(acc[k][j] * sc[j] + sh[j], a.act, 0);
+            for (int j = 0; j < 8; ++j) acc[k][j] = activate_select(acc[k][j] * sc[j] + sh[j], a.act);
             act_st16<ST>(ry, pr < a.P ? out_cell(a, n, cg, pr * a.Q + q) : (int)OOB_OFFSET, pack8(acc[k]));
         }
     }
