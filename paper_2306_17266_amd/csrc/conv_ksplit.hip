@@ -333,7 +333,7 @@ static int ksplit_shape(const ConvArgs &a, double *us) {
     return best;
 }
 
-// Against conv_small_kernel by that fit and one of its own times (3.4 us + its 16 x 16 tiles x steps / 8500, int8 / 5000; 1.6
+// Against conv_small_kernel by that fit and one of its own times (3.4 us + its 16 x 16 tiles x steps / 8500, int8 2.9 + / 5600; 1.6
 // times the work where pixels lie a multiple of 256 bytes apart, which crowds few cache channels): 3 x 14 x 14 x 208 6.5 us here
 // and 6.2 there, x 256 6.5 and 10.9; 1 x 7 x 7 x 720 11.0 and 7.7.  Against the patch kernel: short reductions (two chunks) on
 // many pixels stay there (61 x 28 x 28 x 128 20.4 us here at best, 19.0 there; int8 x 256 channels the same).  Against the
@@ -347,7 +347,7 @@ static hipError_t launch_ksplit(const ConvArgs &a, const QuantArgs &q, hipStream
     const long M = (long)a.B * a.P * a.Q;
     const int cpc = I8 ? 16 : 8, cells = (a.C + cpc - 1) / cpc;
     const double work = (double)((M + 15) / 16) * ((a.K + 15) / 16) * ((9 * cells + 3) / 4);
-    if (us > 3.4 + work / (I8 ? 5000.0 : 8500.0) * (a.C * (I8 ? 1 : 2) % 256 == 0 ? 1.6 : 1.0)) return hipErrorNotSupported;
+    if (us > (I8 ? 2.9 : 3.4) + work / (I8 ? 5600.0 : 8500.0) * (a.C * (I8 ? 1 : 2) % 256 == 0 ? 1.6 : 1.0)) return hipErrorNotSupported;
     if (patch && cells <= 16 && M > 24000) return hipErrorNotSupported;
     switch (shape) {
         case 0: return launch_ksplit_tile<1, 1, I8>(a, q, s);
