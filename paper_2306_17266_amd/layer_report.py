@@ -1,10 +1,11 @@
-"""Per-layer roofline report of one SubNet in exec mode 0 (one launch per op).
+"""Per-layer roofline report of one SubNet in exec mode 0 (one launch per op, or per few ops that run fused).
 
     python -m paper_2306_17266_amd.layer_report --workload resnet_bs16_levels --subnet max --reps 20
 
-The report lists, per op of the SubNet's plan, the median duration over `reps` queries, the algorithmic bytes
-and flops the library counts for it (active slice only), the achieved GB/s and TFLOP/s, and the fraction of the
-op's own bound max(flops / MFMA peak, bytes / HBM peak).
+The report lists, per launch, the median duration over `reps` queries, the algorithmic bytes and flops of its op of
+the SubNet's plan (active slice only), the achieved GB/s and TFLOP/s, and the fraction of its own bound
+max(flops / MFMA peak, bytes / HBM peak).  A launch that runs several ops (1x1 expansion + depthwise, the two layers
+of a squeeze-excite gate, gating + 1x1) stands under its first one; maps between its ops are not counted.
 
 Durations come from one of two clocks:
   * by default, HIP events the library puts around every launch (SUSHI_OPT_KERNEL_TIMING).  An event pair adds
@@ -12,8 +13,8 @@ Durations come from one of two clocks:
   * with --from-trace FILE, the kernel trace of a profiler run of this same command:
         rocprofv3 --kernel-trace --output-format csv -d DIR -o lr -- python3 -m paper_2306_17266_amd.layer_report ... --plain
         python3 -m paper_2306_17266_amd.layer_report ... --from-trace DIR/lr_kernel_trace.csv
-    (--plain runs the queries without events; the second call needs no GPU: the k-th launch of a query is the
-    k-th op of its plan, and the library's kernels are told apart from others by name).
+    (--plain runs the queries without events; the second call needs no GPU: the launches of a query run the ops of
+    its plan in order, and the library's kernels are told apart from others, and fused ones from single ones, by name).
 """
 import argparse
 import os
@@ -90,7 +91,7 @@ def main():
     recs = ctx.sushi_get_launch_records()
     names = [k["name"] for k in ctx.sushi_get_kernel_stats()]
     ctx.sushi_set_option(S.OPT_KERNEL_TIMING, 0)
-    ops = S.sushi_team_plan(arch, cfg, batch, 32)
+    ops = plan_ops(arch, cfg, batch)
     per_op = {}
     for op_index, kc, ms, byts, flops in recs:
         per_op.setdefault(op_index, []).append((ms, names[kc], byts, flops))
@@ -113,64 +114,110 @@ def op_cost(op, es=2.0):
     return (cin + out) * es + (4.0 * op["B"] * op["C"] if kind == 5 else 0.0), (9.0 * out if kind == 2 else cin)
 
 
-def report_from_trace(args, arch, cfg, batch):
-    import csv
-
+def plan_ops(arch, cfg, batch):
+    """The ops of the SubNet's plan as this mode runs them.  The team kernel runs a squeeze-excite block from its pooling's
+    slot (kind 6) and skips the next three; here they are pooling, two FC layers and gating."""
     import paper_2306_17266_amd as S
     ops = S.sushi_team_plan(arch, cfg, batch, 32)
+    for i, op in enumerate(ops):
+        if op["kind"] == 6:
+            ops[i] = dict(op, kind=3, P=1, Q=1, K=op["C"])
+            for k, kind in enumerate((4, 4, 5)):
+                ops[i + 1 + k] = dict(ops[i + 1 + k], kind=kind)
+    return ops
+
+
+def fused_cost(ops, es=2.0):
+    """op_cost of the ops of one launch without the maps that pass between them."""
+    byts = sum(op_cost(op, es)[0] for op in ops if op["kind"] not in (3, 5))
+    flops = sum(op_cost(op, es)[1] for op in ops if op["kind"] not in (3, 5))
+    if [op["kind"] for op in ops[:2]] == [0, 1]:
+        byts -= 2.0 * es * ops[0]["B"] * ops[0]["P"] * ops[0]["Q"] * ops[0]["K"]
+    elif len(ops) > 1 and ops[0]["kind"] == 5:
+        byts += 4.0 * ops[0]["B"] * ops[0]["C"]
+    elif len(ops) == 1:
+        return op_cost(ops[0], es)
+    return byts, flops
+
+
+def ops_of_launch(ops, i, name, following):
+    """How many ops from op i on the launch of kernel `name` runs; `following`: the kernel launched behind it."""
+    kinds = [op["kind"] for op in ops[i:i + 3]]
+    if name == "expand_dw_kernel":
+        return 3 if kinds[2:] == [3] and following == "se_gate_kernel" else 2
+    if name == "se_gate_kernel":
+        return 2
+    return 2 if kinds[0] == 5 and name != "gate_kernel" else 1
+
+
+def report_from_trace(args, arch, cfg, batch):
+    import csv
+    import re
+
+    ops = plan_ops(arch, cfg, batch)
     mine = ("conv_i8_direct_kernel", "maxpool_i8_kernel", "gap_i8_kernel", "fc_i8_kernel",
             "conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel", "conv_tile_kernel", "stem_mfma_kernel", "dw_mfma_kernel", "conv_patch_kernel", "dwconv_kernel",
-            "dwconv_rows_kernel", "maxpool_kernel", "gap_kernel", "gate_kernel")
+            "dwconv_rows_kernel", "maxpool_kernel", "gap_kernel", "gate_kernel", "expand_dw_kernel", "se_gate_kernel")
     rows = []
     for r in csv.DictReader(open(args.from_trace)):
         name = r["Kernel_Name"]
-        short = next((m for m in mine if "sushi::" + m in name or name.startswith(m) or ("::" + m + "<") in name or (" " + m + "<") in name), None)
+        short = next((m for m in mine if re.search(r"(^|::| )" + m + r"\b", name)), None)
         if short is None:
             continue
         rows.append((int(r["Start_Timestamp"]), (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-6, short))
     rows.sort()
-    n_ops = len(ops)
-    assert len(rows) % n_ops == 0 and len(rows) >= n_ops * args.reps, (len(rows), n_ops)
-    rows = rows[-n_ops * args.reps:]                                  # the timed queries come last
-    per_op = {}
+    queries, i = [[]], 0                       # per query its launches, each with the ops it ran
     for k, (_, ms, short) in enumerate(rows):
-        i = k % n_ops
-        byts, flops = op_cost(ops[i], 1.0 if args.int8 else 2.0)
-        per_op.setdefault(i, []).append((ms, short, byts, flops))
+        n = ops_of_launch(ops, i, short, rows[k + 1][2] if k + 1 < len(rows) else "")
+        byts, flops = fused_cost(ops[i:i + n], 1.0 if args.int8 else 2.0)
+        queries[-1].append((i, ms, short, byts, flops))
+        i += n
+        if i >= len(ops):
+            queries.append([])
+            i = 0
+    assert i == 0 and len(queries) > args.reps, (i, len(queries), len(rows), len(ops))
+    per_op = {}
+    for q in queries[-args.reps - 1:-1]:       # the timed queries come last
+        for i, ms, short, byts, flops in q:
+            per_op.setdefault(i, []).append((ms, short, byts, flops))
     print_report(args, cfg, batch, ops, per_op, "rocprofv3 kernel trace")
 
 
 def print_report(args, cfg, batch, ops, per_op, clock):
     names = None
-    print("# %s, SubNet %s, batch %d, resolution %d, exec mode 0, median of %d launches per op; durations: %s" %
+    print("# %s, SubNet %s, batch %d, resolution %d, exec mode 0, median over %d queries per launch; durations: %s" %
           (args.workload, args.subnet, batch, cfg.resolution, args.reps, clock))
     mfma_peak = 5000.0 if getattr(args, "int8", False) else MFMA_TFLOPS
     print("# peaks: HBM %.0f GB/s, dense %s MFMA %.0f T%sOP/s; bound = max(flops / peak, bytes / peak)" %
           (HBM_GBS, "int8" if mfma_peak > MFMA_TFLOPS else "bf16", mfma_peak, "" if mfma_peak > MFMA_TFLOPS else "FL"))
-    print("%3s %-7s %-26s %-24s %9s %9s %9s %9s %8s %5s %6s" %
+    print("%3s %-14s %-26s %-24s %9s %9s %9s %9s %8s %5s %6s" %
           ("op", "kind", "shape BxHxWxC->PxQxK rxr/s", "kernel", "us", "MB", "GFLOP", "GB/s", "TFLOP/s", "bound", "frac"))
     tot_us = tot_bound = 0.0
     by_kind = {}
-    for i in sorted(per_op):
+    firsts = sorted(per_op)
+    for i, end in zip(firsts, firsts[1:] + [len(ops)]):
         ms = float(np.median([r[0] for r in per_op[i]]))
         _, kname, byts, flops = per_op[i][0]
-        op = ops[i]
+        # what a launch of several ops is listed as: its first op's input, its last op's output, its depthwise layer's taps
+        op = dict(max((o for o in ops[i:end] if o["kind"] not in (3, 5)), key=lambda o: o["R"], default=ops[i]), C=ops[i]["C"],
+                  H=ops[i]["H"], W=ops[i]["W"], K=ops[end - 1]["K"])
+        kind_name = "+".join(KIND.get(o["kind"], "?") for o in ops[i:end])
         us = ms * 1e3
         t_mem, t_mma = byts / (HBM_GBS * 1e3), flops / (mfma_peak * 1e6)      # microseconds
         bound_us = max(t_mem, t_mma)
         which = "mfma" if t_mma > t_mem else "hbm"
         shape = "%dx%dx%dx%d->%dx%dx%d %dx%d/%d" % (op["B"], op["H"], op["W"], op["C"], op["P"], op["Q"], op["K"],
                                                    op["R"], op["R"], op["stride"])
-        print("%3d %-7s %-26s %-24s %9.2f %9.3f %9.3f %9.1f %8.1f %5s %6.3f" %
-              (i, KIND.get(op["kind"], "?"), shape, kname, us, byts / 1e6, flops / 1e9, byts / us / 1e3,
+        print("%3d %-14s %-26s %-24s %9.2f %9.3f %9.3f %9.1f %8.1f %5s %6.3f" %
+              (i, kind_name, shape, kname, us, byts / 1e6, flops / 1e9, byts / us / 1e3,
                flops / us / 1e6, which, bound_us / us))
         tot_us += us
         tot_bound += bound_us
-        k = by_kind.setdefault((KIND.get(op["kind"], "?"), which), [0.0, 0.0, 0.0, 0.0])
+        k = by_kind.setdefault((kind_name, which), [0.0, 0.0, 0.0, 0.0])
         k[0] += us; k[1] += byts; k[2] += flops; k[3] += bound_us
-    print("# whole query: %.1f us in kernels, summed per-op bound %.1f us, fraction %.3f" % (tot_us, tot_bound, tot_bound / tot_us))
+    print("# whole query: %.1f us in kernels, summed per-launch bound %.1f us, fraction %.3f" % (tot_us, tot_bound, tot_bound / tot_us))
     for (kind, which), (us, byts, flops, b) in sorted(by_kind.items()):
-        print("# %-7s %-4s-bound ops: %9.1f us, %8.1f GB/s, %8.1f TFLOP/s, fraction of their bound %.3f" %
+        print("# %-14s %-4s-bound ops: %9.1f us, %8.1f GB/s, %8.1f TFLOP/s, fraction of their bound %.3f" %
               (kind, which, us, byts / us / 1e3, flops / us / 1e6, b / us))
 
 
