@@ -366,8 +366,11 @@ static hipError_t launch_tile_ks(const ConvArgs &a, const QuantArgs &q, hipStrea
 // (bf16 3x3), W / 5000 (int8) with W = 16 x 16 tiles x steps of four cells; tile = 0.4 + steps per group x 0.23, 0.42, 0.75
 // (int8 0.5, 0.75, 1.35) for one, two, four groups, and 1 for 3x3.  On both sides of the line (traces of whole queries): 2 x
 // 28 x 28 x 176 3x3 10.4 us small, 11.4 tile; 3 x 28 x 28 13.3 and 11.8; 1 x 56 x 56, 208 -> 56 4.8 and 5.4, 208 -> 128
-// 5.8 and 5.3.  Over 500 layers of both precisions the line costs 0.3 % over the better of the two.
+// 5.8 and 5.3.  Over 500 layers of both precisions the line costs 0.3 % over the better of the two.  Of up to 16 filters the
+// tile kernel's 64 are mostly padding; those short reductions run here for any number of pixels (64 x 112 x 112, 16 -> 16 with
+// residual: 22.5 us small, 36 tile; 128 -> 16: 35 and 43; 16 x 56 x 56, 96 -> 16: 4.2 and 6.0).
 bool conv_small_is_faster(const ConvArgs &a, bool i8) {
+    if (!i8 && a.R == 1 && a.K <= 16 && a.C <= 128) return true;
     const double M = (double)a.B * a.P * a.Q;
     const int cells = a.R * a.R * ((a.C + (i8 ? 15 : 7)) / (i8 ? 16 : 8));
     const double work = (double)(long)((M + 15) / 16) * ((a.K + 15) / 16) * ((cells + 3) / 4);
@@ -383,9 +386,13 @@ bool conv_small_is_faster(const ConvArgs &a, bool i8) {
 //   3x3 with stride 2 where its tiles are 128 filters wide and fill whole rounds of the chip, one on each compute unit, to
 //       0.85 and more (96 x 14 x 14 x 720, 222 tiles: 92 us there, 116 here; 61 x 28 x 28 x 360, 282 tiles, 92 against 76; in
 //       tiles of 96 filters, 61 x 56 x 56 x 176, 748 tiles, 81 against 65);
-//   bf16 1x1 of one step, or of two without a residual: all prologue and epilogue (64 x 112 x 112, 16 -> 96: 54 us there,
-//       110 here; 64 x 14 x 14, 80 -> 480: 8.8 against 10.8; with a residual, 16 x 56 x 56, 88 -> 256: 22.3 against 18.5);
-//   1x1 without a residual where its tiles, two on each compute unit, fill rounds to 0.85, in bf16 those of at most 96
+//   bf16 1x1 of at most 128 channels, all prologue and epilogue, without a residual where its tiles pad fewer filters and there
+//       are pixels for several rounds of the chip (64 x 112 x 112, 32 -> 72: 53 us there, 62 here; 16 x 56 x 56, 64 -> 96: 6.7
+//       and 8.0; 16 x 28 x 28, 64 -> 96: 5.3 and 4.4), and those of very many pixels and more than one tile here (64 x 112 x
+//       112, 64 -> 144: 129 and 145).  The rest ran there until the epilogue here took its activation branch once: 16 x 56 x
+//       56, 64 -> 256 with residual 12.9 us here, 19.0 there, 64 x 14 x 14, 80 -> 256 6.8 and 7.6; 61 x 56 x 56, 64 -> 64
+//       12.0 and 14.1;
+//   1x1 of more channels without a residual where its tiles, two on each compute unit, fill rounds to 0.85, in bf16 those of at most 96
 //       filters (96 x 14 x 14, 816 -> 288, 441 tiles: 24 us there, 29 here; 61 x 14 x 14, 816 -> 288, 282 tiles, 21 on both;
 //       in tiles of 128, 96 x 14 x 14, 1024 -> 360, 40 against 37);
 //   1x1 of many pixels where its tiles pad fewer filters (16 x 56 x 56, 256 -> 88: 11.3 us there, 16.1 here).
@@ -398,9 +405,10 @@ static bool tile_is_faster(const ConvArgs &a, bool patch) {
     auto full_rounds = [&](long per_round) { return tiles * 100 >= (tiles + per_round - 1) / per_round * per_round * 85; };
     if (a.R == 3) return a.stride == 1 ? tiles < 128 : pf != 128 || !full_rounds(256);
     if (a.stride != 1) return true;  // (not covered there)
-    if (!I8 && (a.C <= 64 || (a.C <= 128 && !a.res))) return false;
+    const bool pads_fewer = (a.K + 63) / 64 * 64 > (a.K + pf - 1) / pf * pf;
+    if (!I8 && a.C <= 128) return a.res || M <= 32768 || !(pads_fewer || (M > 1l << 19 && a.K > 64));
     if (M <= 32768) return a.res || (!I8 && pf == 128) || !full_rounds(512);
-    return (a.K + 63) / 64 * 64 <= (a.K + pf - 1) / pf * pf;
+    return !pads_fewer;
 }
 
 bool conv_tile_gated_covers(const ConvArgs &a) { return a.R == 1 && tile_covers<false>(a) && tile_gate_cells(a) * 16 <= 24 * 1024; }
