@@ -309,7 +309,7 @@ int sushi_set_subgraph_cache(sushi_ctx *ctx, const sushi_subgraph_cfg *g, size_t
 int sushi_infer(sushi_ctx *ctx, const sushi_subnet_cfg *cfg, const void *input_dev, int batch, void *logits_dev);
 
 /* For callers that must not allocate device memory while they run (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): sushi_infer as exec mode 0 does it (one launch per layer on
+ * serving loops, harnesses that forbid hipMalloc): sushi_infer as exec mode 0 does it (one launch per layer, or few, on
  * the context's stream, float32 or bf16), with the activation buffers of the query in a static device array
  * of the library instead of the context's arena.  Calls no hipMalloc / hipFree and no allocating library
  * routine; same arguments, results and error behaviour as sushi_infer.
@@ -353,7 +353,8 @@ int sushi_sched_record(sushi_ctx *ctx, const int32_t *vec, int *new_cache_idx_ou
 int sushi_get_stats(sushi_ctx *ctx, sushi_stats *out);
 
 typedef enum {
-    SUSHI_OPT_EXEC_MODE = 0,    /* 0 = one launch per layer (default), 1 = replay a HIP graph per SubNet,
+    SUSHI_OPT_EXEC_MODE = 0,    /* 0 = one launch per layer, or per few that
+                                   run fused (default), 1 = replay a HIP graph per SubNet,
                                    2 = stream kernel: one launch per query, layers separated by grid
                                    barriers (bf16 mode only; a barrier wait that runs out is reported
                                    by the next sushi_infer as SUSHI_EDEVICE),
@@ -387,6 +388,7 @@ typedef enum {
                                    patch in LDS (large batches); below four times this many only if the layer's
                                    reduction (input channels x taps) is at least 1024 (int8: 2048) long.  0 = never.
                                    Until it is set: of the layers with at least 3136, those that it runs fastest.
+                                   Once it is set, to any value, every layer is a launch of its own.
                                    In mode 1 it applies to SubNets recorded afterwards */
 } sushi_option;
 int sushi_set_option(sushi_ctx *ctx, int option, int64_t value);
@@ -406,7 +408,7 @@ typedef struct sushi_kernel_stats {
 int sushi_get_kernel_stats(sushi_ctx *ctx, sushi_kernel_stats *out, int cap, int *n_out);
 
 /* One timed launch of exec mode 0 (SUSHI_OPT_KERNEL_TIMING = 1): which op of the query's plan it ran (the order
- * sushi_team_plan lists them in), the kernel family (index into sushi_get_kernel_stats), its duration by HIP
+ * sushi_team_plan lists them in; of a launch that runs several ops the first), the kernel family (index into sushi_get_kernel_stats), its duration by HIP
  * events and its algorithmic bytes and flops.  The library keeps the records of the launches since timing was
  * switched on, at most 65536.  Waits for outstanding timed launches.  Writes min(n, cap) entries. */
 typedef struct sushi_launch_record {

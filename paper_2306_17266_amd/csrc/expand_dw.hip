@@ -17,6 +17,12 @@
 // The expansion is computed again for the halo (1.7 times in all for 14 x 28 outputs of a 7x7 kernel); with 8 to 160 input
 // channels that costs less than writing and reading the map.
 //
+// Both layers with a launch each and here: 64 x 56 x 56, 24 -> 144, 7x7 80 and 50 us (1.3 TB/s of what is left to move), 64 x
+// 28 x 28, 40 -> 240, with the pooling 40 and 28; one image, 56 x 56, 24 -> 144, 8.3 us in two kernels and 8.5 here, but one
+// launch of 3.7 us less.  Not bound by the matrix cores (by count 5 of the 50 us) nor by memory, but by the vector
+// instructions that scale, activate and pack every expanded value, halo included, and by the phases' LDS traffic between
+// barriers; at one image by the prologue (tables, Toeplitz operands, first loads: 4 us).
+//
 // Zero times infinity: an operand's zeros meet values of the same channel only, and sums that are not finite are computed
 // again tap by tap.
 #include "kernels.h"
@@ -401,6 +407,9 @@ static hipError_t launch_xdw_act(const ExpandDwArgs &a, const ExpandDwGeom &g, h
     return a.act == 1 ? launch_xdw_ks<R, S, 1>(a, g, s) : launch_xdw_ks<R, S, 2>(a, g, s);
 }
 
+// From an expansion of 2 on: below, the map that is kept from memory is no larger than input and output, and the halo's products
+// are paid for all the same.  160 channels are five reduction steps, whose operands a wave still holds in registers.  The
+// families' activations (ReLU, hard swish) and kernel sizes only; offsets within 31 bits.
 bool expand_dw_covers(const ExpandDwArgs &a) {
     const long lim = (1l << 31) - 256;
     if ((a.C & 7) || a.C < 8 || a.C > 160 || (a.K & 7) || a.K < 8 || a.K < 2 * a.C || a.act < 1 || a.act > 2) return false;

@@ -9,7 +9,9 @@
 // meet in LDS in a fixed order.
 //
 // Bound by latency: the weights of both layers are requested before the pooled values have arrived (neither depends on
-// them), and by the L2 bandwidth of one compute unit where the hidden layer is large (960 x 240: 460 KB, 3 us).
+// them), and by the L2 bandwidth of one compute unit where the hidden layer is large (960 x 240: 460 KB, 3 us).  672
+// x 168 takes 8.4 us for 64 images and 8.5 for one; two launches and the pass over the map for the gating that it replaces took a
+// query of one image 366 us instead of 337, one of 64 images 1526 instead of 1441.
 #include "kernels.h"
 #include "device_common.h"
 
