@@ -337,15 +337,18 @@ ExpandDwGeom expand_dw_geom(const ExpandDwArgs &a) {
     const int xb = (a.Q + BW - 1) / BW, yb = (a.P + BH - 1) / BH;
     ExpandDwGeom best{};
     double least = 1e30;
-    for (int bx = 1; bx <= std::min(xb, 8); ++bx)
-        for (int by = 1; by <= std::min(yb, 16); ++by)
+    // (A query that meets a SubNet for the first time pays for this search, for each of its blocks: what is of no use ends early.)
+    for (int bx = 1; bx <= std::min(xb, 8); ++bx) {
+        const int tx = (xb + bx - 1) / bx;
+        if (tx > 1 && (xb + tx - 1) / tx != bx) continue;  // (even tiles only)
+        for (int by = 1; by <= std::min(yb, 16) && bx * by <= 32; ++by) {
+            const int ty = (yb + by - 1) / by, nb = bx * by;
+            if (ty > 1 && (yb + ty - 1) / ty != by) continue;
             for (int im = 1; im <= 8; im *= 2) {
+                if (im > 1 && (tx * ty > 1 || nb > 16 || im > a.B)) break;
                 ExpandDwGeom g{};
                 g.bx = bx, g.by = by, g.im = im;
-                g.tx = (xb + bx - 1) / bx, g.ty = (yb + by - 1) / by;
-                if ((g.tx > 1 && (xb + g.tx - 1) / g.tx != bx) || (g.ty > 1 && (yb + g.ty - 1) / g.ty != by)) continue;  // (even tiles only)
-                const int nb = bx * by;
-                if (im > 1 && (g.tx * g.ty > 1 || nb > 16 || im > a.B)) continue;
+                g.tx = tx, g.ty = ty;
                 g.ns = 1;
                 while (g.ns < nb) g.ns *= 2;
                 g.ng = im == 1 ? (nb + 15) / 16 : (im * g.ns + 15) / 16;
@@ -371,6 +374,8 @@ ExpandDwGeom expand_dw_geom(const ExpandDwArgs &a) {
                 const double cost = turns * (1200 + 300 * ((nqp / 4 + 7) / 8) + 1500 * g.ng) + (a.pool && parts > 16 ? 150.0 * (parts - 16) : 0.0);
                 if (cost < least) least = cost, best = g;
             }
+        }
+    }
     ExpandDwGeom &g = best;
     g.dqw = make_fastdiv(g.qw), g.drows = make_fastdiv(g.rows), g.dper = make_fastdiv(g.tx * g.ty), g.dtx = make_fastdiv(g.tx);
     g.dbx = make_fastdiv(g.bx), g.dtw = make_fastdiv(g.bx * BW), g.dth = make_fastdiv(g.by * BH);
