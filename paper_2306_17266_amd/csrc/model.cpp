@@ -407,6 +407,7 @@ int plan_subnet(const SuperNet &sn, const sushi_subnet_cfg &c, int B, Plan &plan
                 int dH = eH, dW = eW;
                 int d = w.conv(e, dH, dW, cmid, cmid, k, stride, act);
                 w.bufs.put(e);
+                const int map = d;
                 if (a.stage_se[s]) {
                     const int red = round_channels(cmid / 4.0);
                     w.gap(d, dH, dW, cmid, 0);
@@ -414,19 +415,20 @@ int plan_subnet(const SuperNet &sn, const sushi_subnet_cfg &c, int B, Plan &plan
                     w.fc(1, red, cmid, SUSHI_ACT_NONE, 2, true, true, true);
                     // The gated map goes to a buffer of its own (the expanded map's, free again): workgroups that
                     // still average d never see gated values, so pooling, both FC layers and the gating can run as
-                    // one op without a barrier between them.
+                    // one op without a barrier between them.  d itself is held until the projection has its output
+                    // buffer: a projection that applies the gates to its operands reads d instead of the gated map.
                     Op g;
                     g.kind = OP_GATE;
                     g.B = B, g.H = dH, g.W = dW, g.C = cmid, g.K = cmid, g.P = dH, g.Q = dW;
                     g.in_buf = d, g.out_buf = w.bufs.get(), g.gate_buf = 2;
                     plan.ops.push_back(g);
-                    w.bufs.put(d);
                     d = g.out_buf;
                 }
                 const bool skip = stride == 1 && C == cout;
                 int oH = dH, oW = dW;
                 int o = w.conv(d, oH, oW, cmid, cout, 1, 1, SUSHI_ACT_NONE, skip ? x : BUF_NONE);
                 w.bufs.put(d), w.bufs.put(x);
+                if (map != d) w.bufs.put(map);
                 x = o, C = cout, H = oH, W = oW;
             }
         }

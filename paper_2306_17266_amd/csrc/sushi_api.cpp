@@ -325,7 +325,8 @@ void *buf_ptr(sushi_ctx *c, const BufBase &bb, int id, bool small) {
 // cp.steps from cp.launches.  A 1x1 expansion and the depthwise layer behind it, with the sums of a pooling behind that: one
 // launch (nobody else reads the expanded map).  A squeeze-excite block (pooling, two fully connected layers, gating, the 1x1 layer behind it):
 // both fully connected layers in one launch, the gating in the 1x1 layer's operand reads.  Nobody else reads the hidden
-// vector or the gated map.
+// vector or the gated map.  A fused launch reads what its FIRST op reads and writes what its last op writes, and its workgroups
+// run in any order: the plan has to keep the two in buffers of their own (plan_subnet holds the depthwise map for the 1x1 layer).
 void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
     cp.steps.clear();
     if (!c->bf16 || c->int8) return;
@@ -347,7 +348,7 @@ void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
         P.conv.x = in[i + 2].pool.x;
         P.quant.gate = S.se.gate;
         P.op = (int)i + 2;
-        return se_gate_covers(S.se) && gated_conv_covers(P.conv);
+        return P.conv.x != P.conv.y && se_gate_covers(S.se) && gated_conv_covers(P.conv);
     };
     for (size_t i = 0; i < in.size(); ++i) {
         if (i + 1 < in.size() && ops[i].kind == OP_CONV && ops[i].r == 1 && ops[i].stride == 1 && ops[i].res_buf == BUF_NONE && !ops[i].in_small &&
@@ -358,7 +359,7 @@ void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
             X.op = (int)i;
             X.in_patch = in[i].in_patch;
             X.xdw = ExpandDwArgs{e.x, d.y, e.w, d.w, e.scale, e.shift, d.scale, d.shift, nullptr, e.B, e.H, e.W, e.C, d.K, d.P, d.Q, d.R, d.stride, e.Kpad, d.Kpad, e.act};
-            if (e.act == d.act && expand_dw_covers(X.xdw)) {
+            if (X.xdw.x != X.xdw.y && e.act == d.act && expand_dw_covers(X.xdw)) {
                 Launch S, P;
                 if (i + 2 < in.size() && ops[i + 2].kind == OP_GAP && ops[i + 2].in_buf == ops[i + 1].out_buf) {
                     // with the pooling's sums, which go where the expanded map would have been

@@ -5,8 +5,10 @@
 //   * dynamic LDS above 64 KiB only after hipFuncSetAttribute has raised the kernel's limit on the current device.
 //
 // The log has one line per launch: device, workgroups, threads per workgroup, bytes of dynamic LDS, mangled kernel name.
+// A second log says which activations a launch of the per-layer kernels reads and writes, from its arguments: the kernel's name,
+// then r or w, address and bytes of each.
 #define __HIP_PLATFORM_AMD__ 1
-#include <hip/hip_runtime_api.h>
+#include "../paper_2306_17266_amd/csrc/kernels.h"
 #include <sys/mman.h>
 
 #include <cstdio>
@@ -24,6 +26,8 @@ std::map<std::pair<int, const void *>, size_t> lds_limit;
 std::map<std::pair<int, std::string>, void *> symbols;
 std::map<const void *, std::pair<std::string, size_t>> vars;
 std::string log_text;
+std::string memory_text;
+int element_bytes = 2;
 int fail_attributes = 0;
 thread_local int device = 0;
 thread_local hipError_t last = hipSuccess;
@@ -44,6 +48,42 @@ void *take(size_t n) {
     blocks[p] = n ? n : 1;
     return p;
 }
+void log_memory(const std::string &name, void **args) {
+    using namespace sushi;
+    std::string line = name;
+    auto add = [&](char how, const void *p, long bytes) {
+        char text[64];
+        std::snprintf(text, sizeof(text), " %c %llu %ld", how, (unsigned long long)p, bytes);
+        if (p) line += text;
+    };
+    auto has = [&](const char *type) { return name.find(type) != std::string::npos; };
+    const long es = element_bytes;
+    if (has("8ConvArgs")) {
+        const ConvArgs &a = *static_cast<const ConvArgs *>(args[0]);
+        const long out = (long)a.B * a.P * a.Q * a.K;
+        const bool sums = has("12fc_i8_kernel");  // (reads the pooling's 32-bit sums, writes float32)
+        add('r', a.x, (long)a.B * a.H * a.W * a.C * (a.in_f32 || sums ? 4 : es));
+        add('r', a.res, out * es);
+        add('w', a.y, out * (a.out_f32 || sums ? 4 : es));
+        if (has("17conv_small_kernel") || has("16conv_tile_kernel")) add('r', static_cast<const QuantArgs *>(args[2])->gate, (long)a.B * a.C * 4);
+    } else if (has("8PoolArgs")) {
+        const PoolArgs &a = *static_cast<const PoolArgs *>(args[0]);
+        const bool vec = has("10gap_kernel") || has("13gap_i8_kernel");
+        add('r', a.x, (long)a.B * a.H * a.W * a.C * es);
+        add('r', a.gate, (long)a.B * a.C * 4);
+        add('w', a.y, vec ? (long)a.B * a.C * 4 : (long)a.B * a.P * a.Q * a.C * es);
+    } else if (has("12ExpandDwArgs")) {
+        const ExpandDwArgs &a = *static_cast<const ExpandDwArgs *>(args[0]);
+        add('r', a.x, (long)a.B * a.H * a.W * a.C * 2);
+        add('w', a.y, (long)a.B * a.P * a.Q * a.K * 2);
+        add('w', a.pool, (long)a.B * a.K * static_cast<const ExpandDwGeom *>(args[1])->parts * 4);
+    } else if (has("10SeGateArgs")) {
+        const SeGateArgs &a = *static_cast<const SeGateArgs *>(args[0]);
+        add('r', a.pooled, (long)a.B * a.parts * a.C * 4);
+        add('w', a.gate, (long)a.B * a.C * 4);
+    }
+    memory_text += line + "\n";
+}
 void give(void *p) {
     std::lock_guard<std::mutex> g(mu);
     auto it = blocks.find(p);
@@ -56,7 +96,9 @@ void give(void *p) {
 extern "C" {
 // ---- controls of the tests
 const char *fake_log() { return log_text.c_str(); }
-void fake_clear_log() { log_text.clear(); }
+const char *fake_memory_log() { return memory_text.c_str(); }
+void fake_clear_log() { log_text.clear(), memory_text.clear(); }
+void fake_element_bytes(int n) { element_bytes = n; }  // of the activations, for the second log
 void fake_fail_attributes(int n) { fail_attributes = n; }  // the next n calls of hipFuncSetAttribute fail
 
 // ---- what the compiler's host code calls
@@ -75,7 +117,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
     *grid = config.grid, *block = config.block, *lds = config.lds, *s = config.stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t lds, hipStream_t) {
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t) {
     const unsigned long long lim = 1ull << 32;
     if (!g.x || !g.y || !g.z || !b.x || !b.y || !b.z || (unsigned long long)b.x * b.y * b.z > 1024) return ret(hipErrorInvalidConfiguration);
     if ((unsigned long long)g.x * b.x >= lim || (unsigned long long)g.y * b.y >= lim || (unsigned long long)g.z * b.z >= lim)
@@ -88,6 +130,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t lds, h
     char line[128];
     std::snprintf(line, sizeof(line), "%d %llu %u %zu ", device, (unsigned long long)g.x * g.y * g.z, b.x * b.y * b.z, lds);
     log_text += line + names[f] + "\n";
+    log_memory(names[f], args);
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int value) {
@@ -133,15 +176,16 @@ hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 0.f, hipSuccess; }
+// (a capture's launches are logged as they are recorded; replays do nothing)
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *g) { return *g = reinterpret_cast<hipGraph_t>(&device), hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t, hipGraphNode_t *, char *, size_t) { return *x = reinterpret_cast<hipGraphExec_t>(&device), hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
 // (not called by what the tests run; the loader asks for them)
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return ret(hipErrorNotSupported); }
 hipError_t hipStreamQuery(hipStream_t) { return ret(hipErrorNotSupported); }
 hipError_t hipMemsetAsync(void *, int, size_t, hipStream_t) { return ret(hipErrorNotSupported); }
-hipError_t hipGraphDestroy(hipGraph_t) { return ret(hipErrorNotSupported); }
-hipError_t hipGraphExecDestroy(hipGraphExec_t) { return ret(hipErrorNotSupported); }
-hipError_t hipGraphInstantiate(hipGraphExec_t *, hipGraph_t, hipGraphNode_t *, char *, size_t) { return ret(hipErrorNotSupported); }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return ret(hipErrorNotSupported); }
-hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *) { return ret(hipErrorNotSupported); }
 hipError_t hipGetDevicePropertiesR0600(hipDeviceProp_tR0600 *, int) { return ret(hipErrorNotSupported); }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *, const void *, int, size_t) { return ret(hipErrorNotSupported); }
 }

@@ -18,7 +18,7 @@ from paper_2306_17266_amd import binding
 from workloads import arch as A
 from workloads import tensors as T
 fake = ctypes.CDLL("libamdhip64.so.7")
-fake.fake_log.restype = ctypes.c_char_p
+fake.fake_log.restype = fake.fake_memory_log.restype = ctypes.c_char_p
 
 
 def context(arch, dtype="bf16", device=0):
@@ -33,6 +33,13 @@ def context(arch, dtype="bf16", device=0):
     return ctx
 
 
+def kernel_name(mangled):
+    """(the kernel's name, what stands behind it)"""
+    at = next(m for m in re.finditer(r"(?<!\\d)\\d+", mangled) if mangled[m.end():m.end() + int(m.group())].endswith("_kernel"))
+    end = at.end() + int(at.group())
+    return mangled[at.end():end], mangled[end:]
+
+
 def infer(ctx, cfg, batch):
     """One query; its launches as (kernel, template arguments, workgroups, threads per workgroup, bytes of dynamic LDS)."""
     fake.fake_clear_log()
@@ -40,10 +47,22 @@ def infer(ctx, cfg, batch):
     out = []
     for line in fake.fake_log().decode().splitlines():
         _, wgs, threads, lds, name = line.split()
-        at = next(m for m in re.finditer(r"(?<!\\d)\\d+", name) if name[m.end():m.end() + int(m.group())].endswith("_kernel"))
-        end = at.end() + int(at.group())
-        args = [int(v) for v in re.findall(r"L(?:[ib]|NS_\\w+?E)(\\d+)E", name[end:])]
-        out.append((name[at.end():end], args, int(wgs), int(threads), int(lds)))
+        short, rest = kernel_name(name)
+        args = [int(v) for v in re.findall(r"L(?:[ib]|NS_\\w+?E)(\\d+)E", rest)]
+        out.append((short, args, int(wgs), int(threads), int(lds)))
+    return out
+
+
+def memory(dtype, query):
+    """query() and the activations that its launches read and write: [(kernel, reads, writes)], each a list of (address, bytes)."""
+    fake.fake_element_bytes({"fp32": 4, "bf16": 2, "int8": 1}[dtype])
+    fake.fake_clear_log()
+    query()
+    out = []
+    for line in fake.fake_memory_log().decode().splitlines():
+        name, *rest = line.split()
+        ranges = [(how, int(at), int(n)) for how, at, n in zip(rest[::3], rest[1::3], rest[2::3])]
+        out.append((kernel_name(name)[0], [r[1:] for r in ranges if r[0] == "r"], [r[1:] for r in ranges if r[0] == "w"]))
     return out
 
 

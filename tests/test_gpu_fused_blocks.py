@@ -58,9 +58,10 @@ def _check(arch, batch, kernels, seed=83):
 
 # (expand, width, resolution, batch): hidden vectors of less than a filter tile, of one and of several with a ragged last one;
 # 8 gates and more than a chunk's; inputs that end inside a reduction step (24, 72, 144); maps of one pixel and of more than a
-# tile of the 1x1 layer; one image per workgroup, eight and a ragged last group
+# tile of the 1x1 layer; one image per workgroup, eight and a ragged last group; a gated 1x1 layer of more workgroups (1176) than
+# the chip holds at once (1024), so that some start after others have stored
 @pytest.mark.parametrize("expand,width,res,batch", [(1, 8, 8, 1), (3, 24, 14, 3), (6, 24, 34, 2), (6, 120, 8, 5), (1, 136, 8, 300), (3, 72, 8, 130),
-                                                    (6, 160, 12, 64), (6, 24, 62, 9)])
+                                                    (6, 160, 12, 64), (6, 24, 62, 9), (6, 40, 56, 96)])
 def test_squeeze_excite(expand, width, res, batch):
     _check(block_net(expand, 3, (2, 2) if res == 8 else (1, 2), A.ACT_HSWISH, res, width), batch, {"se_gate_kernel"})
 

@@ -1,6 +1,7 @@
 """The library's launches, seen from the host: limits of a launch, per-device state, which kernel serves which layer.  No GPU:
 the library runs on tests/fake_hip.cpp."""
 from tests.fake_hip import run
+from workloads import arch as A
 
 
 def test_large_lds_on_every_device_and_after_a_failure(tmp_path):
@@ -112,3 +113,73 @@ print(repr(seen))
                                             (7, 2, 1, 7), (7, 2, 4, 3))}
     assert seen["dw"] >= want and {(k, v[:2]) for k, v in seen["dw"]} >= {("dwconv_rows_kernel", (r, s)) for r in (3, 5, 7) for s in (1, 2)}, seen["dw"]
     assert seen["stem"] == {("stem_mfma_kernel", v, s) for v in ((1, 1), (1, 4), (2, 1), (2, 4)) for s in (1, 2)} | {("conv_direct_kernel", (), s) for s in (1, 2)}, seen["stem"]
+
+
+def test_launches_do_not_write_what_they_read(tmp_path):
+    """No launch writes memory that it reads (its workgroups run in any order), and what a launch reads is whole what one launch
+    before it wrote and none has touched since: layer by layer and with layers fused, in the arena and in the static array,
+    launched and recorded as a graph."""
+    out = run(tmp_path, '''
+from workloads import streams
+from workloads.rng import Stream
+SELF = 4096  # (where infer's caller keeps its image and its logits)
+
+
+def overlap(a, b):
+    return a[0] < b[0] + b[1] and b[0] < a[0] + a[1]
+
+
+def faults(launches):
+    found, written = [], []  # (of the memory written so far, what still holds)
+    for i, (name, reads, writes) in enumerate(launches):
+        for w in writes:
+            found += [(i, name, "writes what it reads") for r in reads if overlap(r, w)]
+            found += [(i, name, "writes twice") for v in writes if v is not w and overlap(v, w)]
+        found += [(i, name, "reads what is not there") for r in reads if r[0] != SELF and r not in written]
+        written = [v for v in written if not any(overlap(v, w) for w in writes)] + writes
+    return found
+
+
+p = ctypes.c_void_p(SELF)
+seen = {}
+for arch, dtype in ((A.mbv3_arch(), "bf16"), (A.resnet_arch(), "bf16"), (A.resnet_arch(), "int8"), (A.mbv3_arch(), "fp32"), (A.tiny_arch(), "fp32")):
+    ctx = context(arch, dtype)
+    nets = [A.min_cfg(arch), A.max_cfg(arch)] + [streams.uniform_cfg(arch, Stream(n), max(arch.res_choices)) for n in (3, 7)]
+    for option in (None, 0) if dtype == "bf16" else (None,):  # (once the threshold is set every layer is a launch of its own)
+        if option is not None:
+            ctx.sushi_set_option(S.OPT_PATCH_CONV_MIN_PIXELS, option)
+        for mode in (0, 1, "static"):
+            if dtype == "int8" and mode == 1:
+                continue
+            if mode != "static":
+                ctx.sushi_set_option(S.OPT_EXEC_MODE, mode)
+            for k, cfg in enumerate(nets):
+                for batch in (1, 5, 96):
+                    c = ctx.marshal_cfg(cfg)
+                    if mode == "static":
+                        query = lambda: binding.lib().sushi_infer_static(ctx._h, ctypes.byref(c), p, batch, p) in (0, -2) or sys.exit("static")
+                    else:
+                        query = lambda: ctx.infer_marshalled(c, p, batch, p)
+                    launches = memory(dtype, query)
+                    for name, _, _ in launches:
+                        seen[name, mode] = seen.get((name, mode), 0) + 1
+                    bad = faults(launches)
+                    if bad:
+                        print(arch.family, dtype, option, mode, k, batch, len(bad), bad[0])
+    ctx.close()
+for name in ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel"):
+    print(name, min(seen.get((name, mode), 0) for mode in (0, 1)) > 30, seen.get((name, "static"), 0) > 0 or name == "conv_patch_kernel")
+''')
+    names = ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel")
+    assert out.splitlines() == [name + " True True" for name in names], out
+
+
+def test_gated_layer_of_the_gpu_tests_exceeds_one_round_of_the_chip(tmp_path):
+    """A net of test_gpu_fused_blocks.py has a gated 1x1 layer with more workgroups than run at once (1024: four of 256 threads
+    and 35 KB of LDS on each of 256 compute units)."""
+    from tests import test_gpu_fused_blocks as t
+    out = run(tmp_path, '''
+arch, batch = DATA
+print(max(k[2] for k in infer(context(arch), A.max_cfg(arch), batch) if k[0] == "conv_tile_kernel" and k[1][-1] == 1))
+''', (t.block_net(6, 3, (1, 2), A.ACT_HSWISH, 56, 40), 96))
+    assert int(out) > 1024, out
