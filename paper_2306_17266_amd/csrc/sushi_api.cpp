@@ -41,7 +41,8 @@ struct Launch {
 struct CachedPlan {
     Plan plan;
     std::vector<Launch> launches;  // one per op
-    std::vector<Launch> steps;     // the same with ops fused (bf16 mode); exec modes 0 and 1 run these
+    std::vector<Launch> steps;     // the same with ops fused (bf16 mode), empty: nothing to fuse; exec modes 0 and 1 run these
+    bool steps_made = false;       // by the first query that runs them: the other modes do without the tile searches
     uint64_t weight_bytes = 0;
     double alg_bytes = 0.0, alg_flops = 0.0;  // algorithmic traffic and arithmetic of the whole query
     double vec_norm2 = 0.0;           // sum K^2 + C^2 over layers
@@ -328,7 +329,7 @@ void *buf_ptr(sushi_ctx *c, const BufBase &bb, int id, bool small) {
 // vector or the gated map.  A fused launch reads what its FIRST op reads and writes what its last op writes, and its workgroups
 // run in any order: the plan has to keep the two in buffers of their own (plan_subnet holds the depthwise map for the 1x1 layer).
 void fuse_steps(const sushi_ctx *c, CachedPlan &cp) {
-    cp.steps.clear();
+    cp.steps_made = true;
     if (!c->bf16 || c->int8) return;
     const std::vector<Launch> &in = cp.launches;
     const std::vector<Op> &ops = cp.plan.ops;
@@ -446,7 +447,6 @@ void bind_plan(sushi_ctx *c, CachedPlan &cp, const BufBase &bb = BufBase()) {
         }
         cp.launches.push_back(L);
     }
-    fuse_steps(c, cp);
     cp.weight_bytes = 0;
     cp.vec_norm2 = 0.0;
     for (const sushi_layer_dims &d : cp.plan.dims) {
@@ -536,8 +536,9 @@ hipError_t drain_timing(sushi_ctx *c) {
 hipError_t issue_launches(sushi_ctx *c, CachedPlan &cp, const void *input_dev, void *logits_dev, hipStream_t st) {
     const bool timed = c->timing && st == c->stream;
     hipError_t e = hipSuccess;
-    // (a patch threshold set by the caller is about single layers)
-    for (const Launch &L : c->patch_min_pixels == PATCH_AUTO && !cp.steps.empty() ? cp.steps : cp.launches) {
+    const bool fused = c->patch_min_pixels == PATCH_AUTO;  // (a patch threshold set by the caller is about single layers)
+    if (fused && !cp.steps_made) fuse_steps(c, cp);
+    for (const Launch &L : fused && !cp.steps.empty() ? cp.steps : cp.launches) {
         sushi_ctx::Pending pend{};
         pend.op_index = L.op;
         if (timed) {

@@ -1,6 +1,8 @@
 """The library's launches, seen from the host: limits of a launch, per-device state, which kernel serves which layer.  No GPU:
 the library runs on tests/fake_hip.cpp."""
-from tests.fake_hip import run
+import subprocess
+
+from tests.fake_hip import ROOT, run
 from workloads import arch as A
 
 
@@ -172,6 +174,48 @@ for name in ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_ke
 ''')
     names = ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel")
     assert out.splitlines() == [name + " True True" for name in names], out
+
+
+COUNT_SEARCHES = '''
+#define __HIP_PLATFORM_AMD__ 1
+#include "%s/paper_2306_17266_amd/csrc/kernels.h"
+static int calls = 0;
+extern "C" int searches() { return calls; }
+sushi::ExpandDwGeom sushi::expand_dw_geom(const ExpandDwArgs &) {  // (in place of the library's)
+    ExpandDwGeom g{};
+    g.total = g.workers = g.groups = g.parts = 1;
+    return ++calls, g;
+}
+'''
+
+
+def test_tile_search_only_where_layers_run_fused(tmp_path):
+    """The search for an expansion's tile costs a new SubNet's first query some microseconds per block: only queries that launch
+    fused layers make it, not those of the persistent kernels or of a caller's threshold, which never launch one."""
+    src, lib = str(tmp_path / "count.cpp"), str(tmp_path / "libcount.so")
+    with open(src, "w") as f:
+        f.write(COUNT_SEARCHES % ROOT)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-w", "-I/opt/rocm/include", src, "-o", lib], check=True)
+    out = run(tmp_path, '''
+count = ctypes.CDLL(DATA, mode=ctypes.RTLD_GLOBAL)  # (before the library is loaded)
+arch = A.mbv3_arch()
+for option, value in ((S.OPT_EXEC_MODE, 2), (S.OPT_EXEC_MODE, 3), (S.OPT_PATCH_CONV_MIN_PIXELS, 0), (S.OPT_EXEC_MODE, 1), (S.OPT_EXEC_MODE, 0)):
+    ctx = context(arch)
+    ctx.sushi_set_option(option, value)
+    before = count.searches()
+    try:
+        infer(ctx, A.max_cfg(arch), 1)
+    except S.SushiError:
+        pass  # (the stand-in cannot run a persistent kernel; the plan was made)
+    first = count.searches()
+    if option == S.OPT_PATCH_CONV_MIN_PIXELS or value < 2:
+        infer(ctx, A.max_cfg(arch), 1)
+    print(first - before, count.searches() - first)
+    ctx.close()
+''', lib)
+    first = [line.split()[0] for line in out.splitlines()]
+    assert first[:3] == ["0"] * 3 and first[3] == first[4] and int(first[4]) > 10, out
+    assert all(line.split()[1] == "0" for line in out.splitlines()), out
 
 
 def test_gated_layer_of_the_gpu_tests_exceeds_one_round_of_the_chip(tmp_path):
