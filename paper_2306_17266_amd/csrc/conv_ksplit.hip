@@ -1,6 +1,6 @@
-// 3x3 convolution with stride 1 and at least 112 input channels on the matrix cores, bf16 and int8: the tile kernel's second form,
-// in which the four waves of a workgroup split the REDUCTION, so that every weight operand is loaded by one wave only, from
-// memory straight into registers, the input is copied once for all nine taps, and one barrier is passed per nine steps.
+// 3x3 convolution with stride 1 and at least 112 input channels on the matrix cores, bf16 and int8.  The four waves of a workgroup
+// split the REDUCTION, so that every weight operand is loaded by one wave only, from memory straight into registers, the input is
+// copied once for all nine taps, and one barrier is passed per nine steps.
 //
 // A workgroup computes 32 FT filters x 32 PT consecutive output pixels; every wave holds all FT x PT accumulators (32x32x16_bf16,
 // 32x32x32_i8).  The input is addressed in a frame around the image (padded coordinates, see conv_patch.hip), so that a tile
@@ -39,11 +39,8 @@ struct KsplitGeom {
 constexpr int KSPLIT_LOADS = 7;                    // cells of a chunk that a thread copies
 constexpr int KSPLIT_POSITIONS = KSPLIT_LOADS * 32;  // that a tile may need
 
-// (the arguments that the tile kernel's forms have in common come first: waves or wave groups that split the reduction, taps per
-// side, int8)
-template <int WAVES, int R, bool I8, int FT, int PT>
-__global__ __launch_bounds__(64 * WAVES, 2) void conv_tile_kernel(ConvArgs a, KsplitGeom g, QuantArgs q) {
-    static_assert(WAVES == 4 && R == 3, "four pairs of cells in a chunk; a ring of three steps, nine steps per chunk");
+template <bool I8, int FT, int PT>
+__global__ __launch_bounds__(256, 2) void conv_ksplit_kernel(ConvArgs a, KsplitGeom g, QuantArgs q) {
     constexpr int ES = I8 ? 1 : 2, CPC = 16 / ES;  // bytes per element, channels per cell
     constexpr int BN = 32 * FT, BM = 32 * PT, CC = 8, NLD = KSPLIT_LOADS, STEPS = 9, D = 3;
     constexpr int PROW = BN / 4 + 1;               // 16-byte cells per pixel row of a partial tile
@@ -58,7 +55,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void conv_tile_kernel(ConvArgs a, Ks
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, (int)((long)a.B * a.H * a.W * a.C * ES), 0x00020000);
     const __amdgpu_buffer_rsrc_t rw =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)((long)R * R * a.CG * a.Kpad * 16), 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.w), 0, (int)(9l * a.CG * a.Kpad * 16), 0x00020000);
     auto frame = [&](int m) {  // position of output pixel m's first tap
         const int t = fdiv(m, g.dq), qq = m - t * a.Q, n = fdiv(t, g.dp), p = t - n * a.P;
         return (n * g.hp + p) * g.wp + qq;
@@ -289,7 +286,7 @@ static hipError_t launch_ksplit_tile(const ConvArgs &a, const QuantArgs &q, hipS
     g.dq = make_fastdiv(a.Q), g.dp = make_fastdiv(a.P), g.dwp = make_fastdiv(g.wp), g.dhp = make_fastdiv(g.hp);
     const size_t lds = ((size_t)g.part + 3 * (BN / 4)) * 16;  // (less than 64 KiB)
     const int per_xcd = (int)(((long)g.tiles_m * g.tiles_f + 7) / 8);
-    hipLaunchKernelGGL((conv_tile_kernel<4, 3, I8, FT, PT>), dim3(per_xcd * 8), dim3(256), lds, s, a, g, q);
+    hipLaunchKernelGGL((conv_ksplit_kernel<I8, FT, PT>), dim3(per_xcd * 8), dim3(256), lds, s, a, g, q);
     return hipGetLastError();
 }
 

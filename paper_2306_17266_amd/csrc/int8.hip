@@ -195,7 +195,7 @@ hipError_t launch_conv_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, 
         return e;
     };
     hipError_t e = chosen && patch ? picked(launch_conv_patch_i8(a, q, s), KC_CONV_PATCH) : hipErrorNotSupported;
-    if (e == hipErrorNotSupported) e = picked(launch_conv_ksplit_i8(a, q, s, patch && !chosen), KC_CONV_TILE);
+    if (e == hipErrorNotSupported) e = picked(launch_conv_ksplit_i8(a, q, s, patch && !chosen), KC_CONV_KSPLIT);
     if (e == hipErrorNotSupported && conv_small_is_faster(a, true)) e = picked(launch_conv_small_i8(a, q, s), KC_CONV_SMALL);
     if (e == hipErrorNotSupported) e = picked(launch_conv_tile_i8(a, q, s, patch && !chosen), KC_CONV_TILE);
     if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch_i8(a, q, s), KC_CONV_PATCH);

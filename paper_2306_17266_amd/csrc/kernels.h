@@ -169,7 +169,8 @@ enum KernelClass {
     KC_DW = 15,         // dwconv_kernel (depthwise: float32, and tensors of 2 GiB and more)
     KC_SE_GATE = 16,    // se_gate_kernel (both fully connected layers of a squeeze-excite block)
     KC_EXPAND_DW = 17,  // expand_dw_kernel (1x1 expansion and depthwise layer)
-    KC_COUNT = 18
+    KC_CONV_KSPLIT = 18,  // conv_ksplit_kernel (3x3, the reduction split over the waves of a workgroup)
+    KC_COUNT = 19
 };
 const char *kernel_class_name(int kc);
 
@@ -199,8 +200,8 @@ hipError_t launch_conv_tile(const ConvArgs &a, hipStream_t s, bool patch, const 
 bool conv_tile_gated_covers(const ConvArgs &a);
 hipError_t launch_conv_tile_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
 
-// 3x3 with stride 1 and long reductions: the tile kernel's form with a reduction split over waves (conv_ksplit.hip); patch as
-// above.  Returns hipErrorNotSupported (nothing launched) for any other case and where another kernel is the faster one.
+// 3x3 with stride 1 and long reductions, which the waves of a workgroup split (conv_ksplit.hip); patch as above.  Returns
+// hipErrorNotSupported (nothing launched) for any other case and where another kernel is the faster one.
 hipError_t launch_conv_ksplit(const ConvArgs &a, hipStream_t s, bool patch);
 hipError_t launch_conv_ksplit_i8(const ConvArgs &a, const QuantArgs &q, hipStream_t s, bool patch);
 

@@ -491,7 +491,8 @@ const char *kernel_class_name(int kc) {
                                           "gate_kernel",        "sushi_stream_kernel", "sushi_team_kernel",
                                           "conv_patch_kernel",  "conv_i8_direct_kernel", "int8_pool_fc_kernels",
                                           "stem_mfma_kernel",   "conv_tile_kernel",    "dw_mfma_kernel",
-                                          "dwconv_kernel",      "se_gate_kernel",     "expand_dw_kernel"};
+                                          "dwconv_kernel",      "se_gate_kernel",     "expand_dw_kernel",
+                                          "conv_ksplit_kernel"};
     return kc >= 0 && kc < KC_COUNT ? names[kc] : "?";
 }
 
@@ -548,7 +549,7 @@ hipError_t launch_conv(const ConvArgs &a, bool bf16, hipStream_t s, int *kc, lon
         return e;
     };
     hipError_t e = chosen && patch ? picked(launch_conv_patch(a, s), KC_CONV_PATCH) : hipErrorNotSupported;
-    if (e == hipErrorNotSupported) e = picked(launch_conv_ksplit(a, s, patch && !chosen), KC_CONV_TILE);
+    if (e == hipErrorNotSupported) e = picked(launch_conv_ksplit(a, s, patch && !chosen), KC_CONV_KSPLIT);
     if (e == hipErrorNotSupported && conv_small_is_faster(a, false)) e = picked(launch_conv_small(a, s), KC_CONV_SMALL);
     if (e == hipErrorNotSupported) e = picked(launch_conv_tile(a, s, patch && !chosen), KC_CONV_TILE);
     if (e == hipErrorNotSupported && patch && !chosen) e = picked(launch_conv_patch(a, s), KC_CONV_PATCH);

@@ -156,7 +156,7 @@ def report_from_trace(args, arch, cfg, batch):
 
     ops = plan_ops(arch, cfg, batch)
     mine = ("conv_i8_direct_kernel", "maxpool_i8_kernel", "gap_i8_kernel", "fc_i8_kernel",
-            "conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel", "conv_tile_kernel", "stem_mfma_kernel", "dw_mfma_kernel", "conv_patch_kernel", "dwconv_kernel",
+            "conv_direct_kernel", "conv_mfma_kernel", "conv_small_kernel", "conv_tile_kernel", "conv_ksplit_kernel", "stem_mfma_kernel", "dw_mfma_kernel", "conv_patch_kernel", "dwconv_kernel",
             "dwconv_rows_kernel", "maxpool_kernel", "gap_kernel", "gate_kernel", "expand_dw_kernel", "se_gate_kernel")
     rows = []
     for r in csv.DictReader(open(args.from_trace)):

@@ -1,4 +1,4 @@
-"""The tile kernel's form whose waves split the reduction (3x3, 112 channels and more), through small nets against the CPU oracle
+"""conv_ksplit_kernel, whose waves split the reduction (3x3, 112 channels and more), through small nets against the CPU oracle
 (bf16) and bit for bit against the integer oracle (int8); and which of its tile shapes the nets reach, on the CPU."""
 import pytest
 
@@ -23,7 +23,7 @@ def test_nets_reach_every_tile_shape(tmp_path):
 for dtype in ("bf16", "int8"):
     seen = set()
     for arch, batch in DATA:
-        seen |= {tuple(k[1][3:]) for o, k in layers(arch, dtype, batch) if k[0] == "conv_tile_kernel" and len(k[1]) == 5}
+        seen |= {tuple(k[1][1:]) for o, k in layers(arch, dtype, batch) if k[0] == "conv_ksplit_kernel"}
     print(sorted(seen))
 ''', NETS)
     assert out.splitlines() == [str([(1, 1), (1, 2), (2, 2), (2, 4), (3, 2)])] * 2, out

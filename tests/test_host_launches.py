@@ -106,7 +106,7 @@ print(repr(seen))
     seen = eval(out)
     # (wave groups, taps per side, stride, residual)
     tile = {(1, 1, 1, 0), (1, 1, 1, 1), (1, 1, 2, 0), (2, 1, 1, 0), (2, 1, 1, 1), (2, 1, 2, 0), (1, 3, 1, 0), (1, 3, 2, 0), (2, 3, 1, 0), (2, 3, 2, 0),
-            (4, 3, 1, 0), (4, 3, 2, 0)}
+            (4, 3, 2, 0)}  # (long 3x3 reductions with stride 1 run in conv_ksplit_kernel: test_gpu_split_reduction.py)
     assert seen["bf16"][0] >= tile and seen["int8"][0] >= tile | {(4, 1, 1, 0)}, seen
     for dtype in ("bf16", "int8", "fp32"):
         small = seen[dtype][1]
@@ -169,10 +169,10 @@ for arch, dtype in ((A.mbv3_arch(), "bf16"), (A.resnet_arch(), "bf16"), (A.resne
                     if bad:
                         print(arch.family, dtype, option, mode, k, batch, len(bad), bad[0])
     ctx.close()
-for name in ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel"):
-    print(name, min(seen.get((name, mode), 0) for mode in (0, 1)) > 30, seen.get((name, "static"), 0) > 0 or name == "conv_patch_kernel")
+for name in ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel", "conv_ksplit_kernel"):
+    print(name, min(seen.get((name, mode), 0) for mode in (0, 1)) > 30, seen.get((name, "static"), 0) > 0 or name in ("conv_patch_kernel", "conv_ksplit_kernel"))
 ''')
-    names = ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel")
+    names = ("expand_dw_kernel", "se_gate_kernel", "gate_kernel", "conv_patch_kernel", "conv_small_kernel", "conv_tile_kernel", "conv_ksplit_kernel")
     assert out.splitlines() == [name + " True True" for name in names], out
 
 
