@@ -1,4 +1,4 @@
-// 3x3 convolution with stride 1 and at least 112 input channels on the matrix cores, bf16 and int8.  The four waves of a workgroup
+// 3x3 convolution with stride 1 and at least 96 (int8: 120) input channels on the matrix cores, bf16 and int8.  The four waves of a workgroup
 // split the REDUCTION, so that every weight operand is loaded by one wave only, from memory straight into registers, the input is
 // copied once for all nine taps, and one barrier is passed per nine steps.
 //
@@ -290,13 +290,15 @@ static hipError_t launch_ksplit_tile(const ConvArgs &a, const QuantArgs &q, hipS
     return hipGetLastError();
 }
 
-// From 112 channels on: with fewer, the second of two chunks is mostly empty and the 64 x 64 tiles of conv_tile.hip or the patch kernel
-// are as fast or faster (32 x 28 x 28 x 88 13.1 us here, 12.7 there; of 104 channels some gain, 16 x 28 x 28 9.5 against 11.5, some
-// lose, 61 x 28 x 28 23.9 against 20.1: they stay, as the layer that the tests hold to the 64 x 64 form does).
+// From 96 channels on, int8 from 120 (eight cells, a whole chunk): below, the last chunk is half empty or more, and the gain over the
+// other kernels goes.  By the rule below over 48 square layers of each width (7 x 7 to 56 x 56, 1 to 96 images, warm), us without
+// and with this kernel, and how many layers get slower by 3 % and more: bf16 80 channels 544 / 534, 88 570 / 553, 1 (24 x 28 x 28
+// 11.6 / 12.2), 96 577 / 554, 0, 104 737 / 710, 0 (16 x 28 x 28 11.4 / 9.7), 128 799 / 737, 0; int8 96 533 / 528, 1, 104 and 112
+// 595 / 591, 5 (12 x 28 x 28 9.2 / 11.1), 120 630 / 614, 1, 128 640 / 620, 1.
 template <bool I8>
 static bool ksplit_covers(const ConvArgs &a) {
     const int es = I8 ? 1 : 2;
-    if (a.in_f32 || a.out_f32 || (a.C & 7) || a.C < 112 || (a.K & 7) || a.K < 8) return false;
+    if (a.in_f32 || a.out_f32 || (a.C & 7) || a.C < (I8 ? 120 : 96) || (a.K & 7) || a.K < 8) return false;
     if (a.R != 3 || a.pad != 1 || a.stride != 1 || a.Rmax != 3) return false;
     const long M = (long)a.B * a.P * a.Q, lim = (1l << 31) - 4096;
     return M * a.K * es < lim && (long)a.B * a.H * a.W * a.C * es < lim && 9l * a.CG * a.Kpad * 16 < (1l << 30) &&

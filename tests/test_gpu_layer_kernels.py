@@ -258,7 +258,7 @@ def _check_dense(arch, batch, int8):
 # channel counts that are no multiple of a cell of 16, reductions of one step and of 33 (the last net: a 1x1 in four groups)
 TILED = [(_bottleneck([136, 1040], [1, 2], 112, 0.2), 9), (_bottleneck([136, 1040], [1, 2], 60, 0.6), 9), (_chain([8, 264, 40], 29), 6),
          (_bottleneck([520, 264], [1, 2], 112, 0.2), 9), (_bottleneck([680], [2], 112, 0.2), 57), (_bottleneck([2056], [1], 60, 0.1), 7),
-         (_bottleneck([200, 328], [1, 2], 112, 0.2), 9)]
+         (_bottleneck([200, 328], [1, 2], 112, 0.2), 9), (_chain([8, 88, 88], 29), 6)]
 
 
 @pytest.mark.parametrize("arch,batch", TILED)
