@@ -453,6 +453,13 @@ int patch_positions(const ConvArgs &a, int BM) {
     return (int)best;
 }
 
+// Filters fast (bf16, 1x1)?  The layers of whole queries (7 x 7 to 56 x 56, 4 to 96 images), us with pixels fast and with filters fast:
+// from 16384 pixels on better by 1.10 in all (24 x 28 x 28, 512 -> 288 16.3 and 14.2; 96 x 14 x 14, 816 -> 576 42.6 and 35.8; 61 x 56 x 56,
+// 256 -> 176 58.4 and 47.1; at worst 39.8 and 40.8), with less 0.94 to 1.23 and mostly even.  Short reductions without a residual
+// only from 100000 pixels on: 64 -> 256 at 16 x 56 x 56 15.1 and 17.9, with 32 images 25.0 and 23.2; 40 -> 168 14.8 and 15.9, 18.9 and
+// 20.4, with 61 images 27.6 and 26.9.  3x3 (16.9 and 17.4) and int8 layers are even.
+bool patch_filters_fast(const ConvArgs &a, long M) { return M >= 16384 && (a.C > 64 || a.res || M >= 100000); }
+
 template <int TF, int TM, int CK, int R, int MAXP, int MINB, int NW, bool I8 = false>
 hipError_t launch_patch(const ConvArgs &a, hipStream_t s, const QuantArgs &q = QuantArgs{}) {
     constexpr int NT = 64 * NW, BN = 32 * TF, BM = 32 * NW * TM, NKG = CK / (I8 ? 16 : 8), WPS = BN + 4, ROWC = BN / 8 + 1;
@@ -465,8 +472,7 @@ hipError_t launch_patch(const ConvArgs &a, hipStream_t s, const QuantArgs &q = Q
     g.M = a.B * a.P * a.Q;
     g.tiles_m = (g.M + BM - 1) / BM;
     g.tiles_f = (a.K + BN - 1) / BN;
-    // (filters fast, us: 61 x 56 x 56, 56 -> 208 60.8 -> 54.5; with 16 images 64 -> 256 15.7 -> 18.0, 3x3 16.9 -> 17.4, int8 likewise)
-    g.order = tile_order(R == 1 && !I8 && g.M >= 100000, g.tiles_f, g.tiles_m);
+    g.order = tile_order(R == 1 && !I8 && patch_filters_fast(a, g.M), g.tiles_f, g.tiles_m);
     g.hp = a.H + 2 * a.pad, g.wp = a.W + 2 * a.pad;
     g.ps = ps;
     const size_t cells = std::max<size_t>(2 * (size_t)NKG * ps + 2 * (size_t)R * NKG * WPS, (size_t)BM * ROWC);

@@ -303,6 +303,39 @@ def test_int8_patch_kernel(arch, batch):
     np.testing.assert_array_equal(got, Q.forward_int8(arch, qm, cfg, np.ascontiguousarray(xq.transpose(0, 3, 1, 2))))
 
 
+# The patch kernel with its filter tiles next to each other (1x1, 16384 pixels and more) and pixel tiles next to each other (fewer),
+# ragged in both, against the other kernels bit for bit: images and weights are small integers, few weights per filter, so that all
+# sums stay below 2^24 and are exact whatever their order.
+@pytest.mark.parametrize("arch,batch", [(_bottleneck([136, 264], [1, 1], 112, 0.75), 21), (_bottleneck([136, 264], [1, 1], 112, 0.75), 20),
+                                        (_bottleneck([72, 200], [1, 2], 108, 1.0), 129)])
+def test_patch_kernel_tile_order(arch, batch):
+    import paper_2306_17266_amd as S
+    rng = np.random.default_rng(103)
+    tens = []
+    for name, shape, kind in S.sushi_describe_supernet(arch):
+        t = np.ones(shape) if kind in (T.KIND_SCALE, T.KIND_SCALE_RES) else rng.integers(-1, 2, shape)
+        if kind == T.KIND_CONV:
+            t = np.zeros(shape)
+            for k, row in enumerate(t.reshape(shape[0], -1)):
+                row[rng.choice(row.size, 4, False)] = rng.choice([-1.0, 1.0], 4)
+        tens.append(np.ascontiguousarray(t, dtype=np.float32))
+    x = torch.from_numpy(rng.integers(0, 3, (batch, arch.res_choices[0], arch.res_choices[0], 3)).astype(np.float32)).cuda().to(torch.bfloat16)
+    got = []
+    for pixels in (1, 0):  # the patch kernel wherever it covers a layer, and nowhere
+        ctx = S.Sushi(0)
+        ctx.sushi_load_supernet(arch, T.flatten(tens), S.BF16)
+        ctx.sushi_set_option(S.OPT_PATCH_CONV_MIN_PIXELS, pixels)
+        ctx.sushi_set_option(S.OPT_KERNEL_TIMING, 1)
+        y = torch.full((batch, arch.n_classes), float("nan"), device="cuda", dtype=torch.float32)
+        ctx.sushi_infer(A.max_cfg(arch), x, y)
+        torch.cuda.synchronize()
+        assert ("conv_patch_kernel" in [k["name"] for k in ctx.sushi_get_kernel_stats() if k["launches"]]) == (pixels == 1)
+        ctx.close()
+        got.append(y.cpu().numpy())
+    assert len(np.unique(got[0])) > got[0].size // 4
+    np.testing.assert_array_equal(got[0], got[1])
+
+
 # Maps of 2 GiB and more go to the kernels with 64-bit addresses.  An image's logits do not depend on the batch: four
 # images, repeated, against the same four alone.
 @pytest.mark.parametrize("kernel,dtype,batch,arch", [
