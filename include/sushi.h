@@ -309,9 +309,9 @@ int sushi_set_subgraph_cache(sushi_ctx *ctx, const sushi_subgraph_cfg *g, size_t
 int sushi_infer(sushi_ctx *ctx, const sushi_subnet_cfg *cfg, const void *input_dev, int batch, void *logits_dev);
 
 /* For callers that must not allocate device memory while they run (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): sushi_infer as exec mode 0 does it (one launch per layer, or few, on
- * the context's stream, float32 or bf16), with the activation buffers of the query in a static device array
- * of the library instead of the context's arena.  Calls no hipMalloc / hipFree and no allocating library
+ * serving loops, harnesses that forbid hipMalloc): sushi_infer as exec mode 0 does it (a launch per
+ * layer or per few layers that run fused, on the context's stream, float32 or bf16), with the activation
+ * buffers of the query in a static device array of the library instead of the context's arena.  Calls no hipMalloc / hipFree and no allocating library
  * routine; same arguments, results and error behaviour as sushi_infer.
  *   - The array holds SUSHI_STATIC_SCRATCH_BYTES per GPU for as long as the library is loaded.  A query whose
  *     SubNet needs more at its batch size and resolution (six feature-map buffers of its largest layer output

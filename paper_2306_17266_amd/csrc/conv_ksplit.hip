@@ -10,9 +10,10 @@
 // The partial tiles are added in LDS, 32 pixels at a time, in the order of the waves, and finished as 16-byte pieces (8 filters).
 //
 // Bound by the weights' way into a compute unit, 70 clocks a step for each 32 filters (four waves' KiB at 60 B per clock), whatever
-// the pixels: a ring of nine steps gains nothing.  16 x 14 x 14 x 360, us: 14.5 with 96 x 64 tiles (64 x 64 tiles whose
-// waves share operands through LDS, conv_tile.hip: 25.1); 16 x 7 x 7 x 720 17.9 (24.4), 61 x 14 x 14 x 256 19.5 (27.6 in the
-// patch kernel), int8 16 x 14 x 14 x 360 12 (16.5).
+// the pixels: a ring of nine steps gains nothing.  us, one layer over and over: 16 x 14 x 14 x 360 14.5 with 96 x 64 tiles (64 x
+// 64 tiles whose waves share operands through LDS, conv_tile.hip: 25.1); 16 x 7 x 7 x 720 17.9 (24.4), 61 x 14 x 14 x 256 19.5
+// (27.6 in the patch kernel), int8 16 x 14 x 14 x 360 12 (16.5).  Inside a query, its weights not in the caches: 16 x 14 x 14 x 360
+// 15.7 (25.9), 16 x 7 x 7 x 720 19.0 (24.5).
 #include "kernels.h"
 #include "device_common.h"
 
@@ -294,7 +295,8 @@ static hipError_t launch_ksplit_tile(const ConvArgs &a, const QuantArgs &q, hipS
 // other kernels goes.  By the rule below over 48 square layers of each width (7 x 7 to 56 x 56, 1 to 96 images, warm), us without
 // and with this kernel, and how many layers get slower by 3 % and more: bf16 80 channels 544 / 534, 88 570 / 553, 1 (24 x 28 x 28
 // 11.6 / 12.2), 96 577 / 554, 0, 104 737 / 710, 0 (16 x 28 x 28 11.4 / 9.7), 128 799 / 737, 0; int8 96 533 / 528, 1, 104 and 112
-// 595 / 591, 5 (12 x 28 x 28 9.2 / 11.1), 120 630 / 614, 1, 128 640 / 620, 1.
+// 595 / 591, 5 (12 x 28 x 28 9.2 / 11.1), 120 630 / 614, 1, 128 640 / 620, 1.  Inside queries 28 x 28 x 104 of 2 to 24 images takes
+// 79.3 / 69.6 in all, at the extremes 5.9 / 6.4 (2 images) and 17.1 / 12.2 (24).
 template <bool I8>
 static bool ksplit_covers(const ConvArgs &a) {
     const int es = I8 ? 1 : 2;

@@ -1770,7 +1770,7 @@ int sushi_infer_static(sushi_ctx *c, const sushi_subnet_cfg *cfg, const void *in
     }
     refresh_residency(c, *cp);
     c->stream_dirty = true;
-    // one launch per op on the context's stream; no events, no allocation
+    // launches on the context's stream; no events, no allocation
     const bool timing = c->timing;
     c->timing = false;
     e = issue_launches(c, *cp, input_dev, logits_dev, c->stream);
